@@ -261,6 +261,60 @@ def test_fused_concat_upsample_pool(shape):
     assert np.array_equal(host_u32(p1), bitref.pack_pm1(O.maxpool2x2(o1)))
 
 
+SPLIT_SHAPES = [
+    # N, H, W, Ca, Cb, upsample, Cout: Cb = 0 is a single input
+    (1, 1, 1, 64, 0, 0, 32),          # one pixel, one step, one slice
+    (1, 2, 3, 1024, 0, 0, 32),        # tiles 8 wide, eight slices of two steps
+    (3, 7, 6, 320, 0, 0, 96),         # five steps in four slices, three images
+    (1, 9, 17, 96, 0, 0, 64),         # tiles 16 wide (with the pooled output too), half a step at the end
+    (1, 5, 65, 40, 0, 0, 160),        # tiles 32 wide, Cin not a multiple of 32
+    (2, 33, 31, 128, 0, 0, 64),
+    (1, 31, 33, 512, 0, 0, 320),      # two groups per wave, ragged both ways
+    (1, 66, 63, 512, 0, 0, 512),      # four groups, S = 4
+    (1, 31, 32, 1024, 0, 0, 1024),    # four groups, S = 8
+    (1, 20, 8, 1024, 0, 0, 1024),     # no wider than the narrowest tile
+    (1, 5, 13, 32, 32, 0, 32),        # a step straddles the two inputs
+    (2, 9, 7, 64, 96, 0, 64),
+    (1, 21, 19, 512, 1024, 1, 64),    # up-sampled second input, a row and a column short
+    (1, 16, 12, 256, 320, 1, 32),
+]
+
+
+@pytest.mark.parametrize("shape", SPLIT_SHAPES)
+def test_small_layers_split_over_their_input_channels(shape):
+    """Shapes for which the automatic choice is the kernel that splits the input channels over a
+    block's waves, at the edges of its tiles and slices, with and without the pooled output;
+    tuning 7 runs the kernels for larger layers on the same calls."""
+    N, H, W, Ca, Cb, up, Cout = shape
+    say(f"conv split N={N} H={H} W={W} Ca={Ca} Cb={Cb} up={up} Cout={Cout}")
+    rng = np.random.default_rng(H * 100 + W)
+    a = synth.pm1_bits(rng, (N, H, W, Ca))
+    x, b = a, None
+    if Cb:
+        b = synth.pm1_bits(rng, (N, H >> up, W >> up, Cb) if up else (N, H - 1, W - 1, Cb))
+        x = O.concat(a, O.zero_pad_to(O.upsample2x(b) if up else b, H, W))
+    w = synth.ternary_weights(14, 0, 0, Cout, Ca + Cb, 0.6)
+    th = synth.thresholds(14, 0, 0, Cout, (9 * (Ca + Cb)) // 16)
+    _, out_ref = O.masked_binary_layer(x, w, th)
+    ref = bitref.pack_pm1(out_ref)
+    pool_ref = bitref.pack_pm1(O.maxpool2x2(out_ref)) if min(H, W) > 1 else None
+    pa, blob, thd = B.pack_act(dev(a)), B.pack_weights(dev(w)), dev(th)
+    pb = B.pack_act(dev(b)) if Cb else None
+    for mode in (0, 7):
+        B.set_conv_tuning(mode)
+        for pool in (False, True) if pool_ref is not None else (False,):
+            if Cb:
+                bits, pooled = B.conv3x3_masked_binary_two_inputs(pa, Ca, pb, Cb, bool(up), blob, Cout, thd, pool)
+            elif pool:
+                bits, pooled = B.conv3x3_masked_binary_fused(pa, Ca, None, 0, blob, Cout, thd, True, True)
+            else:
+                bits, pooled = B.conv3x3_masked_binary(pa, Ca, blob, Cout, thd)
+            torch.cuda.synchronize()
+            assert np.array_equal(host_u32(bits), ref), (mode, pool)
+            if pool:
+                assert np.array_equal(host_u32(pooled), pool_ref), mode
+
+
 UPCAT_SHAPES = [
     # N, H, W, Ca, Clow, Cout, keep: skip channels % 64 == 0 and low channels % 128 == 0
     (1, 16, 128, 64, 128, 64, 0.6),
