@@ -887,15 +887,15 @@ int launch_conv_mfma_two(const uint32_t *act, int Ca, const uint32_t *low, int C
                          int Hb, int Wb, int N, int H, int W, const BlobLayout &L, const void *blob,
                          const int32_t *thresh, uint32_t *out_bits, uint32_t *out_pool, hipStream_t s)
 {
+    if (low && low_shift == 1 && 2 * Hb == H && 2 * Wb == W && t_cfg.tune_rw != 1 &&
+        conv_upcat_supported(Ca, Clow, N, H, W, L, out_bits, out_pool))
+        return launch_conv_mfma_upcat(act, Ca, low, Clow, N, H, W, L, blob, thresh, out_bits, s);
     if (t_cfg.tune_rw == 0) {
         const SplitPlan p = conv_split_plan(N, H, W, L, low && low_shift, out_pool != nullptr);
         if (p.s)
             return launch_conv_mfma_split(p, act, ceil_div(Ca, 32), low, low ? ceil_div(Clow, 32) : 0, low ? low_shift : 0,
                                           low ? Hb : 0, low ? Wb : 0, N, H, W, L, blob, thresh, out_bits, out_pool, s);
     }
-    if (low && low_shift == 1 && 2 * Hb == H && 2 * Wb == W && t_cfg.tune_rw != 1 &&
-        conv_upcat_supported(Ca, Clow, N, H, W, L, out_bits, out_pool))
-        return launch_conv_mfma_upcat(act, Ca, low, Clow, N, H, W, L, blob, thresh, out_bits, s);
     if (!low && rows_kernel_waves() && conv_rows_supported(H, W, L, out_bits != nullptr))
         return launch_conv_mfma_rows(act, N, H, W, L, blob, thresh, out_bits, out_pool, rows_kernel_waves(), s);
     if (!low && use_rows2k(N, H, W, L, out_bits != nullptr))

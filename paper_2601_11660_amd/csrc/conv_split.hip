@@ -20,14 +20,12 @@ namespace mbu {
 // What bounds it: the tiny shapes by their latency chain (arguments, first fetch from beyond the L2, LDS,
 // about 1.5 us next to the 2.5 us of a dispatch); 1024->1024 at 32 x 32 spends 12 K cycles in a block: 1.2 K
 // issuing, 1.5 K for the first fetch, 4.6 K in the matrix loop (2 waves per SIMD: the matrix pipe is full),
-// 4.2 K in the reduction, 0.7 K storing.  us per launch in a kernel trace, before (block / up-sampled
-// decoder kernel) -> now:
+// 4.2 K in the reduction, 0.7 K storing.  us per launch in a kernel trace, before -> now:
 //   1024->1024 at 4x6 21.6 -> 5.2, at 32x32 22.3 -> 9.8;  512->1024 at 32x32 14.2 -> 6.5;
 //   512->512 at 8x12 13.2 -> 4.2, at 64x64 14.1 -> 10.0;  256->512 at 64x64 9.1 -> 7.0;
 //   256->256 at 16x24 8.7 -> 3.8;  128->128 at 32x48 7.3 -> 3.7;
-//   [512 | 1024 up]->512 at 8x12 24.2 -> 5.8, at 64x64 24.6 -> 16.6;  [512 | 512]->512 at 64x64 24.2 -> 13.8
-// (the up-sampled channels cost 9 taps here instead of the decoder kernel's 4: at these sizes filling
-// the chip is worth more).
+//   [512 | 512]->512 at 64x64 24.2 -> 13.8
+// (before: block kernel).  Up-sampled second inputs come here only where conv_upcat.hip does not take them.
 // Measured and not kept: the whole window of all steps staged by the block in one go (coalesced, but a
 // barrier and 2-3 dependent LDS passes before the first matrix instruction: 0.5-1 us slower on the tiny
 // shapes, no faster on the others); 64 output channels per wave (no faster: the reduction doubles).

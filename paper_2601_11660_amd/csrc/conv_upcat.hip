@@ -379,6 +379,253 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------------
+// The same contraction for small layers (a 512 x 512 frame's two deepest decoder levels, every level of a
+// smaller frame), where the kernel above has fewer waves than the chip has SIMDs and a wave's time is its
+// serial chain over the input steps.  The S waves of a block share one tile - one group of 32 low pixels
+// (TWC columns x 32 / TWC rows), NC parity classes, 32 output channels - and contract a slice of the input
+// steps each; the partial sums (half-integers, exact in any order) meet in LDS.  A wave with all four classes
+// stages the window once for them and uses a skip fragment of the weights four times (36 matrix instructions
+// for 9 + 16 fragments of weights and window), at the price of one use per low fragment; a wave with one class
+// spreads the fewest pixels over four times as many compute units, whose rate of weight fetches is
+// then the bound.  Every wave stages for itself: fetch of the next step's window and weights during a
+// step, expansion into the other of two LDS buffers in slots between the matrix instructions, bodies
+// instantiated per kind of the current and the next step (no branch in a slot).  A fetch beyond the slice
+// gets an offset outside the buffer and moves nothing.
+template <int NC, int TWC>
+struct UpSplitGeo {
+    static constexpr int RS = 32 / TWC;                       // low rows of the group
+    static constexpr int AR = 2 * RS + 2, AC = 2 * TWC + 2;   // skip window, columns split by parity
+    static constexpr int AROW = 4 * (TWC + 1);                // uint4 of a window row: [half][parity][TWC + 1]
+    static constexpr int BR = RS + 2, BC = TWC + 2;           // low window
+    static constexpr int BROW = 2 * BC;                       // uint4 of a window row: [half][BC]
+    static constexpr int NLA = (AR * AC + 63) / 64, NLB = (BR * BC + 63) / 64;
+    static constexpr int WIN = AR * AROW;                     // the larger of the two windows
+    static constexpr int PART = NC * 4 * 64;
+    static constexpr int WAVE = 2 * WIN > PART ? 2 * WIN : PART;
+    static constexpr int HEAD = 32 + NC * 32;                 // words: start values, output words
+    static int lds_bytes(int s) { return HEAD * 4 + s * WAVE * 16; }
+};
+
+template <int NC, int TWC>
+__global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
+    const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int ksA, int ksL,
+    const uint4 *__restrict__ wfrag, const uint4 *__restrict__ wup, int Cout, int ctiles, int tiles_x, int tiles_y,
+    const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum, uint32_t *__restrict__ out_bits)
+{
+    static_assert(NC == 1 || NC == 4, "one parity class or all of them");
+    using G = UpSplitGeo<NC, TWC>;
+    constexpr int NLA = G::NLA, NLB = G::NLB;
+    constexpr uint32_t NOWHERE = 0x7ffffff0u;
+    extern __shared__ uint4 lds[];
+    float *start = reinterpret_cast<float *>(lds);
+    uint32_t *words = reinterpret_cast<uint32_t *>(start + 32);   // [class][pixel]
+    uint4 *const body = lds + G::HEAD / 4;
+    const int S = blockDim.x >> 6;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int ct = blockIdx.x % ctiles;
+    const int rest = blockIdx.x / ctiles;
+    const int cls0 = NC == 1 ? rest & 3 : 0;
+    const TilePos tp = tile_pos(NC == 1 ? rest >> 2 : rest, tiles_x, tiles_y);
+    const int Y0 = tp.ty * G::RS, X0 = tp.tx * TWC;
+    const int Hl = H >> 1, Wl = W >> 1;
+    const int ksteps = ksA + ksL;
+    uint4 *const win = body + wave * G::WAVE;
+
+    // slice of the step sequence [skip steps | low steps], by matrix instructions (9 and 4 per class)
+    auto step_at = [&](int cost) {
+        return cost <= 9 * ksA ? (cost + 8) / 9 : ksA + (cost - 9 * ksA + 3) / 4;
+    };
+    const int total = 9 * ksA + 4 * ksL;
+    const int k_first = step_at(total * wave / S), k_end = step_at(total * (wave + 1) / S);
+
+    // ---- weights
+    const int m = ct & 1;
+    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(wfrag + (size_t)(ct >> 1) * ksteps * (18 * 64)), 0, ksteps * (18 * 1024), 0x00020000);
+    const __amdgpu_buffer_rsrc_t urs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(wup + (size_t)(ct >> 1) * ksteps * (32 * 64)), 0, ksteps * (32 * 1024), 0x00020000);
+    constexpr int NWL = 4 * NC, NW = NWL > 9 ? NWL : 9;
+    v4i Wg[NW];   // skip step: [kx][ky]; low step: [class][a][b]
+    auto load_w = [&](auto is_low, bool want, int ks, int i) {
+        const uint32_t off = want ? lane * 16 : NOWHERE;
+        const auto w = decltype(is_low)::value
+                           ? __builtin_amdgcn_raw_buffer_load_b128(urs, off, (ks * 32 + (cls0 * 4 + i) * 2 + m) * 1024, 0)
+                           : __builtin_amdgcn_raw_buffer_load_b128(
+                                 wrs, off, (ks * 18 + ((i % 3) * 3 + i / 3) * 2 + m) * 1024, 0);
+        Wg[i] = (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+    };
+
+    // ---- staging plans: pixels lane + 64 * j of either window (surplus lanes duplicate pixel 0)
+    const __amdgpu_buffer_rsrc_t ars =
+        __builtin_amdgcn_make_buffer_rsrc((void *)act, 0, (int)((size_t)N * H * W * ksA * 8), 0x00020000);
+    const __amdgpu_buffer_rsrc_t brs =
+        __builtin_amdgcn_make_buffer_rsrc((void *)low, 0, (int)((size_t)N * Hl * Wl * ksL * 8), 0x00020000);
+    uint32_t offa[NLA], offb[NLB], in_a = 0, in_b = 0;
+#pragma unroll
+    for (int j = 0; j < NLA; ++j) {
+        int p = lane + 64 * j;
+        p = p < G::AR * G::AC ? p : 0;
+        const int y = 2 * Y0 - 1 + p / G::AC, x = 2 * X0 - 1 + p % G::AC;
+        in_a |= (y >= 0 && y < H && x >= 0 && x < W ? 1u : 0u) << j;
+        offa[j] = (uint32_t)((((size_t)tp.n * H + min(max(y, 0), H - 1)) * W + min(max(x, 0), W - 1)) * ksA * 8);
+    }
+#pragma unroll
+    for (int j = 0; j < NLB; ++j) {
+        int p = lane + 64 * j;
+        p = p < G::BR * G::BC ? p : 0;
+        const int y = Y0 - 1 + p / G::BC, x = X0 - 1 + p % G::BC;
+        in_b |= (y >= 0 && y < Hl && x >= 0 && x < Wl ? 1u : 0u) << j;
+        offb[j] = (uint32_t)((((size_t)tp.n * Hl + min(max(y, 0), Hl - 1)) * Wl + min(max(x, 0), Wl - 1)) * ksL * 8);
+    }
+    uint2 gq[NLA];
+    auto fetch = [&](auto is_low, bool want, int ks) {
+        constexpr bool LOW = decltype(is_low)::value;
+#pragma unroll
+        for (int j = 0; j < (LOW ? NLB : NLA); ++j) {
+            const auto v = LOW ? __builtin_amdgcn_raw_buffer_load_b64(brs, want ? offb[LOW ? j : 0] : NOWHERE, (ks - ksA) * 8, 0)
+                               : __builtin_amdgcn_raw_buffer_load_b64(ars, want ? offa[j] : NOWHERE, ks * 8, 0);
+            gq[j] = make_uint2(v[0], v[1]);
+        }
+    };
+    auto commit = [&](auto is_low, uint4 *buf, int i) {   // word i & 1 of staged pixel i >> 1
+        constexpr bool LOW = decltype(is_low)::value;
+        const int j = i >> 1, h = i & 1;
+        int p = lane + 64 * j;
+        p = p < (LOW ? G::BR * G::BC : G::AR * G::AC) ? p : 0;
+        const int r = p / (LOW ? G::BC : G::AC), c = p % (LOW ? G::BC : G::AC);
+        const bool in = ((LOW ? in_b : in_a) >> j) & 1u;
+        buf[LOW ? r * G::BROW + h * G::BC + c : r * G::AROW + (h * 2 + (c & 1)) * (TWC + 1) + (c >> 1)] =
+            expand_word_masked(h ? gq[j].y : gq[j].x, in ? 0x22222222u : 0u, in ? 0u : 0x11111111u);
+    };
+
+    v16f acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][i] = 0.0f;
+
+    // One step.  Slot j: window fragment j, at position (row j % n, column j / n) of the n x n positions the
+    // classes' taps fall on; the matrix instructions that use it; then the refill of the weights of which this
+    // was the last use, and, in the last slots, one word of the next step's window.
+    constexpr int NB = 3;
+    const int lr = col / TWC, lc = col % TWC;
+    const int dy0 = cls0 >> 1, dx0 = cls0 & 1;
+    auto step = [&](auto is_low, auto next_low, int ks, const uint4 *cur, uint4 *nxt) {
+        constexpr bool LOW = decltype(is_low)::value, NLOW = decltype(next_low)::value;
+        constexpr int K = LOW ? 2 : 3, P = K + (NC == 4 ? 1 : 0), NF = P * P;
+        const bool more = ks + 1 < k_end;
+        fetch(next_low, more, ks + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        auto frag = [&](int j) {
+            const int pr = j % P, pc = j / P;
+            uint4 b;
+            if (LOW) {
+                b = cur[(lr + dy0 + pr) * G::BROW + half * G::BC + lc + dx0 + pc];
+            } else {
+                const int x = dx0 + pc;
+                b = cur[(2 * lr + dy0 + pr) * G::AROW + (half * 2 + (x & 1)) * (TWC + 1) + lc + (x >> 1)];
+            }
+            return (v4i){(int)b.x, (int)b.y, (int)b.z, (int)b.w};
+        };
+        v4i fr[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) fr[j] = frag(j);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            const int pr = j % P, pc = j / P;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int ky = pr - (c >> 1), kx = pc - (c & 1);
+                if (ky >= 0 && ky < K && kx >= 0 && kx < K)
+                    acc[c] = mfma_f4(Wg[LOW ? c * 4 + ky * 2 + kx : kx * 3 + ky], fr[j % NB], acc[c]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (j + NB < NF) fr[j % NB] = frag(j + NB);
+            if (LOW) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const int ky = pr - (c >> 1), kx = pc - (c & 1);
+                    if (ky >= 0 && ky < K && kx >= 0 && kx < K) load_w(next_low, more, ks + 1, c * 4 + ky * 2 + kx);
+                }
+            } else {
+                const int ky = pr - (P - K), kx = pc - (P - K);
+                if (ky >= 0 && kx >= 0) {
+                    if (!NLOW || kx * 3 + ky < NWL) load_w(next_low, more, ks + 1, kx * 3 + ky);
+                    if (NLOW && 9 + kx * 3 + ky < NWL) load_w(next_low, more, ks + 1, 9 + kx * 3 + ky);
+                }
+            }
+            // the words of the next window over the last slots
+            constexpr int NWORD = 2 * (NLOW ? NLB : NLA), PER = (NWORD + NF - 1) / NF, FROM = NF - (NWORD + PER - 1) / PER;
+            if (j >= FROM)
+#pragma unroll
+                for (int i = (j - FROM) * PER; i < (j - FROM + 1) * PER && i < NWORD; ++i) commit(next_low, nxt, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    constexpr std::true_type LOW_STEP{};
+    constexpr std::false_type SKIP_STEP{};
+    if (k_first < k_end) {
+        if (k_first < ksA) {
+            fetch(SKIP_STEP, true, k_first);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) load_w(SKIP_STEP, true, k_first, i);
+#pragma unroll
+            for (int i = 0; i < 2 * NLA; ++i) commit(SKIP_STEP, win, i);
+        } else {
+            fetch(LOW_STEP, true, k_first);
+#pragma unroll
+            for (int i = 0; i < NWL; ++i) load_w(LOW_STEP, true, k_first, i);
+#pragma unroll
+            for (int i = 0; i < 2 * NLB; ++i) commit(LOW_STEP, win, i);
+        }
+    }
+    if (tid < 32) start[tid] = start_value(thresh[ct * 32 + tid], wsum[ct * 32 + tid]);
+    for (int i = tid; i < NC * 32; i += 64 * S) words[i] = 0;
+    auto cur = [&](int ks) { return win + ((ks - k_first) & 1) * G::WIN; };
+    int ks = k_first;
+    // skip steps that a skip step or nothing follows, the one before the first low step, low steps
+    const int skips = k_end <= ksA ? k_end : ksA - 1;
+    for (; ks < skips; ++ks) step(SKIP_STEP, SKIP_STEP, ks, cur(ks), cur(ks + 1));
+    if (ks < ksA && ks < k_end) {
+        step(SKIP_STEP, LOW_STEP, ks, cur(ks), cur(ks + 1));
+        ++ks;
+    }
+    for (; ks < k_end; ++ks) step(LOW_STEP, LOW_STEP, ks, cur(ks), cur(ks + 1));
+
+    // ---- sum over the slices, in the place of the wave's windows; a unit is four channels of one class
+    float4 *const part = reinterpret_cast<float4 *>(win);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            part[(c * 4 + q) * 64 + lane] =
+                make_float4(acc[c][4 * q], acc[c][4 * q + 1], acc[c][4 * q + 2], acc[c][4 * q + 3]);
+    __syncthreads();
+    for (int u = wave; u < NC * 4; u += S) {
+        const int q = u & 3;
+        float4 v = *reinterpret_cast<const float4 *>(start + 16 * half + 4 * q);
+        const float4 *src = reinterpret_cast<const float4 *>(body) + u * 64 + lane;
+        for (int s = 0; s < S; ++s) {
+            const float4 t = src[s * G::WAVE];
+            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+        }
+        const uint32_t nib = (v.x >= 0.0f ? 1u : 0u) | (v.y >= 0.0f ? 2u : 0u) | (v.z >= 0.0f ? 4u : 0u) |
+                             (v.w >= 0.0f ? 8u : 0u);
+        atomicOr(&words[(u >> 2) * 32 + col], nib << (16 * half + 4 * q));
+    }
+    __syncthreads();
+    const int Cow = Cout >> 5;
+    for (int i = tid; i < NC * 32; i += 64 * S) {
+        const int c = cls0 + (i >> 5), p = i & 31;
+        const int y = 2 * (Y0 + p / TWC) + (c >> 1), x = 2 * (X0 + p % TWC) + (c & 1);
+        if (y < H && x < W) out_bits[(((size_t)tp.n * H + y) * W + x) * Cow + ct] = words[i];
+    }
+}
+
 // Combined weights of the up-sampled channels.  Thread (o, class, a, b, word k) sums the taps
 // of the 3x3 kernel that fall on low pixel (a, b) of class (dy, dx) for 32 input channels and
 // stores the E2M1 codes of the sums as one
@@ -436,6 +683,49 @@ bool conv_upcat_supported(int Ca, int Clow, int N, int H, int W, const BlobLayou
            (double)L.ksteps * 32 * 1024 < lim;
 }
 
+// When, and with which tile (kernel trace, caches flushed between launches, us with the large kernel -> with
+// the best tile here):
+//  - The large kernel runs waves of 4 x 32 low pixels x one class x 64 channels.  Below 512 of them this one
+//    wins ([512 | 1024]->512 at 64x64, 256 waves, 25.5 -> 15.6; [256 | 512]->256 at 80x120, 320, 16.0 -> 13.0;
+//    [128 | 256]->128 at 120x160, 360, 11.6 -> 10.6; [64 | 128]->64 at 120x160, 180, 8.4 -> 6.5); at 512 with
+//    many steps still (128x128, 12 steps, 16.0 -> 14.5), with few no more (256x256, 3 steps, 7.8 -> 8.4).
+//  - One class per wave up to 40000 matrix instructions in all ([512 | 1024]->512 at 8x12, 8704, 26.0 -> 6.0
+//    against 8.3 with four; [64 | 128]->64 at 120x160, 20400, 6.5 against 7.7), four beyond
+//    (81600, [128 | 256]->128 at 120x160, 10.6 against 11.6; 104448, 30x40, 24.9 -> 8.6 against 12.0).
+//  - Fewest groups; of equals the narrow ones, whose window has fewer pixels.
+//  - As many slices as stay within 2048 waves (two per SIMD), at most 8 and one per step.
+struct UpSplitPlan {
+    int nc, tw, s;   // s = 0: the large kernel
+};
+static UpSplitPlan upcat_split_plan(int N, int Hl, int Wl, int ksA, int ksL, const BlobLayout &L)
+{
+    UpSplitPlan p{0, 0, 0};
+    const long other = 4L * N * ceil_div(Hl, UC_RW) * ceil_div(Wl, 32) * (L.cout_pad64 / 64);
+    const int ksteps = ksA + ksL;
+    if (other > 512 || (other == 512 && ksteps < 12)) return p;
+    const long g8 = (long)N * ceil_div(Wl, 8) * ceil_div(Hl, 4), g16 = (long)N * ceil_div(Wl, 16) * ceil_div(Hl, 2);
+    p.tw = g8 <= g16 ? 8 : 16;
+    const long tiles = std::min(g8, g16) * (L.cout >> 5);
+    p.nc = tiles * (36 * ksA + 16 * ksL) <= 40000 ? 1 : 4;
+    const long blocks = tiles * (4 / p.nc);
+    p.s = 1;
+    while (p.s < 8 && 2 * p.s <= ksteps && blocks * 2 * p.s <= 2048) p.s *= 2;
+    return p;
+}
+
+template <int NC, int TWC>
+static int launch_upcat_split(int slices, const uint32_t *act, int Ca, const uint32_t *low, int Clow, int N, int H, int W,
+                              const BlobLayout &L, const uint4 *wfrag, const uint4 *wup, const int32_t *thresh,
+                              const int32_t *wsum, uint32_t *out_bits, hipStream_t s)
+{
+    using G = UpSplitGeo<NC, TWC>;
+    const int tiles_x = ceil_div(W / 2, TWC), tiles_y = ceil_div(H / 2, G::RS), ctiles = L.cout >> 5;
+    MBU_LAUNCH((conv_mfma_upcat_kernel<NC, TWC>), dim3((unsigned)((long)N * tiles_x * tiles_y * ctiles * (4 / NC))),
+               dim3(64 * slices), (size_t)G::lds_bytes(slices), s, act, low, N, H, W, Ca / 64, Clow / 64, wfrag, wup,
+               L.cout, ctiles, tiles_x, tiles_y, thresh, wsum, out_bits);
+    return check_launch("conv_mfma_upcat_split");
+}
+
 int launch_conv_mfma_upcat(const uint32_t *act, int Ca, const uint32_t *low, int Clow, int N, int H, int W,
                            const BlobLayout &L, const void *blob, const int32_t *thresh, uint32_t *out_bits,
                            hipStream_t s)
@@ -444,6 +734,17 @@ int launch_conv_mfma_upcat(const uint32_t *act, int Ca, const uint32_t *low, int
     const uint4 *wup = (const uint4 *)((const uint8_t *)blob + L.off_up);
     // sums of the weights per output channel: row 10 of the count section
     const int32_t *wsum = (const int32_t *)((const uint8_t *)blob + L.off_cnt) + (size_t)10 * L.cout_pad64;
+    if (t_cfg.tune_rw == 0) {
+        const UpSplitPlan p = upcat_split_plan(N, H / 2, W / 2, Ca / 64, Clow / 64, L);
+#define MBU_GO(NC_, TW_)                                                                                        \
+    if (p.nc == NC_ && p.tw == TW_)                                                                             \
+        return launch_upcat_split<NC_, TW_>(p.s, act, Ca, low, Clow, N, H, W, L, wfrag, wup, thresh, wsum, out_bits, s)
+        MBU_GO(1, 8);
+        MBU_GO(1, 16);
+        MBU_GO(4, 8);
+        MBU_GO(4, 16);
+#undef MBU_GO
+    }
     const int tiles64 = L.cout_pad64 / 64;
     const int tiles_x = ceil_div(W / 2, 32), tiles_y = ceil_div(H / 2, UC_RW);
     const long tiles = (long)N * tiles_y * tiles_x;

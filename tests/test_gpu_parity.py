@@ -360,6 +360,40 @@ def test_upsampled_decoder_kernel_matches_oracle(shape):
             assert np.array_equal(host_u32(b1), bitref.pack_pm1(ref1))
 
 
+@pytest.mark.parametrize("shape", [
+    # N, H, W, Ca, Clow, Cout
+    (1, 2, 2, 64, 128, 32),           # one low pixel, one class per wave
+    (2, 10, 18, 64, 128, 96),         # tiles 8 wide, ragged; slices that begin with a low step
+    (1, 4, 34, 192, 128, 64),         # tiles 16 wide; a slice of skip steps only
+    (1, 14, 30, 512, 1024, 512),      # all classes per wave, eight slices
+    (1, 2, 200, 256, 512, 512),       # the same, 16 wide
+    (1, 62, 62, 512, 1024, 512),      # four slices
+])
+def test_small_upsampled_decoder_layers(shape):
+    """Decoder layers over [skip | 2x up-sampled low] small enough for the kernel whose waves split
+    the input steps, with every summed tap at its extreme too; tuning 7 takes the kernel for larger
+    layers on the same call."""
+    N, H, W, Ca, Clow, Cout = shape
+    say(f"conv upcat split N={N} H={H} W={W} Ca={Ca} Clow={Clow} Cout={Cout}")
+    rng = np.random.default_rng(H * 100 + W)
+    skip = synth.pm1_bits(rng, (N, H, W, Ca))
+    low = synth.pm1_bits(rng, (N, H // 2, W // 2, Clow))
+    x = O.concat(skip, O.upsample2x(low))
+    th = synth.thresholds(15, 0, 0, Cout, (9 * (Ca + Clow)) // 16)
+    pa, pl = B.pack_act(dev(skip)), B.pack_act(dev(low))
+    weights = [synth.ternary_weights(15, 0, 0, Cout, Ca + Clow, 0.6)]
+    if Cout * (Ca + Clow) < 100000:
+        weights += [np.ones_like(weights[0]), -np.ones_like(weights[0])]
+    for w in weights:
+        _, out_ref = O.masked_binary_layer(x, w, th)
+        ref, blob = bitref.pack_pm1(out_ref), B.pack_weights(dev(w))
+        for mode in (0, 7):
+            B.set_conv_tuning(mode)
+            bits, _ = B.conv3x3_masked_binary_fused(pa, Ca, pl, Clow, blob, Cout, dev(th), True, False)
+            torch.cuda.synchronize()
+            assert np.array_equal(host_u32(bits), ref), mode
+
+
 TCONV_SHAPES = [
     # N, H, W, Cin, Cout
     (1, 8, 32, 128, 64),
