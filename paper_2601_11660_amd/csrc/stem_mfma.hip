@@ -465,12 +465,19 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 //     h = 1:  P2[j] P2[j+1] P2[j+2] R2[j]  |  R2[j+1] R2[j+2] R01[j+2] (1.0, 0)
 // The last dword is the constant that gives an all-zero weight row a decidable estimate (see
 // the kernel above).  The weights are loaded in the same order.
+// Bound by the vector ALU: about 165 vector instructions a tile against 12 matrix instructions, which
+// it does not overlap (counters at 1024x2048: matrix 32 %, vector 66 % of the SIMD cycles).  The
+// undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, and a block's
+// waves share the preparation of the weights: 41.0 -> 40.1 us at 1024x2048, 315 -> 306 us at
+// 32x640x959, 2 us of a 64x96 network's 87.
 constexpr int SR_HW = 34;                    // halo pixels of a strip
 constexpr int SR_ARR = 36;                   // dwords per LDS array (34 used)
 constexpr int SR_PLANE = 5 * SR_ARR;         // arrays P0 P1 R01 P2 R2 of one plane (hi or lo)
 constexpr int SR_CONST = SR_PLANE - 1;       // spare dword of R2: the constant entry
 constexpr int SR_N = 2 * SR_PLANE;           // per halo pixel: squared column norm, OR of the bits
-constexpr int SR_WAVE = SR_N + 2 * SR_ARR;   // dwords per wave
+constexpr int SR_Q = SR_N + 2 * SR_ARR;       // undecided outputs that wait for their sequential sums
+constexpr int SR_QCAP = 192;
+constexpr int SR_WAVE = SR_Q + SR_QCAP;      // dwords per wave
 constexpr float SR_FLOOR = 0x1p-9f;
 
 // index into the 27 weights of an output channel for half h, dword dh = 4t + d, fp16 value e;
@@ -508,13 +515,14 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 {
     constexpr int KV = 27;
     __shared__ uint32_t lds[4][SR_WAVE];
+    __shared__ uint4 wts[2][2][2][64];         // [hi, lo][tile][block of K][lane]
+    __shared__ uint32_t wnorm[2], winsane[2];  // per tile: largest scaled norm; a norm out of range
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gw = blockIdx.x * 4 + wave;
-    if (gw >= units) return;                   // whole wave leaves; nothing is shared
+    const int chunk = blockIdx.x % nchunks;    // 64 output channels of the block
+    const int gw = blockIdx.x / nchunks * 4 + wave;
     int q = gw;
-    const int chunk = q % nchunks; q /= nchunks;   // 64 output channels
     const int sx = q % strips; q /= strips;        // strip of 32 pixel columns
     const int sg = q % nseg;                       // segment of seg_rows image rows
     const int n = q / nseg;
@@ -524,12 +532,11 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const int rows = min(H, y0 + seg_rows) - y0;
     const int x0 = sx * 32;
 
-    // ---- weights: rows scaled to a norm in [2^12, 2^13), split once, in the K order above
-    uint4 Wh[2][2], Wl[2][2];
-    uint32_t rb = 0;
-    bool w_sane = true;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
+    // ---- weights: rows scaled to a norm in [2^12, 2^13), split once, in the K order above.  Wave w
+    // prepares tile w & 1, block w >> 1 of K (the norm needs the whole row) and the block shares them:
+    // a quarter of the 32 splits each, which is what a short segment otherwise spends its time on.
+    {
+        const int m = wave & 1, t = wave >> 1;
         const int ch = chunk * 64 + m * 32 + tile_row_to_channel(col);
         float v[16];
         float part = 0.0f;
@@ -544,23 +551,34 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         }
         const float nrm = __builtin_sqrtf(swap_add(part));
         const bool in_range = nrm >= 0x1p-60f && nrm <= 0x1p60f;
-        if (!(in_range || nrm == 0.0f)) w_sane = false;
         const float sc = in_range ? norm_scale(nrm) : 1.0f;
         if (nrm == 0.0f && ch < Co && half == 1) v[14] = 0x1p13f;   // the constant term (dword 7)
-        rb = max(rb, __float_as_uint(nrm * sc));
+        uint32_t h4[4], l4[4];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            uint32_t h4[4], l4[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-                split_pair(v[8 * t + 2 * d] * sc, v[8 * t + 2 * d + 1] * sc, h4[d], l4[d]);
-            Wh[m][t] = make_uint4(h4[0], h4[1], h4[2], h4[3]);
-            Wl[m][t] = make_uint4(l4[0], l4[1], l4[2], l4[3]);
+        for (int d = 0; d < 4; ++d)
+            split_pair((t ? v[8 + 2 * d] : v[2 * d]) * sc, (t ? v[9 + 2 * d] : v[2 * d + 1]) * sc, h4[d], l4[d]);
+        wts[0][m][t][lane] = make_uint4(h4[0], h4[1], h4[2], h4[3]);
+        wts[1][m][t][lane] = make_uint4(l4[0], l4[1], l4[2], l4[3]);
+        const uint32_t rb = wave_umax(__float_as_uint(nrm * sc));
+        const bool insane = __builtin_amdgcn_ballot_w64(!(in_range || nrm == 0.0f)) != 0;
+        if (t == 0 && lane == 0) {
+            wnorm[m] = rb;
+            winsane[m] = insane ? 1u : 0u;
         }
     }
-    rb = wave_umax(rb);
-    const float KW = STEM_KAPPA * 1.002f * __uint_as_float(rb);   // margin: the patch norm is good to 2^-10
-    w_sane = __builtin_amdgcn_ballot_w64(!w_sane) == 0;
+    __syncthreads();
+    if (gw >= units) return;                   // whole wave leaves; nothing is shared from here on
+    uint4 Wh[2][2], Wl[2][2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            Wh[m][t] = wts[0][m][t][lane];
+            Wl[m][t] = wts[1][m][t][lane];
+        }
+    // (margin: the patch norm is good to 2^-10)
+    const float KW = STEM_KAPPA * 1.002f * __uint_as_float(max(wnorm[0], wnorm[1]));
+    const bool w_sane = (winsane[0] | winsane[1]) == 0;
 
     // ---- addresses.  Staging: lane p < 34 owns halo pixel p (image column x0 - 1 + p); the
     // other lanes repeat pixel 33.  Zero padding: a column or row outside the image gets an
@@ -704,6 +722,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         }
     };
 
+    int qn = 0;   // entries of the list of undecided outputs
     // ---- decision and store of a finished row
     struct Done { float T; bool zero; int i; };
     struct Epi { float mn; uint32_t sg[2]; };
@@ -737,18 +756,36 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
             const float T = dn.T;
             const bool live = xo < W && dn.i >= 0 && dn.i < rows;
             const bool flag = live && !dn.zero && !(ep.mn > T);
-            // ---- sequential route for the undecided outputs (rare)
+            // ---- sequential route for the undecided outputs (rare): a few of them are put on the wave's
+            // list and summed later, one per lane, instead of in the lane that found them with 63 idle
+            // (their bits are provisional until then); a tile with many (unusual data) sums in place
             if (__builtin_amdgcn_ballot_w64(flag) != 0) {
-                if (flag) {
-                    uint32_t fl[2];
+                uint32_t fl[2] = {0, 0};
+                if (flag)
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
-                        fl[m] = 0;
 #pragma unroll
                         for (int e = 0; e < 16; ++e)
                             fl[m] |= (!(__builtin_fabsf(acc[m][e]) > T) ? 1u : 0u) << e;
                         if (chunk * 64 + m * 32 + 16 * half >= Co) fl[m] = 0;
                     }
+                uint32_t todo = fl[0] | fl[1] << 16;
+                if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(todo != 0)) <= 16 &&
+                    __builtin_amdgcn_ballot_w64(__builtin_popcount(todo) > 4) == 0) {
+                    uint64_t who;
+                    while ((who = __builtin_amdgcn_ballot_w64(todo != 0)) != 0) {
+                        if (todo) {
+                            const int b = __builtin_ctz(todo);
+                            todo &= todo - 1;
+                            const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0));
+                            // channel of the chunk: tile b / 16, half, register b % 16
+                            ldsw[SR_Q + qn + at] =
+                                (uint32_t)dn.i << 11 | (uint32_t)((b >> 4) * 32 + 16 * half + (b & 15)) << 5 | (uint32_t)col;
+                        }
+                        qn += __builtin_popcountll(who);
+                    }
+                } else if (flag) {
                     const uint32_t pb = (uint32_t)((((size_t)n * 3 * H + y) * W + xo) * 4);
                     // the 27 patch values of this pixel, fetched once and in one batch (a tap
                     // outside the image is skipped in the chain below)
@@ -862,10 +899,47 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 #pragma unroll
         for (int k = 0; k < STAGE_PIECES; ++k) stage_piece(k, a, rm, st, B0);
     }
-    // two rows per trip (operand planes and fetch registers alternate); with an odd row count the
-    // second row of the last trip is computed and dropped
+    // the listed outputs, one per lane: the sum in its defined order (ky, kx, ci), then the bit
+    auto flush = [&]() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the words with the provisional bits are out
+        for (int b = 0; b < qn; b += 64)
+            if (b + lane < qn) {
+                const uint32_t en = ldsw[SR_Q + b + lane];
+                const int y = y0 + (int)(en >> 11), x = x0 + (int)(en & 31u), ch = chunk * 64 + (int)(en >> 5 & 63u);
+                float sum = 0.0f;
 #pragma unroll 1
-    for (int i = 0; i < rows; i += 2) {
+                for (int ky = 0; ky < 3; ++ky) {
+                    const int yy = y + ky - 1;
+                    float pv[9], wv[9];
+#pragma unroll
+                    for (int u = 0; u < 9; ++u) {
+                        const int xx = x + u / 3 - 1;
+                        const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
+                        const uint32_t o = (uint32_t)(((((size_t)n * 3 + u % 3) * H + yy) * W + xx) * 4);
+                        pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, ok ? o : OOB, 0, 0));
+                        wv[u] = w[(size_t)ch * KV + ky * 9 + u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 9; ++u) {
+                        const int xx = x + u / 3 - 1;
+                        const float f = __builtin_fmaf(wv[u], pv[u], sum);
+                        sum = yy >= 0 && yy < H && xx >= 0 && xx < W ? f : sum;   // a tap outside is skipped
+                    }
+                }
+                uint32_t *const word = out + (((size_t)n * H + y) * W + x) * Cow + (ch >> 5);
+                if (sum >= 0.0f) atomicOr(word, 1u << (ch & 31));
+                else atomicAnd(word, ~(1u << (ch & 31)));   // NaN -> bit 0
+            }
+        qn = 0;
+    };
+    // two rows per trip (operand planes and fetch registers alternate); with an odd row count the
+    // second row of the last trip is computed and dropped.  A row lists at most 64 outputs.
+#pragma unroll 1
+    for (int i = 0;; i += 2) {
+        if (i >= rows || qn > SR_QCAP - 128) {
+            flush();
+            if (i >= rows) break;
+        }
         tile(i, B0, B1, a, rm, ld0);
         tile(i + 1, B1, B0, a, rm, ld1);
     }
@@ -883,9 +957,9 @@ static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int 
     int seg_rows = ceil_div(H, want);
     seg_rows = std::max(2, seg_rows + (seg_rows & 1));
     const int nseg = ceil_div(H, seg_rows);
-    const long units = base * nseg;
-    if (units > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");
-    MBU_LAUNCH(stem_rows_kernel, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, s, img, bytes, H, W, w, Co,
+    const long units = (long)N * strips * nseg;   // of every chunk
+    if ((units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");
+    MBU_LAUNCH(stem_rows_kernel, dim3((unsigned)((units + 3) / 4 * nchunks)), dim3(256), 0, s, img, bytes, H, W, w, Co,
                nchunks, strips, nseg, seg_rows, (int)units, out_bits);
     return check_launch("stem_rows");
 }

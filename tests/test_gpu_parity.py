@@ -1021,6 +1021,31 @@ def test_stem_degenerate_inputs(path, pname):
     check_stem(img, rng.standard_normal((Co, 3, 3, 3), dtype=np.float32), path, pname, "non-finite")
 
 
+@pytest.mark.parametrize("ties", [1, 8, 64])
+def test_stem_lists_of_undecided_outputs(ties):
+    """Row-walking kernel: integer images and weight rows that are the difference of two taps give
+    exact zeros at a known rate, few enough per tile for the wave's list (1 and 8 such rows; segments
+    long enough to fill it several times) or too many of them (64).  Against the chain kernel."""
+    say(f"stem lists ties={ties}")
+    rng = np.random.default_rng(ties)
+    n, h, w = 64, 131, 1024
+    img = dev(rng.integers(-100, 101, (n, 3, h, w)).astype(np.float32))
+    wts = rng.standard_normal((64, 27)).astype(np.float32)
+    for o in range(ties):
+        wts[o] = 0
+        i, j = rng.choice(27, 2, replace=False)
+        wts[o, i], wts[o, j] = 1, -1
+    wd = dev(wts.reshape(64, 3, 3, 3))
+    bits, _ = B.stem_fp32(img, wd)
+    B.set_stem_path(B.STEM_VALU)
+    try:
+        ref, _ = B.stem_fp32(img, wd)
+        torch.cuda.synchronize()
+    finally:
+        B.set_stem_path(B.STEM_AUTO)
+    assert torch.equal(bits, ref)
+
+
 def test_stem_full_size_frame():
     """All 134 M outputs of the benchmark frame's first layer against the oracle."""
     case = synth.unet_case(3, 0, 1, 1024, 2048, keep=0.6)
