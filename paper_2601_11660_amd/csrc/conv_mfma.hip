@@ -862,7 +862,7 @@ int launch_conv_mfma(const uint32_t *act, int N, int H, int W, const BlobLayout 
     const int mode = t_cfg.tune_rw;   // 0 = automatic; see mbu_set_conv_tuning
     if (mode == 0) {
         const SplitPlan p = conv_split_plan(N, H, W, L, false, false);
-        if (p.s)
+        if (p.r)
             return launch_conv_mfma_split(p, act, L.cin_words, nullptr, 0, 0, 0, 0, N, H, W, L, blob, thresh, out_bits,
                                           nullptr, s);
     }
@@ -892,7 +892,7 @@ int launch_conv_mfma_two(const uint32_t *act, int Ca, const uint32_t *low, int C
         return launch_conv_mfma_upcat(act, Ca, low, Clow, N, H, W, L, blob, thresh, out_bits, s);
     if (t_cfg.tune_rw == 0) {
         const SplitPlan p = conv_split_plan(N, H, W, L, low && low_shift, out_pool != nullptr);
-        if (p.s)
+        if (p.r)
             return launch_conv_mfma_split(p, act, ceil_div(Ca, 32), low, low ? ceil_div(Clow, 32) : 0, low ? low_shift : 0,
                                           low ? Hb : 0, low ? Wb : 0, N, H, W, L, blob, thresh, out_bits, out_pool, s);
     }

@@ -46,14 +46,14 @@ struct SplitGeo {
 template <int R, int TWC, bool EVEN, bool TWO>
 __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
     const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int Cwa, int Cwb,
-    int low_shift, int Hb, int Wb, int ksteps, const uint4 *__restrict__ wfrag, int Cout, int ctiles, int tiles_x,
-    int tiles_y, const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum,
+    int low_shift, int Hb, int Wb, int ksteps, const uint4 *__restrict__ wfrag, int Cout, int log_s, int tiles_y,
+    const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum,
     uint32_t *__restrict__ out_bits, uint32_t *__restrict__ out_pool)
 {
     using G = SplitGeo<R, TWC>;
     constexpr int RS = G::RS, HW = G::HW, NLD = G::NLD;
     extern __shared__ uint4 lds[];
-    const int S = blockDim.x >> 6;
+    const int S = 1 << log_s;
     float *start = reinterpret_cast<float *>(lds);
     uint32_t *words = reinterpret_cast<uint32_t *>(start + 32);
     uint4 *const body = lds + G::HEAD / 4;
@@ -63,12 +63,17 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
     // channel tile fastest: consecutive blocks go to different XCDs, so where there are eight tiles or
-    // more an XCD's L2 only sees its share of the weights
-    const int ct = blockIdx.x % ctiles;
-    const TilePos tp = tile_pos(blockIdx.x / ctiles, tiles_x, tiles_y);
-    const int y0 = tp.ty * G::TR, x0 = tp.tx * TWC;
+    // more an XCD's L2 only sees its share of the weights.  A grid of three dimensions and slices by
+    // shift: every division by an argument is 0.1 us of a latency chain of about 1.5.
+    const int ct = blockIdx.x;
+    int n = 0, ty = blockIdx.z;
+    if (ty >= tiles_y) {
+        n = ty / tiles_y;
+        ty -= n * tiles_y;
+    }
+    const int y0 = ty * G::TR, x0 = (int)blockIdx.y * TWC;
 
-    const int k_first = ksteps * wave / S, k_end = ksteps * (wave + 1) / S;
+    const int k_first = ksteps * wave >> log_s, k_end = ksteps * (wave + 1) >> log_s;
     const int Cw = Cwa + (TWO ? Cwb : 0);
 
     // ---- weights: fragments of the 32-channel tile, [tile64][kstep][tap][m][lane]
@@ -103,12 +108,12 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
         const int yy = y0 + r - 1, xx = x0 + c - 1;
         const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W;
         const int yc = min(max(yy, 0), H - 1), xc = min(max(xx, 0), W - 1);
-        offa[j] = (uint32_t)((((size_t)tp.n * H + yc) * W + xc) * Cwa * 4);
+        offa[j] = (uint32_t)((((size_t)n * H + yc) * W + xc) * Cwa * 4);
         inside |= (in ? 1u : 0u) << j;
         if (TWO) {
             const int yb = yc >> low_shift, xb = xc >> low_shift;
             inside_b |= ((in && yb < Hb && xb < Wb) ? 1u : 0u) << j;
-            offb[j] = (uint32_t)((((size_t)tp.n * Hb + min(yb, Hb - 1)) * Wb + min(xb, Wb - 1)) * Cwb * 4);
+            offb[j] = (uint32_t)((((size_t)n * Hb + min(yb, Hb - 1)) * Wb + min(xb, Wb - 1)) * Cwb * 4);
         }
     }
     uint2 gq[NLD];
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
     if (out_bits)
         for (int i = tid; i < R * 32; i += 64 * S) {
             const int y = y0 + i / TWC, x = x0 + i % TWC;
-            if (y < H && x < W) out_bits[(((size_t)tp.n * H + y) * W + x) * Cow + ct] = words[i];
+            if (y < H && x < W) out_bits[(((size_t)n * H + y) * W + x) * Cow + ct] = words[i];
         }
     if (G::TR % 2 == 0 && out_pool) {
         // the tile origin is even: every 2x2 window lies inside the tile
@@ -228,7 +233,7 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
             const int y = (y0 >> 1) + r, x = (x0 >> 1) + c;
             const uint32_t *p = words + 2 * r * TWC + 2 * c;
             if (y < Hl && x < Wl)
-                out_pool[(((size_t)tp.n * Hl + y) * Wl + x) * Cow + ct] = p[0] | p[1] | p[TWC] | p[TWC + 1];
+                out_pool[(((size_t)n * Hl + y) * Wl + x) * Cow + ct] = p[0] | p[1] | p[TWC] | p[TWC + 1];
         }
     }
 }
@@ -275,8 +280,10 @@ SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool up, boo
         if (units > 12288 && 7 * round_up(W, 32) <= 8 * round_up(W, 16)) { p.r = 4; p.tw = 32; }
     }
     const long tiles = (long)N * ceil_div(W, p.tw) * ceil_div(H, p.r * 32 / p.tw) * ctiles;
-    p.s = 1;
-    while (p.s < 8 && 2 * p.s <= L.ksteps && tiles * p.s < 2048) p.s *= 2;
+    p.log_s = 0;
+    while (p.log_s < 3 && 2 << p.log_s <= L.ksteps && tiles << p.log_s < 2048) ++p.log_s;
+    // the grid's second and third dimension end at 65535
+    if (ceil_div(W, p.tw) > 65535 || (long)N * ceil_div(H, p.r * 32 / p.tw) > 65535) return SplitPlan{0, 0, 0};
     return p;
 }
 
@@ -289,13 +296,12 @@ static int launch_split_t(const SplitPlan &p, const uint32_t *act, int cwa, cons
     const uint4 *wfrag = (const uint4 *)((const uint8_t *)blob + L.off_f4);
     const int32_t *wsum = (const int32_t *)((const uint8_t *)blob + L.off_cnt) + (size_t)10 * L.cout_pad64;
     const int tiles_x = ceil_div(W, TWC), tiles_y = ceil_div(H, G::TR);
-    const int ctiles = L.cout >> 5;
-    const dim3 grid((unsigned)((long)N * tiles_x * tiles_y * ctiles)), block(64 * p.s);
-    const size_t shmem = G::lds_bytes(p.s);
+    const dim3 grid((unsigned)(L.cout >> 5), (unsigned)tiles_x, (unsigned)(N * tiles_y)), block(64 << p.log_s);
+    const size_t shmem = G::lds_bytes(1 << p.log_s);
     const bool even = cwa % 2 == 0 && (!low || cwb % 2 == 0);
 #define MBU_SPLIT(EVEN_, TWO_)                                                                                       \
     MBU_LAUNCH((conv_mfma_split_kernel<R, TWC, EVEN_, TWO_>), grid, block, shmem, s, act, low, N, H, W, cwa, cwb,     \
-               low_shift, hb, wb, L.ksteps, wfrag, L.cout, ctiles, tiles_x, tiles_y, thresh, wsum, out_bits, out_pool)
+               low_shift, hb, wb, L.ksteps, wfrag, L.cout, p.log_s, tiles_y, thresh, wsum, out_bits, out_pool)
     if (low) {
         if (even) MBU_SPLIT(true, true);
         else MBU_SPLIT(false, true);

@@ -410,7 +410,7 @@ struct UpSplitGeo {
 template <int NC, int TWC>
 __global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
     const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int ksA, int ksL,
-    const uint4 *__restrict__ wfrag, const uint4 *__restrict__ wup, int Cout, int ctiles, int tiles_x, int tiles_y,
+    const uint4 *__restrict__ wfrag, const uint4 *__restrict__ wup, int Cout, int log_s, int tiles_y,
     const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum, uint32_t *__restrict__ out_bits)
 {
     static_assert(NC == 1 || NC == 4, "one parity class or all of them");
@@ -421,16 +421,19 @@ __global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
     float *start = reinterpret_cast<float *>(lds);
     uint32_t *words = reinterpret_cast<uint32_t *>(start + 32);   // [class][pixel]
     uint4 *const body = lds + G::HEAD / 4;
-    const int S = blockDim.x >> 6;
+    const int S = 1 << log_s;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
-    const int ct = blockIdx.x % ctiles;
-    const int rest = blockIdx.x / ctiles;
-    const int cls0 = NC == 1 ? rest & 3 : 0;
-    const TilePos tp = tile_pos(NC == 1 ? rest >> 2 : rest, tiles_x, tiles_y);
-    const int Y0 = tp.ty * G::RS, X0 = tp.tx * TWC;
+    const int ct = blockIdx.x;     // (three grid dimensions: no division by an argument)
+    const int cls0 = NC == 1 ? blockIdx.y & 3 : 0;
+    int n = 0, ty = blockIdx.z;
+    if (ty >= tiles_y) {
+        n = ty / tiles_y;
+        ty -= n * tiles_y;
+    }
+    const int Y0 = ty * G::RS, X0 = (int)(NC == 1 ? blockIdx.y >> 2 : blockIdx.y) * TWC;
     const int Hl = H >> 1, Wl = W >> 1;
     const int ksteps = ksA + ksL;
     uint4 *const win = body + wave * G::WAVE;
@@ -440,7 +443,7 @@ __global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
         return cost <= 9 * ksA ? (cost + 8) / 9 : ksA + (cost - 9 * ksA + 3) / 4;
     };
     const int total = 9 * ksA + 4 * ksL;
-    const int k_first = step_at(total * wave / S), k_end = step_at(total * (wave + 1) / S);
+    const int k_first = step_at(total * wave >> log_s), k_end = step_at(total * (wave + 1) >> log_s);
 
     // ---- weights
     const int m = ct & 1;
@@ -471,7 +474,7 @@ __global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
         p = p < G::AR * G::AC ? p : 0;
         const int y = 2 * Y0 - 1 + p / G::AC, x = 2 * X0 - 1 + p % G::AC;
         in_a |= (y >= 0 && y < H && x >= 0 && x < W ? 1u : 0u) << j;
-        offa[j] = (uint32_t)((((size_t)tp.n * H + min(max(y, 0), H - 1)) * W + min(max(x, 0), W - 1)) * ksA * 8);
+        offa[j] = (uint32_t)((((size_t)n * H + min(max(y, 0), H - 1)) * W + min(max(x, 0), W - 1)) * ksA * 8);
     }
 #pragma unroll
     for (int j = 0; j < NLB; ++j) {
@@ -479,7 +482,7 @@ __global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
         p = p < G::BR * G::BC ? p : 0;
         const int y = Y0 - 1 + p / G::BC, x = X0 - 1 + p % G::BC;
         in_b |= (y >= 0 && y < Hl && x >= 0 && x < Wl ? 1u : 0u) << j;
-        offb[j] = (uint32_t)((((size_t)tp.n * Hl + min(max(y, 0), Hl - 1)) * Wl + min(max(x, 0), Wl - 1)) * ksL * 8);
+        offb[j] = (uint32_t)((((size_t)n * Hl + min(max(y, 0), Hl - 1)) * Wl + min(max(x, 0), Wl - 1)) * ksL * 8);
     }
     uint2 gq[NLA];
     auto fetch = [&](auto is_low, bool want, int ks) {
@@ -622,7 +625,7 @@ __global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
     for (int i = tid; i < NC * 32; i += 64 * S) {
         const int c = cls0 + (i >> 5), p = i & 31;
         const int y = 2 * (Y0 + p / TWC) + (c >> 1), x = 2 * (X0 + p % TWC) + (c & 1);
-        if (y < H && x < W) out_bits[(((size_t)tp.n * H + y) * W + x) * Cow + ct] = words[i];
+        if (y < H && x < W) out_bits[(((size_t)n * H + y) * W + x) * Cow + ct] = words[i];
     }
 }
 
@@ -695,7 +698,7 @@ bool conv_upcat_supported(int Ca, int Clow, int N, int H, int W, const BlobLayou
 //  - Fewest groups; of equals the narrow ones, whose window has fewer pixels.
 //  - As many slices as stay within 2048 waves (two per SIMD), at most 8 and one per step.
 struct UpSplitPlan {
-    int nc, tw, s;   // s = 0: the large kernel
+    int nc, tw, log_s;   // nc = 0: the large kernel
 };
 static UpSplitPlan upcat_split_plan(int N, int Hl, int Wl, int ksA, int ksL, const BlobLayout &L)
 {
@@ -705,24 +708,26 @@ static UpSplitPlan upcat_split_plan(int N, int Hl, int Wl, int ksA, int ksL, con
     if (other > 512 || (other == 512 && ksteps < 12)) return p;
     const long g8 = (long)N * ceil_div(Wl, 8) * ceil_div(Hl, 4), g16 = (long)N * ceil_div(Wl, 16) * ceil_div(Hl, 2);
     p.tw = g8 <= g16 ? 8 : 16;
+    // the grid's second and third dimension end at 65535
+    if (4L * ceil_div(Wl, p.tw) > 65535 || (long)N * ceil_div(Hl, 32 / p.tw) > 65535) return p;
     const long tiles = std::min(g8, g16) * (L.cout >> 5);
     p.nc = tiles * (36 * ksA + 16 * ksL) <= 40000 ? 1 : 4;
     const long blocks = tiles * (4 / p.nc);
-    p.s = 1;
-    while (p.s < 8 && 2 * p.s <= ksteps && blocks * 2 * p.s <= 2048) p.s *= 2;
+    while (p.log_s < 3 && 2 << p.log_s <= ksteps && blocks * 2 << p.log_s <= 2048) ++p.log_s;
     return p;
 }
 
 template <int NC, int TWC>
-static int launch_upcat_split(int slices, const uint32_t *act, int Ca, const uint32_t *low, int Clow, int N, int H, int W,
+static int launch_upcat_split(int log_s, const uint32_t *act, int Ca, const uint32_t *low, int Clow, int N, int H, int W,
                               const BlobLayout &L, const uint4 *wfrag, const uint4 *wup, const int32_t *thresh,
                               const int32_t *wsum, uint32_t *out_bits, hipStream_t s)
 {
     using G = UpSplitGeo<NC, TWC>;
-    const int tiles_x = ceil_div(W / 2, TWC), tiles_y = ceil_div(H / 2, G::RS), ctiles = L.cout >> 5;
-    MBU_LAUNCH((conv_mfma_upcat_kernel<NC, TWC>), dim3((unsigned)((long)N * tiles_x * tiles_y * ctiles * (4 / NC))),
-               dim3(64 * slices), (size_t)G::lds_bytes(slices), s, act, low, N, H, W, Ca / 64, Clow / 64, wfrag, wup,
-               L.cout, ctiles, tiles_x, tiles_y, thresh, wsum, out_bits);
+    const int tiles_x = ceil_div(W / 2, TWC), tiles_y = ceil_div(H / 2, G::RS);
+    MBU_LAUNCH((conv_mfma_upcat_kernel<NC, TWC>),
+               dim3((unsigned)(L.cout >> 5), (unsigned)(tiles_x * (4 / NC)), (unsigned)(N * tiles_y)), dim3(64 << log_s),
+               (size_t)G::lds_bytes(1 << log_s), s, act, low, N, H, W, Ca / 64, Clow / 64, wfrag, wup, L.cout, log_s,
+               tiles_y, thresh, wsum, out_bits);
     return check_launch("conv_mfma_upcat_split");
 }
 
@@ -738,7 +743,7 @@ int launch_conv_mfma_upcat(const uint32_t *act, int Ca, const uint32_t *low, int
         const UpSplitPlan p = upcat_split_plan(N, H / 2, W / 2, Ca / 64, Clow / 64, L);
 #define MBU_GO(NC_, TW_)                                                                                        \
     if (p.nc == NC_ && p.tw == TW_)                                                                             \
-        return launch_upcat_split<NC_, TW_>(p.s, act, Ca, low, Clow, N, H, W, L, wfrag, wup, thresh, wsum, out_bits, s)
+        return launch_upcat_split<NC_, TW_>(p.log_s, act, Ca, low, Clow, N, H, W, L, wfrag, wup, thresh, wsum, out_bits, s)
         MBU_GO(1, 8);
         MBU_GO(1, 16);
         MBU_GO(4, 8);

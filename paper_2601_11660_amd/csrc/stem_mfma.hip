@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int chunk = blockIdx.x % nchunks;    // 64 output channels of the block
     const int gw = blockIdx.x / nchunks * 4 + wave;
-    int q = gw;
+    int q = min(gw, units - 1);                // (surplus waves: addresses of the last unit)
     const int sx = q % strips; q /= strips;        // strip of 32 pixel columns
     const int sg = q % nseg;                       // segment of seg_rows image rows
     const int n = q / nseg;
@@ -531,6 +531,54 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const int y0 = sg * seg_rows;
     const int rows = min(H, y0 + seg_rows) - y0;
     const int x0 = sx * 32;
+
+    // ---- addresses.  Staging: lane p < 34 owns halo pixel p (image column x0 - 1 + p); the
+    // other lanes repeat pixel 33.  Zero padding: a column or row outside the image gets an
+    // offset beyond the buffer and reads 0.0f.
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void *)img, 0, (int)img_bytes, 0x00020000);
+    const int p = min(lane, SR_HW - 1);
+    const int xs = x0 - 1 + p;
+    const uint32_t xoff = (xs >= 0 && xs < W) ? (uint32_t)xs * 4u : OOB;
+    uint32_t *const ldsw = lds[wave];
+    uint32_t *const wr = ldsw + p;
+    const uint32_t *const q0 = ldsw + (half ? 3 * SR_ARR : 0) + col;            // P0 | P2, then P1 | R2
+    const uint32_t *const q2 = ldsw + 2 * SR_ARR + col + (half ? 2 : 0);        // R01[j] | R01[j+2]
+    const uint32_t *const q3 = ldsw + (half ? SR_CONST : 2 * SR_ARR + col + 1); // R01[j+1] | constant
+    if (lane == 0) {
+        ldsw[SR_CONST] = 0x3c00u;              // (1.0, 0) in the hi plane, 0 in the lo plane
+        ldsw[SR_CONST + SR_PLANE] = 0u;
+    }
+
+    const int Cow = Co >> 5;
+    const uint32_t psel = half ? 0x07060302u : 0x05040100u;
+    const int widx = chunk * 2 + half;
+    const int xo = x0 + col;                   // output pixel column of this lane
+    // packed output of image n as a buffer: lane offset inside a row, row offset per tile
+    const uint32_t out_row_bytes = (uint32_t)W * Cow * 4u;
+    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(out + (size_t)n * H * W * Cow), 0, (int)(H * out_row_bytes), 0x00020000);
+    // (validity goes into the row offset alone: two out-of-range marks would add up to 0)
+    const uint32_t out_voff = (uint32_t)(xo * Cow + widx) * 4u;
+
+    struct Planes { uint4 h[2], l[2]; float ns[3]; uint32_t ob[3]; bool ok; };
+
+    // one image row of the strip: three floats per lane
+    auto fetch = [&](int yy, float (&v)[3]) {
+        const bool rin = yy >= 0 && yy < H;
+        const int yc = min(max(yy, 0), H - 1);
+        const uint32_t vo = rin ? xoff : OOB;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            v[c] = __uint_as_float(
+                __builtin_amdgcn_raw_buffer_load_b32(rsrc, vo, (int)((((size_t)n * 3 + c) * H + yc) * W * 4), 0));
+    };
+    // rows y0 - 1 .. y0 + 1 for the first tile, rows y0 + 2 and y0 + 3: under way while the weights are prepared
+    float a[3][3], ld0[3], ld1[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) fetch(y0 - 1 + r, a[r]);
+    fetch(y0 + 2, ld0);
+    fetch(y0 + 3, ld1);
 
     // ---- weights: rows scaled to a norm in [2^12, 2^13), split once, in the K order above.  Wave w
     // prepares tile w & 1, block w >> 1 of K (the norm needs the whole row) and the block shares them:
@@ -580,47 +628,6 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const float KW = STEM_KAPPA * 1.002f * __uint_as_float(max(wnorm[0], wnorm[1]));
     const bool w_sane = (winsane[0] | winsane[1]) == 0;
 
-    // ---- addresses.  Staging: lane p < 34 owns halo pixel p (image column x0 - 1 + p); the
-    // other lanes repeat pixel 33.  Zero padding: a column or row outside the image gets an
-    // offset beyond the buffer and reads 0.0f.
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc((void *)img, 0, (int)img_bytes, 0x00020000);
-    const int p = min(lane, SR_HW - 1);
-    const int xs = x0 - 1 + p;
-    const uint32_t xoff = (xs >= 0 && xs < W) ? (uint32_t)xs * 4u : OOB;
-    uint32_t *const ldsw = lds[wave];
-    uint32_t *const wr = ldsw + p;
-    const uint32_t *const q0 = ldsw + (half ? 3 * SR_ARR : 0) + col;            // P0 | P2, then P1 | R2
-    const uint32_t *const q2 = ldsw + 2 * SR_ARR + col + (half ? 2 : 0);        // R01[j] | R01[j+2]
-    const uint32_t *const q3 = ldsw + (half ? SR_CONST : 2 * SR_ARR + col + 1); // R01[j+1] | constant
-    if (lane == 0) {
-        ldsw[SR_CONST] = 0x3c00u;              // (1.0, 0) in the hi plane, 0 in the lo plane
-        ldsw[SR_CONST + SR_PLANE] = 0u;
-    }
-
-    const int Cow = Co >> 5;
-    const uint32_t psel = half ? 0x07060302u : 0x05040100u;
-    const int widx = chunk * 2 + half;
-    const int xo = x0 + col;                   // output pixel column of this lane
-    // packed output of image n as a buffer: lane offset inside a row, row offset per tile
-    const uint32_t out_row_bytes = (uint32_t)W * Cow * 4u;
-    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(out + (size_t)n * H * W * Cow), 0, (int)(H * out_row_bytes), 0x00020000);
-    // (validity goes into the row offset alone: two out-of-range marks would add up to 0)
-    const uint32_t out_voff = (uint32_t)(xo * Cow + widx) * 4u;
-
-    struct Planes { uint4 h[2], l[2]; float ns[3]; uint32_t ob[3]; bool ok; };
-
-    // one image row of the strip: three floats per lane
-    auto fetch = [&](int yy, float (&v)[3]) {
-        const bool rin = yy >= 0 && yy < H;
-        const int yc = min(max(yy, 0), H - 1);
-        const uint32_t vo = rin ? xoff : OOB;
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            v[c] = __uint_as_float(
-                __builtin_amdgcn_raw_buffer_load_b32(rsrc, vo, (int)((((size_t)n * 3 + c) * H + yc) * W * 4), 0));
-    };
     // largest magnitude of a row over the wave, as the bit pattern of a non-negative float
     auto row_max = [&](const float (&v)[3]) {
         const uint32_t a = __float_as_uint(v[0]) & 0x7fffffffu, b = __float_as_uint(v[1]) & 0x7fffffffu,
@@ -884,14 +891,9 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         for (int k = 0; k < EPI_PIECES; ++k) epi_piece(k, acc, dn, ep);
     };
 
-    // ---- prologue: rows y0 - 1 .. y0 + 1 staged for the first tile, rows y0 + 2 and y0 + 3 in flight
-    float a[3][3], ld0[3], ld1[3];
+    // ---- prologue: rows y0 - 1 .. y0 + 1 staged for the first tile
     uint32_t rm[3];
     Planes B0, B1;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) fetch(y0 - 1 + r, a[r]);
-    fetch(y0 + 2, ld0);
-    fetch(y0 + 3, ld1);
 #pragma unroll
     for (int r = 0; r < 3; ++r) rm[r] = row_max(a[r]);
     {

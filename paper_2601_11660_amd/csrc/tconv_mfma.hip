@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
     // sets alternate): a fetch has two group times to arrive
     auto fetch = [&](const Plan &P, uint32_t (&st)[PW]) {
         const int x = P.gx * 32 + spx, y = P.gy * RGX + sr;
-        // a pixel outside the image: any offset beyond the tensor (reads 0; masked at expansion)
+        // a pixel outside the image: any offset beyond the tensor (reads 0; nothing of it is stored)
         const uint32_t off = (x < W && y < H) ? (uint32_t)((((P.n * H + y) * W + x) * CW + k0) * 4) : BAD;
         if (PW == 4) {
             const auto v = __builtin_amdgcn_raw_buffer_load_b128(ars, off, 0, 0);
@@ -541,6 +541,15 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
     commit(0, sa);
     __syncthreads();
     int buf = 0;
+    v16f init[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = init_tab[p][half][m][q];
+            init[m][4 * q] = f.x; init[m][4 * q + 1] = f.y;
+            init[m][4 * q + 2] = f.z; init[m][4 * q + 3] = f.w;
+        }
 
     // one group: fetch of group g + 2 stride into sf, matrix work of group g from LDS buffer
     // `buf`, words of group g + stride (in sc since the previous group) into the other buffer.
@@ -550,34 +559,19 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
         fetch(nn, sf);
         v16f acc[RGX][2];
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 f = init_tab[p][half][m][q];
-#pragma unroll
-                for (int r = 0; r < RGX; ++r) {
-                    acc[r][m][4 * q] = f.x; acc[r][m][4 * q + 1] = f.y;
-                    acc[r][m][4 * q + 2] = f.z; acc[r][m][4 * q + 3] = f.w;
-                }
-            }
-        uint32_t k8[RGX];
-#pragma unroll
-        for (int r = 0; r < RGX; ++r)
-            k8[r] = (cur.gx * 32 + col < W && cur.gy * RGX + r < H) ? 0x22222222u : 0u;
-#pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             v4i B[RGX];
 #pragma unroll
             for (int r = 0; r < RGX; ++r) {
-                const uint32_t m2 = k8[r];
-                const uint32_t word = srd[buf * TILE + (r * CW + 2 * ks) * 32];
-                B[r] = (v4i){(int)((word << 1) & m2), (int)(word & m2), (int)((word >> 1) & m2),
-                             (int)((word >> 2) & m2)};
+                const uint4 e = expand_word(srd[buf * TILE + (r * CW + 2 * ks) * 32]);
+                B[r] = (v4i){(int)e.x, (int)e.y, (int)e.z, (int)e.w};
             }
+            // the first step's matrix instructions take the start values as their addend: setting
+            // the accumulators would cost as many vector instructions as collecting the signs
 #pragma unroll
             for (int r = 0; r < RGX; ++r)
 #pragma unroll
-                for (int m = 0; m < 2; ++m) acc[r][m] = mfma_f4(Wt[ks][m], B[r], acc[r][m]);
+                for (int m = 0; m < 2; ++m) acc[r][m] = mfma_f4(Wt[ks][m], B[r], ks == 0 ? init[m] : acc[r][m]);
         }
         // ---- epilogue: input pixel (y, x) -> output pixel (2y + dy, 2x + dx)
         const uint32_t lane_off = (cur.gx * 32 + col < W) ? out_lane + (uint32_t)(cur.gx * 64 * Cow * 4) : BAD;
