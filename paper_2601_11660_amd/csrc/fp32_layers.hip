@@ -130,26 +130,42 @@ __global__ __launch_bounds__(256, CW == 4 ? 2 : 3) void classifier_kernel(const 
     const int row = col;  // class index of this lane in the weight operand
     const size_t rbase = (size_t)(row < K ? row : 0) * C;   // loads are unconditional (clamped row)
 
+    // weight operand: instruction t = 2*wd + tp covers, in lane half h, dword d:
+    // low fp16 = channel 32*wd + 8*tp + 4*h + d, high fp16 = that + 16.  The lane's half of the row in one
+    // batch of 16-byte fetches; the other half of the largest magnitude comes from the partner lane.
+    float4 wv[2 * CW][2];
+#pragma unroll
+    for (int t = 0; t < 2 * CW; ++t) {
+        const float *src = w + rbase + 32 * (t >> 1) + 8 * (t & 1) + 4 * half;
+        wv[t][0] = *reinterpret_cast<const float4 *>(src);
+        wv[t][1] = *reinterpret_cast<const float4 *>(src + 16);
+    }
     // power-of-two scale of this lane's class row: largest |weight| into [0.5, 1)
     float mx = 0.0f;
-#pragma unroll 8
-    for (int c = 0; c < C; ++c) mx = fmaxf(mx, fabsf(w[rbase + c]));
+#pragma unroll
+    for (int t = 0; t < 2 * CW; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            mx = fmaxf(fmaxf(fmaxf(mx, fabsf(wv[t][i].x)), fmaxf(fabsf(wv[t][i].y), fabsf(wv[t][i].z))), fabsf(wv[t][i].w));
+    {
+        const uint32_t u = __float_as_uint(mx);
+        const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    }
     int e = 0;
     if (mx > 0.0f && mx < __builtin_inff()) (void)frexpf(mx, &e);
     const float scale = ldexpf(1.0f, -e);
 
-    // weight operand: instruction t = 2*wd + tp covers, in lane half h, dword d:
-    // low fp16 = channel 32*wd + 8*tp + 4*h + d, high fp16 = that + 16
     uint4 wa[2 * CW][2];
 #pragma unroll
     for (int t = 0; t < 2 * CW; ++t) {
         uint32_t hi4[4], lo4[4];
+        const float a0[4] = {wv[t][0].x, wv[t][0].y, wv[t][0].z, wv[t][0].w};
+        const float a1[4] = {wv[t][1].x, wv[t][1].y, wv[t][1].z, wv[t][1].w};
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            const int clo = 32 * (t >> 1) + 8 * (t & 1) + 4 * half + d;
-            const float w0 = w[rbase + clo], w1 = w[rbase + clo + 16];
-            const float v0 = row < K ? -w0 * scale : 0.0f;   // exact scaling
-            const float v1 = row < K ? -w1 * scale : 0.0f;
+            const float v0 = row < K ? -a0[d] * scale : 0.0f;   // exact scaling
+            const float v1 = row < K ? -a1[d] * scale : 0.0f;
             const _Float16 h0 = (_Float16)v0, h1 = (_Float16)v1;
             hi4[d] = f16_pair(v0, v1);
             lo4[d] = f16_pair(v0 - (float)h0, v1 - (float)h1);
@@ -263,61 +279,90 @@ __global__ __launch_bounds__(256, CW == 4 ? 2 : 3) void classifier_kernel(const 
 // and a thread sums C / 8 table entries per pixel: logit[k] = b[k] + sum_j table[j][byte j][k].
 // The partial sums are formed in another order than the channel-by-channel definition; the
 // difference is a few float32 roundings (1e-7 relative), far inside the layer's 1e-4.
-template <int KP>
+//
+// The table costs a block about as long as 1024 pixels: its weights come from LDS (read from memory term
+// by term, one dependent fetch after the other, they cost a frame of 73 K pixels 8 of its 11 us), a thread
+// knows its eight signs in advance, and a launch has a block for every 512 pixels up to 1024 blocks.
+template <int K, int CW>
 __global__ __launch_bounds__(256) void classifier_lut_kernel(const uint32_t *__restrict__ act, long pixels,
-                                                             long HW, int CW, const float *__restrict__ w,
-                                                             const float *__restrict__ b, int K,
+                                                             long HW, const float *__restrict__ w,
+                                                             const float *__restrict__ b,
                                                              float *__restrict__ out)
 {
-    __shared__ float lut[16 * 256 * KP];
-    const int nb = 4 * CW;            // byte positions
-    {
-        const int v = threadIdx.x;
-        for (int j = 0; j < nb; ++j)
+    constexpr int KP = K == 3 ? 4 : K;
+    constexpr int NB = 4 * CW;        // byte positions
+    struct alignas(4 * KP) entry { float v[KP]; };   // one LDS access per byte
+    __shared__ entry lut[NB * 256];
+    __shared__ float wt[KP * 32 * CW];
+    for (int i = threadIdx.x; i < KP * 32 * CW; i += 256) wt[i] = i < K * 32 * CW ? w[i] : 0.0f;
+    float bias[K];
 #pragma unroll
-            for (int k = 0; k < KP; ++k) {
-                float sum = 0.0f;
-                if (k < K) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const float wv = w[(size_t)k * (32 * CW) + 8 * j + i];
-                        sum += ((v >> i) & 1) ? wv : -wv;
-                    }
-                }
-                lut[(j * 256 + v) * KP + k] = sum;
-            }
-    }
-    float bias[KP];
-#pragma unroll
-    for (int k = 0; k < KP; ++k) bias[k] = k < K ? b[k] : 0.0f;
-    __syncthreads();
-
+    for (int k = 0; k < K; ++k) bias[k] = b[k];
     const long stride = (long)gridDim.x * 256;
     long p = (long)blockIdx.x * 256 + threadIdx.x;
+    auto fetch = [&](long pix, uint32_t (&wd)[CW]) {
+        const uint32_t *src = act + pix * CW;
+        if (CW == 1) {
+            wd[0] = src[0];
+        } else {
+#pragma unroll
+            for (int q = 0; q < CW; q += 2) {
+                const uint2 v = *reinterpret_cast<const uint2 *>(src + q);
+                wd[q] = v.x;
+                wd[q + (CW > 1)] = v.y;
+            }
+        }
+    };
+    uint32_t cur[CW];
+    float sign[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sign[i] = (threadIdx.x >> i) & 1 ? 1.0f : -1.0f;
+    __syncthreads();
+#pragma unroll 2
+    for (int j = 0; j < NB; ++j) {
+        entry e;
+#pragma unroll
+        for (int k = 0; k < KP; ++k) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum = __builtin_fmaf(sign[i], wt[k * 32 * CW + 8 * j + i], sum);
+            e.v[k] = sum;
+        }
+        lut[j * 256 + threadIdx.x] = e;
+    }
+    __syncthreads();
+
     // (image, pixel inside the image) of p, advanced by the stride without divisions
     long n = p / HW, rem = p - n * HW;
     const long dn = stride / HW, dr = stride - dn * HW;
     for (; p < pixels; p += stride) {
-        float acc[KP];
+        fetch(p, cur);
+        float acc[K];
 #pragma unroll
-        for (int k = 0; k < KP; ++k) acc[k] = bias[k];
-        for (int q = 0; q < CW; ++q) {
-            const uint32_t word = act[p * CW + q];
+        for (int k = 0; k < K; ++k) acc[k] = bias[k];
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const float *e = lut + ((q * 4 + jj) * 256 + ((word >> (8 * jj)) & 255u)) * KP;
+        for (int j = 0; j < NB; ++j) {
+            const entry e = lut[j * 256 + ((cur[j >> 2] >> (8 * (j & 3))) & 255u)];
 #pragma unroll
-                for (int k = 0; k < KP; ++k) acc[k] += e[k];
-            }
+            for (int k = 0; k < K; ++k) acc[k] += e.v[k];
         }
         float *o = out + (size_t)n * K * HW + rem;
 #pragma unroll
-        for (int k = 0; k < KP; ++k)
-            if (k < K) __builtin_nontemporal_store(acc[k], o + (size_t)k * HW);
+        for (int k = 0; k < K; ++k)
+            __builtin_nontemporal_store(acc[k], o + (size_t)k * HW);
         n += dn;
         rem += dr;
         if (rem >= HW) { rem -= HW; ++n; }
     }
+}
+
+template <int K>
+static void launch_classifier_lut(unsigned blocks, int CW, const uint32_t *act, long pixels, long HW, const float *w,
+                                  const float *b, float *out, hipStream_t s)
+{
+    if (CW == 1) MBU_LAUNCH((classifier_lut_kernel<K, 1>), dim3(blocks), dim3(256), 0, s, act, pixels, HW, w, b, out);
+    else if (CW == 2) MBU_LAUNCH((classifier_lut_kernel<K, 2>), dim3(blocks), dim3(256), 0, s, act, pixels, HW, w, b, out);
+    else MBU_LAUNCH((classifier_lut_kernel<K, 4>), dim3(blocks), dim3(256), 0, s, act, pixels, HW, w, b, out);
 }
 
 int launch_classifier(const uint32_t *act, int N, int H, int W, int C, const float *w,
@@ -329,12 +374,11 @@ int launch_classifier(const uint32_t *act, int N, int H, int W, int C, const flo
     if ((double)(K + 5) * (double)HW * 4.0 >= 4294967296.0)
         return fail(MBU_ERR_SHAPE, "classifier: image too large (%ld pixels, %d classes)", HW, K);
     if (K <= 4 && (C == 32 || C == 64 || C == 128)) {
-        // few classes: table look-up, many pixels per thread so that building the table is amortised
-        const unsigned blocks = (unsigned)std::max(1L, std::min((pixels + 2047) / 2048, 1024L));
-        const int CW = C / 32;
-        if (K == 1) MBU_LAUNCH(classifier_lut_kernel<1>, dim3(blocks), dim3(256), 0, s, act, pixels, HW, CW, w, b, K, out);
-        else if (K == 2) MBU_LAUNCH(classifier_lut_kernel<2>, dim3(blocks), dim3(256), 0, s, act, pixels, HW, CW, w, b, K, out);
-        else MBU_LAUNCH(classifier_lut_kernel<4>, dim3(blocks), dim3(256), 0, s, act, pixels, HW, CW, w, b, K, out);
+        const unsigned blocks = (unsigned)std::max(1L, std::min((pixels + 511) / 512, 1024L));
+        if (K == 1) launch_classifier_lut<1>(blocks, C / 32, act, pixels, HW, w, b, out, s);
+        else if (K == 2) launch_classifier_lut<2>(blocks, C / 32, act, pixels, HW, w, b, out, s);
+        else if (K == 3) launch_classifier_lut<3>(blocks, C / 32, act, pixels, HW, w, b, out, s);
+        else launch_classifier_lut<4>(blocks, C / 32, act, pixels, HW, w, b, out, s);
         return check_launch("classifier");
     }
     long groups = (pixels + 31) / 32;

@@ -1059,6 +1059,24 @@ def test_stem_full_size_frame():
     assert worst <= 1.0
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1, 32, 1), (1, 3, 7, 64, 1), (2, 40, 77, 64, 2), (1, 33, 31, 128, 3), (3, 5, 5, 32, 4),
+                                   (1, 700, 800, 128, 4), (1, 1, 31, 32, 5), (2, 3, 43, 128, 32)])
+def test_classifier_block_edges(shape):
+    """Both classifier kernels from one pixel to more pixels than one pass of the largest grid; logits
+    against 64-bit sums (a few float32 roundings of at most sum |w| + |b|)."""
+    N, H, W, C, K = shape
+    say(f"classifier edges {shape}")
+    rng = np.random.default_rng(K)
+    a = synth.pm1_bits(rng, (N, H, W, C))
+    w = rng.standard_normal((K, C)).astype(np.float32)
+    w[0, 0] *= 1e-6
+    b = rng.standard_normal(K).astype(np.float32)
+    got = host(B.classifier_fp32(B.pack_act(dev(a)), C, dev(w), dev(b)))
+    ref = np.moveaxis(a.astype(np.float64) @ w.T.astype(np.float64) + b, 3, 1)
+    bound = (np.abs(w).sum(1) + np.abs(b)) * C * 2.0 ** -24
+    assert (np.abs(got - ref) <= bound[None, :, None, None]).all()
+
+
 @pytest.mark.parametrize("shape", [(1, 9, 33, 32, 5), (2, 16, 40, 64, 19), (1, 7, 100, 128, 32),
                                    (1, 64, 64, 64, 1),
                                    (3, 5, 7, 64, 19), (4, 3, 5, 32, 3), (5, 1, 1, 64, 19),    # 32-pixel groups across images
