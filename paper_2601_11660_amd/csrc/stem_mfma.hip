@@ -729,6 +729,31 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         }
     };
 
+    // the sum of one output in its defined order (ky, kx, ci); a tap outside the image is skipped.  One
+    // row of taps at a time: all 27 pairs at once would cost the tile loop its registers.
+    auto chain = [&](int y, int x, int ch) {
+        float sum = 0.0f;
+#pragma unroll 1
+        for (int ky = 0; ky < 3; ++ky) {
+            const int yy = y + ky - 1;
+            float pv[9], wv[9];
+#pragma unroll
+            for (int u = 0; u < 9; ++u) {
+                const int xx = x + u / 3 - 1;
+                const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
+                const uint32_t o = (uint32_t)(((((size_t)n * 3 + u % 3) * H + yy) * W + xx) * 4);
+                pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, ok ? o : OOB, 0, 0));
+                wv[u] = w[(size_t)ch * KV + ky * 9 + u];
+            }
+#pragma unroll
+            for (int u = 0; u < 9; ++u) {
+                const int xx = x + u / 3 - 1;
+                const float f = __builtin_fmaf(wv[u], pv[u], sum);
+                sum = yy >= 0 && yy < H && xx >= 0 && xx < W ? f : sum;
+            }
+        }
+        return sum;
+    };
     int qn = 0;   // entries of the list of undecided outputs
     // ---- decision and store of a finished row
     struct Done { float T; bool zero; int i; };
@@ -793,40 +818,14 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                         qn += __builtin_popcountll(who);
                     }
                 } else if (flag) {
-                    const uint32_t pb = (uint32_t)((((size_t)n * 3 * H + y) * W + xo) * 4);
-                    // the 27 patch values of this pixel, fetched once and in one batch (a tap
-                    // outside the image is skipped in the chain below)
-                    float pv[27];
-                    uint32_t okm = 0;
 #pragma unroll
-                    for (int u = 0; u < 27; ++u) {
-                        const int ky = u / 9, kx = (u % 9) / 3, ci = u % 3;
-                        const bool ok = !((ky == 0 && y == 0) || (ky == 2 && y == H - 1) ||
-                                          (kx == 0 && xo == 0) || (kx == 2 && xo == W - 1));
-                        const uint32_t o = pb + (uint32_t)(((long)ci * H * W + (long)(ky - 1) * W + (kx - 1)) * 4);
-                        pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, ok ? o : OOB, 0, 0));
-                        okm |= (ok ? 1u : 0u) << u;
-                    }
-#pragma unroll
-                    for (int m = 0; m < 2; ++m) {
-                        const int cb = chunk * 64 + m * 32 + 16 * half;
+                    for (int m = 0; m < 2; ++m)
                         while (fl[m]) {
                             const int e = __builtin_ctz(fl[m]);
                             fl[m] &= fl[m] - 1;
-                            const float *wp = w + (size_t)(cb + e) * KV;
-                            float wv[27];
-#pragma unroll
-                            for (int u = 0; u < 27; ++u) wv[u] = wp[u];
-                            // the sum in its defined order: ky, kx, ci
-                            float sum = 0.0f;
-#pragma unroll
-                            for (int u = 0; u < 27; ++u) {
-                                const float f = __builtin_fmaf(wv[u], pv[u], sum);
-                                sum = ((okm >> u) & 1u) ? f : sum;
-                            }
+                            const float sum = chain(y, xo, chunk * 64 + m * 32 + 16 * half + e);
                             ep.sg[m] = (ep.sg[m] & ~(1u << e)) | ((sum >= 0.0f ? 0u : 1u) << e);   // NaN -> bit 0
                         }
-                    }
                 }
             }
             if (dn.zero) { ep.sg[0] = 0u; ep.sg[1] = 0u; }   // a chain of zero terms ends at +0.0f
@@ -901,33 +900,14 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 #pragma unroll
         for (int k = 0; k < STAGE_PIECES; ++k) stage_piece(k, a, rm, st, B0);
     }
-    // the listed outputs, one per lane: the sum in its defined order (ky, kx, ci), then the bit
+    // the listed outputs, one per lane
     auto flush = [&]() {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the words with the provisional bits are out
         for (int b = 0; b < qn; b += 64)
             if (b + lane < qn) {
                 const uint32_t en = ldsw[SR_Q + b + lane];
                 const int y = y0 + (int)(en >> 11), x = x0 + (int)(en & 31u), ch = chunk * 64 + (int)(en >> 5 & 63u);
-                float sum = 0.0f;
-#pragma unroll 1
-                for (int ky = 0; ky < 3; ++ky) {
-                    const int yy = y + ky - 1;
-                    float pv[9], wv[9];
-#pragma unroll
-                    for (int u = 0; u < 9; ++u) {
-                        const int xx = x + u / 3 - 1;
-                        const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
-                        const uint32_t o = (uint32_t)(((((size_t)n * 3 + u % 3) * H + yy) * W + xx) * 4);
-                        pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, ok ? o : OOB, 0, 0));
-                        wv[u] = w[(size_t)ch * KV + ky * 9 + u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 9; ++u) {
-                        const int xx = x + u / 3 - 1;
-                        const float f = __builtin_fmaf(wv[u], pv[u], sum);
-                        sum = yy >= 0 && yy < H && xx >= 0 && xx < W ? f : sum;   // a tap outside is skipped
-                    }
-                }
+                const float sum = chain(y, x, ch);
                 uint32_t *const word = out + (((size_t)n * H + y) * W + x) * Cow + (ch >> 5);
                 if (sum >= 0.0f) atomicOr(word, 1u << (ch & 31));
                 else atomicAnd(word, ~(1u << (ch & 31)));   // NaN -> bit 0
