@@ -122,8 +122,15 @@ def check(rc: int) -> None:
         raise MbuError(rc, last_error())
 
 
+# The handle of the current stream without building a Stream object: 0.3 instead of 2.7 us of the
+# 9 us a call of a small layer takes on the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, dtypes) -> int:
