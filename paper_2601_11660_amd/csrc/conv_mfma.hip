@@ -538,12 +538,20 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_block_kernel(
                 // window row RW - 1 + ky of column kx; in that order the 18 fragments of the NEXT
                 // step go to slots 3 .. 17 and the last three - tap column 2, first used in slot
                 // 13 - to slots 0 .. 2 of the step that uses them.
-                {
+                if (RW == 4) {
                     const int i = j < 3 ? 15 + j : j - 3;
                     const int g = i / 6, ky = (i % 6) >> 1, m = i & 1;
                     const auto w = __builtin_amdgcn_raw_buffer_load_b128(
                         wrs, wlane, ((j < 3 ? ks : kn) * 18 + (ky * 3 + g) * 2 + m) * 1024, 0);
                     Wg[g][ky][m] = (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+                } else if (rho >= RW - 1) {   // fewer slots: both fragments of a tap as soon as they are free
+                    const int ky = rho - (RW - 1);
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const auto w = __builtin_amdgcn_raw_buffer_load_b128(
+                            wrs, wlane, (kn * 18 + (ky * 3 + kx) * 2 + m) * 1024, 0);
+                        Wg[kx][ky][m] = (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+                    }
                 }
                 // the next step's window (fetched at the start of this one): one word per slot
                 if (j >= NF - 1 - 2 * NLD && j < NF - 1) commit_word(kn, tile[buf ^ 1], j - (NF - 1 - 2 * NLD));
@@ -835,6 +843,20 @@ static int launch_block_auto(const ConvIO &io, int N, int H, int W, const BlobLa
 {
     // waves of a block over output-channel tiles when there are enough of them
     const int tiles64 = L.cout_pad64 / 64;
+    // Two rows per wave instead of four, where twice the blocks fill the chip better than twice the use of
+    // every weight fragment helps: while they still get a compute unit each (128 -> 256 blocks: 256->256 at
+    // 128x128 10.1 -> 8.1 us, 128->256 7.4 -> 6.0; 75 -> 145: 9.9 -> 7.0), and where the larger blocks leave
+    // most units one and a few two (300 -> 600 blocks: 128->128 at 240x320 10.7 -> 9.5; 360: 15.4 -> 14.7).
+    // In between and beyond four rows win (150 blocks: 10.0 against 11.5 us; 256: 26.4 against 32.0;
+    // 1024: 27.5 against 31.6).
+    const int wn = tiles64 % 4 == 0 ? 4 : tiles64 % 2 == 0 ? 2 : 1, wm = 4 / wn;
+    const long blocks4 = (long)N * ceil_div(H, 4 * wm) * ceil_div(W, TW) * (tiles64 / wn);
+    const long blocks2 = (long)N * ceil_div(H, 2 * wm) * ceil_div(W, TW) * (tiles64 / wn);
+    if (t_cfg.tune_rw == 0 && (blocks2 <= 256 || (blocks4 > 256 && blocks4 <= 384))) {
+        if (wn == 4) return launch_block<2, 1, 4>(io, N, H, W, L, wfrag, thresh, s);
+        if (wn == 2) return launch_block<2, 2, 2>(io, N, H, W, L, wfrag, thresh, s);
+        return launch_block<2, 4, 1>(io, N, H, W, L, wfrag, thresh, s);
+    }
     if (tiles64 % 4 == 0) return launch_block<4, 1, 4>(io, N, H, W, L, wfrag, thresh, s);
     if (tiles64 % 2 == 0) return launch_block<4, 2, 2>(io, N, H, W, L, wfrag, thresh, s);
     return launch_block<4, 4, 1>(io, N, H, W, L, wfrag, thresh, s);

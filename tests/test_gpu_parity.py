@@ -315,6 +315,43 @@ def test_small_layers_split_over_their_input_channels(shape):
                 assert np.array_equal(host_u32(pooled), pool_ref), mode
 
 
+@pytest.mark.parametrize("shape", [
+    # N, H, W, Ca, Cb, Cout: waves over channels, over both, over rows; ragged last rows and columns
+    (1, 127, 127, 128, 0, 256), (1, 126, 33, 96, 0, 512),
+    (1, 250, 131, 128, 0, 128), (1, 299, 330, 128, 0, 128),
+    (1, 509, 130, 128, 0, 64), (2, 333, 63, 96, 0, 64),
+    (1, 129, 123, 64, 96, 256), (1, 253, 127, 96, 64, 128), (1, 515, 129, 64, 64, 64),
+])
+def test_block_kernel_with_two_rows_per_wave(shape):
+    """Layers whose block count makes the block-cooperative kernel take two rows per wave (and
+    neighbours just outside), with the pooled output, against the four-row form of tuning 1 and, on
+    the smaller ones, the oracle."""
+    N, H, W, Ca, Cb, Cout = shape
+    say(f"conv block rows N={N} H={H} W={W} Ca={Ca} Cb={Cb} Cout={Cout}")
+    rng = np.random.default_rng(H + W)
+    a = synth.pm1_bits(rng, (N, H, W, Ca))
+    b = synth.pm1_bits(rng, (N, H, W - 1, Cb)) if Cb else None
+    w = synth.ternary_weights(16, 0, 0, Cout, Ca + Cb, 0.6)
+    th = synth.thresholds(16, 0, 0, Cout, (9 * (Ca + Cb)) // 16)
+    pa, blob, thd = B.pack_act(dev(a)), B.pack_weights(dev(w)), dev(th)
+    pb = B.pack_act(dev(b)) if Cb else None
+    outs = []
+    for mode in (0, 1):
+        B.set_conv_tuning(mode)
+        if Cb:
+            o = B.conv3x3_masked_binary_two_inputs(pa, Ca, pb, Cb, False, blob, Cout, thd, True)
+        else:
+            o = B.conv3x3_masked_binary_fused(pa, Ca, None, 0, blob, Cout, thd, True, True)
+        torch.cuda.synchronize()
+        outs.append([host_u32(t) for t in o])
+    assert all(np.array_equal(x, y) for x, y in zip(*outs))
+    if N * H * W * Cout * (Ca + Cb) < 1.0e9:
+        x = O.concat(a, O.zero_pad_to(b, H, W)) if Cb else a
+        _, ref = O.masked_binary_layer(x, w, th)
+        assert np.array_equal(outs[0][0], bitref.pack_pm1(ref))
+        assert np.array_equal(outs[0][1], bitref.pack_pm1(O.maxpool2x2(ref)))
+
+
 UPCAT_SHAPES = [
     # N, H, W, Ca, Clow, Cout, keep: skip channels % 64 == 0 and low channels % 128 == 0
     (1, 16, 128, 64, 128, 64, 0.6),
