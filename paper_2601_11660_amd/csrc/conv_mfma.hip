@@ -725,17 +725,19 @@ static const int32_t *weight_sums(const uint4 *wfrag, const BlobLayout &L)
 
 
 // Layers with two input steps: the row-streaming kernel (32 output channels per wave) or the
-// block-cooperative one?  Measured on MI355X: 128->128 at 512x1024 30.5 us against 33.1 us,
-// 128->256 at 256x512 21.3 us against 19.2 us - every wave of another channel tile stages the
-// strip again, and short row segments pay the prologue more often.  So: at most four channel
-// tiles, and segments of 24 rows or more when every wave slot has one.
+// block-cooperative one?  Every wave of another channel tile stages the strip again (128->256 at
+// 256x512 21.3 us against 19.2), and short row segments pay the prologue more often.  So: at most
+// four channel tiles, and segments of six rows or more when every wave slot has one.  Kernel trace,
+// block -> rows: 128->128 at 512x512 (16 rows) 17.4 -> 16.2 us, 320x479 (9) 13.7 -> 12.4, 256x256 (4)
+// 7.5 -> 7.9; [64 | 64]->64 at 512x512 (8) 13.2 -> 12.2, 600x900 (17) 22.2 -> 19.6, 320x480 (4.7)
+// 10.4 -> 10.9.
 static bool use_rows2k(int N, int H, int W, const BlobLayout &L, bool wants_bits)
 {
     if (!conv_rows2k_supported(H, W, L, wants_bits)) return false;
     if (t_cfg.tune_rw == 9) return true;
     if (t_cfg.tune_rw != 0) return false;
     const long wave_rows = (long)N * H * ceil_div(W, 32) * (L.cout >> 5);
-    return L.cout <= 128 && wave_rows >= 24L * 2048;
+    return L.cout <= 128 && wave_rows >= 6L * 2048;
 }
 static const int kPersistentBlocks = 512;   // resident blocks of the block-cooperative kernel (2 per CU)
 
