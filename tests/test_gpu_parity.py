@@ -39,6 +39,19 @@ def test_pack_act_int8_and_float(C):
     assert np.array_equal(got, bitref.pack_pm1(np.where(f >= 0, 1, -1)))
 
 
+@pytest.mark.parametrize("C", [4, 12, 28, 36, 44, 100, 124])
+def test_pack_act_words_that_end_early(C):
+    """A multiple of four channels that is no multiple of 32: packed four values at a time."""
+    say(f"pack_act ragged C={C}")
+    rng = np.random.default_rng(C)
+    a = synth.pm1_bits(rng, (3, 7, 9, C))
+    a.ravel()[::7] = 0                                   # 0 is not > 0
+    assert np.array_equal(host_u32(B.pack_act(dev(a))), bitref.pack_pm1(np.where(a > 0, 1, -1).astype(np.int8)))
+    f = rng.standard_normal((3, 7, 9, C)).astype(np.float32)
+    f.ravel()[::5], f.ravel()[1::7], f.ravel()[2::11] = 0.0, -0.0, np.nan
+    assert np.array_equal(host_u32(B.pack_act(dev(f))), bitref.pack_pm1(np.where(f >= 0, 1, -1).astype(np.int8)))
+
+
 def run_layer(case, path, want_acc=True):
     B.set_conv_path(path)
     N, H, W, Cin = case.a.shape
