@@ -455,6 +455,8 @@ TCONV_SHAPES = [
     (2, 5, 37, 256, 96),      # four input steps: weights-resident kernel, ragged groups, two images
     (1, 7, 70, 512, 64),      # eight steps, groups of two rows
     (1, 9, 33, 128, 128),     # two steps, groups of four rows with a ragged last group
+    (2, 7, 45, 64, 96),       # one step, weights resident
+    (1, 1, 1, 64, 32),
 ]
 
 
