@@ -38,6 +38,7 @@
 // values k = 16t + 8h + i of pixel x0 + j through a raw buffer resource - a border tap or a
 // padded k gets an offset beyond the buffer and reads 0.0f.
 #include "mbu_internal.h"
+#include <type_traits>
 #include "mfma_common.h"
 #include <algorithm>
 
@@ -729,31 +730,34 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         }
     };
 
-    // the sum of one output in its defined order (ky, kx, ci); a tap outside the image is skipped.  One
-    // row of taps at a time: all 27 pairs at once would cost the tile loop its registers.
-    auto chain = [&](int y, int x, int ch) {
+    // the sum of one output in its defined order (ky, kx, ci); a tap outside the image is skipped.  R rows
+    // of taps are fetched at a time: inside the tile loop one, because all 27 pairs would cost it its
+    // registers; behind it, where their latency is the end of the launch, all three.
+    auto chain = [&](auto at_once, int y, int x, int ch) {
+        constexpr int R = decltype(at_once)::value;
         float sum = 0.0f;
 #pragma unroll 1
-        for (int ky = 0; ky < 3; ++ky) {
-            const int yy = y + ky - 1;
-            float pv[9], wv[9];
+        for (int k0 = 0; k0 < 3; k0 += R) {
+            float pv[9 * R], wv[9 * R];
 #pragma unroll
-            for (int u = 0; u < 9; ++u) {
-                const int xx = x + u / 3 - 1;
+            for (int u = 0; u < 9 * R; ++u) {
+                const int yy = y + k0 + u / 9 - 1, xx = x + u % 9 / 3 - 1;
                 const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
                 const uint32_t o = (uint32_t)(((((size_t)n * 3 + u % 3) * H + yy) * W + xx) * 4);
                 pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, ok ? o : OOB, 0, 0));
-                wv[u] = w[(size_t)ch * KV + ky * 9 + u];
+                wv[u] = w[(size_t)ch * KV + k0 * 9 + u];
             }
 #pragma unroll
-            for (int u = 0; u < 9; ++u) {
-                const int xx = x + u / 3 - 1;
+            for (int u = 0; u < 9 * R; ++u) {
+                const int yy = y + k0 + u / 9 - 1, xx = x + u % 9 / 3 - 1;
                 const float f = __builtin_fmaf(wv[u], pv[u], sum);
                 sum = yy >= 0 && yy < H && xx >= 0 && xx < W ? f : sum;
             }
         }
         return sum;
     };
+    constexpr std::integral_constant<int, 1> ONE_ROW{};
+    constexpr std::integral_constant<int, 3> ALL_ROWS{};
     int qn = 0;   // entries of the list of undecided outputs
     // ---- decision and store of a finished row
     struct Done { float T; bool zero; int i; };
@@ -823,7 +827,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                         while (fl[m]) {
                             const int e = __builtin_ctz(fl[m]);
                             fl[m] &= fl[m] - 1;
-                            const float sum = chain(y, xo, chunk * 64 + m * 32 + 16 * half + e);
+                            const float sum = chain(ONE_ROW, y, xo, chunk * 64 + m * 32 + 16 * half + e);
                             ep.sg[m] = (ep.sg[m] & ~(1u << e)) | ((sum >= 0.0f ? 0u : 1u) << e);   // NaN -> bit 0
                         }
                 }
@@ -901,13 +905,13 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         for (int k = 0; k < STAGE_PIECES; ++k) stage_piece(k, a, rm, st, B0);
     }
     // the listed outputs, one per lane
-    auto flush = [&]() {
+    auto flush = [&](auto at_once) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the words with the provisional bits are out
         for (int b = 0; b < qn; b += 64)
             if (b + lane < qn) {
                 const uint32_t en = ldsw[SR_Q + b + lane];
                 const int y = y0 + (int)(en >> 11), x = x0 + (int)(en & 31u), ch = chunk * 64 + (int)(en >> 5 & 63u);
-                const float sum = chain(y, x, ch);
+                const float sum = chain(at_once, y, x, ch);
                 uint32_t *const word = out + (((size_t)n * H + y) * W + x) * Cow + (ch >> 5);
                 if (sum >= 0.0f) atomicOr(word, 1u << (ch & 31));
                 else atomicAnd(word, ~(1u << (ch & 31)));   // NaN -> bit 0
@@ -917,14 +921,12 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     // two rows per trip (operand planes and fetch registers alternate); with an odd row count the
     // second row of the last trip is computed and dropped.  A row lists at most 64 outputs.
 #pragma unroll 1
-    for (int i = 0;; i += 2) {
-        if (i >= rows || qn > SR_QCAP - 128) {
-            flush();
-            if (i >= rows) break;
-        }
+    for (int i = 0; i < rows; i += 2) {
+        if (qn > SR_QCAP - 128) flush(ONE_ROW);
         tile(i, B0, B1, a, rm, ld0);
         tile(i + 1, B1, B0, a, rm, ld1);
     }
+    if (qn) flush(ALL_ROWS);
 }
 
 static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int W, const float *w, int Co,
