@@ -434,7 +434,7 @@ __global__ __launch_bounds__(256, RG == 2 ? 4 : 2) void tconv_bits_kernel(
 // a wave's reads are conflict-free); the fetch of the next group is in flight while the current
 // one multiplies, one barrier per group.  With KS <= 16 input steps the weights of a wave's
 // position and channel tile are only 8 KS registers: loaded once.  A group's first step takes
-// -theta as the addend of its matrix instructions.  RGX rows of 32 pixels per group, so that a group is 1024 words (512 for
+// -theta as the addend of its matrix instructions.  RGX rows of 32 pixels per group, so that a group is 1024 words or so (512 for
 // KS = 2, 256 for KS = 1): one fetch per thread.
 // Needs an even word count (Cin a multiple of 64).
 template <int KS, int RGX>
@@ -446,8 +446,8 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
     constexpr uint32_t BAD = 0x40000000u;   // beyond any tensor this kernel accepts (< 2^30 bytes)
     constexpr int CW = 2 * KS;              // words per pixel
     constexpr int TILE = RGX * CW * 32;     // words per pixel group
-    constexpr int PW = TILE / 256;          // words per thread and group: 4 (2 for KS = 2, 1 for KS = 1)
-    static_assert(PW == 4 || PW == 2 || PW == 1, "one fetch per thread");
+    constexpr int PW = TILE / 256;          // words per thread and group: 1 ... 5
+    static_assert(TILE % 256 == 0 && PW <= 5 && CW % PW == 0, "a thread's words belong to one pixel");
     __shared__ float4 init_tab[4][2][2][4]; // [position][half][m][4 x 4 channels]: -(theta + sum w) / 2
     __shared__ uint32_t words[2][TILE];     // [buffer][row][word][pixel]
     const int tid = threadIdx.x;
@@ -514,16 +514,20 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
         const int x = P.gx * 32 + spx, y = P.gy * RGX + sr;
         // a pixel outside the image: any offset beyond the tensor (reads 0; nothing of it is stored)
         const uint32_t off = (x < W && y < H) ? (uint32_t)((((P.n * H + y) * W + x) * CW + k0) * 4) : BAD;
-        if (PW == 4) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(ars, off, 0, 0);
 #pragma unroll
-            for (int i = 0; i < PW; ++i) st[i] = v[i];
-        } else if (PW == 2) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(ars, off, 0, 0);
+        for (int i = 0; i < PW; i += 4) {
+            if (PW - i >= 4) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(ars, off, 4 * i, 0);
 #pragma unroll
-            for (int i = 0; i < PW; ++i) st[i] = v[i];
-        } else {
-            st[0] = __builtin_amdgcn_raw_buffer_load_b32(ars, off, 0, 0);
+                for (int k = 0; k < 4; ++k) st[min(i + k, PW - 1)] = v[k];
+            } else {
+                if (PW - i >= 2) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(ars, off, 4 * i, 0);
+                    st[i] = v[0];
+                    st[min(i + 1, PW - 1)] = v[1];
+                }
+                if ((PW - i) & 1) st[PW - 1] = __builtin_amdgcn_raw_buffer_load_b32(ars, off, 4 * (PW - 1), 0);
+            }
         }
     };
     auto commit = [&](int buf, const uint32_t (&st)[PW]) {
@@ -639,10 +643,15 @@ int launch_tconv_mfma(const uint32_t *act, int N, int H, int W, const TconvLayou
     const int tiles64 = L.cout_pad64 / 64;
     const double GiB = 1073741824.0;
     const bool small = (double)N * H * W * L.cin_words * 4 < GiB && (double)N * H * W * 4 * (L.cout >> 5) * 4 < GiB;
-    // 64, 128, 256, 512 or 1024 input channels (an even word count): weights resident (64->64 at 8x160x239
-    // 18.5 us with the general kernel below, 10.4 with this one)
+    // 64 ... 1024 input channels where a group divides evenly over the block: weights resident.  Against the
+    // kernels below: 64->64 at 8x160x239 18.5 -> 10.4 us, 192->96 at 2x160x239 11.2 -> 8.3, 320->512 at
+    // 20x872 16.2 -> 10.3, 384->192 at 4x80x80 12.5 -> 8.6, 768->512 at 64x64 10.5 -> 7.0.
     if (!out_acc && small && L.cin_words == 2 * L.ksteps) {
         if (L.ksteps == 1) return launch_tconv_res<1, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        if (L.ksteps == 3) return launch_tconv_res<3, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        if (L.ksteps == 5) return launch_tconv_res<5, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        if (L.ksteps == 6) return launch_tconv_res<6, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        if (L.ksteps == 12) return launch_tconv_res<12, 1>(act, N, H, W, L, wfrag, thresh, out_bits, s);
         if (L.ksteps == 2) return launch_tconv_res<2, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
         if (L.ksteps == 4) return launch_tconv_res<4, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
         if (L.ksteps == 8) return launch_tconv_res<8, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);

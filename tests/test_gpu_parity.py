@@ -457,6 +457,11 @@ TCONV_SHAPES = [
     (1, 9, 33, 128, 128),     # two steps, groups of four rows with a ragged last group
     (2, 7, 45, 64, 96),       # one step, weights resident
     (1, 1, 1, 64, 32),
+    (1, 9, 35, 192, 64),      # three, five, six and twelve steps, weights resident
+    (2, 6, 33, 320, 96),
+    (1, 5, 34, 384, 64),
+    (1, 3, 40, 768, 64),
+    (1, 7, 50, 448, 64),      # seven: not resident
 ]
 
 
