@@ -466,11 +466,11 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 //     h = 1:  P2[j] P2[j+1] P2[j+2] R2[j]  |  R2[j+1] R2[j+2] R01[j+2] (1.0, 0)
 // The last dword is the constant that gives an all-zero weight row a decidable estimate (see
 // the kernel above).  The weights are loaded in the same order.
-// Bound by the vector ALU: about 165 vector instructions a tile against 12 matrix instructions, which
-// it does not overlap (counters at 1024x2048: matrix 32 %, vector 66 % of the SIMD cycles).  The
-// undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, and a block's
-// waves share the preparation of the weights: 41.0 -> 40.1 us at 1024x2048, 315 -> 306 us at
-// 32x640x959, 2 us of a 64x96 network's 87.
+// Bound by the vector ALU: about 180 vector instructions a tile, prologue included, against 12 matrix
+// instructions, which it does not overlap (counters at 1024x2048: matrix 34 %, vector 63 % of the SIMD
+// cycles).  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
+// taps of a sum fetched at once, and a block's waves share the preparation of the weights, behind the
+// fetches of the first image rows: 41.0 -> 39.0 us at 1024x2048, 315 -> 306 us at 32x640x959.
 constexpr int SR_HW = 34;                    // halo pixels of a strip
 constexpr int SR_ARR = 36;                   // dwords per LDS array (34 used)
 constexpr int SR_PLANE = 5 * SR_ARR;         // arrays P0 P1 R01 P2 R2 of one plane (hi or lo)
