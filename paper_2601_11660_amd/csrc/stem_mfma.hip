@@ -38,7 +38,6 @@
 // values k = 16t + 8h + i of pixel x0 + j through a raw buffer resource - a border tap or a
 // padded k gets an offset beyond the buffer and reads 0.0f.
 #include "mbu_internal.h"
-#include <type_traits>
 #include "mfma_common.h"
 #include <algorithm>
 
@@ -470,7 +469,11 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 // instructions, which it does not overlap (counters at 1024x2048: matrix 34 %, vector 63 % of the SIMD
 // cycles).  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
 // taps of a sum fetched at once, and a block's waves share the preparation of the weights, behind the
-// fetches of the first image rows: 41.0 -> 39.0 us at 1024x2048, 315 -> 306 us at 32x640x959.
+// fetches of the first image rows: 41.0 -> 37.1 us at 1024x2048, 315 -> 306 us at 32x640x959.  A tile with
+// many undecided outputs (non-finite or tiny windows, a weight row out of range, dense ties) sums them in the
+// lanes that hold them, a pixel's patch fetched once for all of them: with every output undecided 512x1024 x 64
+// takes 124 us, with 200 NaN pixels 50, ordinary data 15.2 (a patch fetched again for every output, a kernel
+// row at a time: 560 and 392).
 constexpr int SR_HW = 34;                    // halo pixels of a strip
 constexpr int SR_ARR = 36;                   // dwords per LDS array (34 used)
 constexpr int SR_PLANE = 5 * SR_ARR;         // arrays P0 P1 R01 P2 R2 of one plane (hi or lo)
@@ -730,34 +733,35 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         }
     };
 
-    // the sum of one output in its defined order (ky, kx, ci); a tap outside the image is skipped.  R rows
-    // of taps are fetched at a time: inside the tile loop one, because all 27 pairs would cost it its
-    // registers; behind it, where their latency is the end of the launch, all three.
-    auto chain = [&](auto at_once, int y, int x, int ch) {
-        constexpr int R = decltype(at_once)::value;
-        float sum = 0.0f;
-#pragma unroll 1
-        for (int k0 = 0; k0 < 3; k0 += R) {
-            float pv[9 * R], wv[9 * R];
+    // the sum of one output in its defined order (ky, kx, ci), term u = (ky * 3 + kx) * 3 + ci; a tap outside the
+    // image is skipped
+    struct Pixel { uint32_t off; bool up, dn, lf, rt; };   // offset in channel 0; has a neighbour on that side
+    auto pixel = [&](int y, int x) {
+        return Pixel{(uint32_t)((((size_t)n * 3 * H + y) * W + x) * 4), y > 0, y < H - 1, x > 0, x < W - 1};
+    };
+    auto inside = [](int u, const Pixel &px) {
+        const int ky = u / 9, kx = u % 9 / 3;
+        return (ky == 1 || (ky == 0 ? px.up : px.dn)) && (kx == 1 || (kx == 0 ? px.lf : px.rt));
+    };
+    auto patch = [&](const Pixel &px, float (&pv)[KV]) {
 #pragma unroll
-            for (int u = 0; u < 9 * R; ++u) {
-                const int yy = y + k0 + u / 9 - 1, xx = x + u % 9 / 3 - 1;
-                const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
-                const uint32_t o = (uint32_t)(((((size_t)n * 3 + u % 3) * H + yy) * W + xx) * 4);
-                pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, ok ? o : OOB, 0, 0));
-                wv[u] = w[(size_t)ch * KV + k0 * 9 + u];
-            }
+        for (int u = 0; u < KV; ++u) {
+            const uint32_t o = px.off + (uint32_t)(((u % 3 * H + u / 9 - 1) * W + u % 9 / 3 - 1) * 4);
+            pv[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, inside(u, px) ? o : OOB, 0, 0));
+        }
+    };
+    auto chain = [&](const Pixel &px, const float (&pv)[KV], int ch) {
+        const float *const wp = w + (size_t)ch * KV;
+        float wv[KV], sum = 0.0f;
 #pragma unroll
-            for (int u = 0; u < 9 * R; ++u) {
-                const int yy = y + k0 + u / 9 - 1, xx = x + u % 9 / 3 - 1;
-                const float f = __builtin_fmaf(wv[u], pv[u], sum);
-                sum = yy >= 0 && yy < H && xx >= 0 && xx < W ? f : sum;
-            }
+        for (int u = 0; u < KV; ++u) wv[u] = wp[u];   // in one batch
+#pragma unroll
+        for (int u = 0; u < KV; ++u) {
+            const float f = __builtin_fmaf(wv[u], pv[u], sum);
+            sum = inside(u, px) ? f : sum;
         }
         return sum;
     };
-    constexpr std::integral_constant<int, 1> ONE_ROW{};
-    constexpr std::integral_constant<int, 3> ALL_ROWS{};
     int qn = 0;   // entries of the list of undecided outputs
     // ---- decision and store of a finished row
     struct Done { float T; bool zero; int i; };
@@ -822,14 +826,18 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                         qn += __builtin_popcountll(who);
                     }
                 } else if (flag) {
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        while (fl[m]) {
-                            const int e = __builtin_ctz(fl[m]);
-                            fl[m] &= fl[m] - 1;
-                            const float sum = chain(ONE_ROW, y, xo, chunk * 64 + m * 32 + 16 * half + e);
-                            ep.sg[m] = (ep.sg[m] & ~(1u << e)) | ((sum >= 0.0f ? 0u : 1u) << e);   // NaN -> bit 0
-                        }
+                    // the patch is fetched once for all of the pixel's outputs
+                    const Pixel px = pixel(y, xo);
+                    float pv[KV];
+                    patch(px, pv);
+                    uint32_t neg = 0;
+                    for (uint32_t left = todo; left; left &= left - 1) {
+                        const int b = __builtin_ctz(left);
+                        const float sum = chain(px, pv, chunk * 64 + (b >> 4) * 32 + 16 * half + (b & 15));
+                        neg |= (sum >= 0.0f ? 0u : 1u) << b;   // NaN -> bit 0
+                    }
+                    ep.sg[0] = (ep.sg[0] & ~todo) | (neg & 0xffffu);
+                    ep.sg[1] = (ep.sg[1] & ~(todo >> 16)) | (neg >> 16);
                 }
             }
             if (dn.zero) { ep.sg[0] = 0u; ep.sg[1] = 0u; }   // a chain of zero terms ends at +0.0f
@@ -905,13 +913,16 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         for (int k = 0; k < STAGE_PIECES; ++k) stage_piece(k, a, rm, st, B0);
     }
     // the listed outputs, one per lane
-    auto flush = [&](auto at_once) {
+    auto flush = [&]() {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the words with the provisional bits are out
         for (int b = 0; b < qn; b += 64)
             if (b + lane < qn) {
                 const uint32_t en = ldsw[SR_Q + b + lane];
                 const int y = y0 + (int)(en >> 11), x = x0 + (int)(en & 31u), ch = chunk * 64 + (int)(en >> 5 & 63u);
-                const float sum = chain(at_once, y, x, ch);
+                const Pixel px = pixel(y, x);
+                float pv[KV];
+                patch(px, pv);
+                const float sum = chain(px, pv, ch);
                 uint32_t *const word = out + (((size_t)n * H + y) * W + x) * Cow + (ch >> 5);
                 if (sum >= 0.0f) atomicOr(word, 1u << (ch & 31));
                 else atomicAnd(word, ~(1u << (ch & 31)));   // NaN -> bit 0
@@ -922,11 +933,11 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     // second row of the last trip is computed and dropped.  A row lists at most 64 outputs.
 #pragma unroll 1
     for (int i = 0; i < rows; i += 2) {
-        if (qn > SR_QCAP - 128) flush(ONE_ROW);
+        if (qn > SR_QCAP - 128) flush();
         tile(i, B0, B1, a, rm, ld0);
         tile(i + 1, B1, B0, a, rm, ld1);
     }
-    if (qn) flush(ALL_ROWS);
+    if (qn) flush();
 }
 
 static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int W, const float *w, int Co,

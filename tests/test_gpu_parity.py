@@ -1103,6 +1103,47 @@ def test_stem_lists_of_undecided_outputs(ties):
     assert torch.equal(bits, ref)
 
 
+def test_stem_tiles_with_many_undecided_outputs():
+    """Row-walking kernel on data that leaves whole tiles undecided: the bits of the chain kernel, at a
+    price per output that shares the fetches of a patch among the outputs of a pixel.  Measured against
+    ordinary data: 8 times with every output undecided, 3 with one pixel in 60 near a NaN; 34 and 24 when
+    every output fetches its patch for itself."""
+    say("stem tiles with many undecided outputs")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    img = torch.randn((1, 3, 512, 1024), generator=g, device="cuda")
+    wts = torch.randn((64, 3, 3, 3), generator=g, device="cuda")
+    row = wts.clone()
+    row[5] *= 1e30                                      # its norm is out of range: no bound for any output
+    nan = img.clone()
+    nan.view(-1)[torch.randint(0, nan.numel(), (200,), generator=g, device="cuda")] = float("nan")
+    tiny = img.clone()
+    tiny[:, :, :128] *= 2.0 ** -120                     # windows below the range of the shared scale
+
+    def time(x, w):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = float("inf")
+        for _ in range(5):
+            e[0].record()
+            for _ in range(20):
+                B.stem_fp32(x, w)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 20)
+        return best
+
+    ordinary = time(img, wts)
+    for name, x, w, most in (("row out of range", img, row, 16), ("NaN", nan, wts, 9), ("tiny", tiny, wts, 9)):
+        bits, _ = B.stem_fp32(x, w)
+        B.set_stem_path(B.STEM_VALU)
+        try:
+            ref, _ = B.stem_fp32(x, w)
+            torch.cuda.synchronize()
+        finally:
+            B.set_stem_path(B.STEM_AUTO)
+        assert torch.equal(bits, ref), name
+        assert time(x, w) < most * ordinary, name
+
+
 def test_stem_full_size_frame():
     """All 134 M outputs of the benchmark frame's first layer against the oracle."""
     case = synth.unet_case(3, 0, 1, 1024, 2048, keep=0.6)
