@@ -953,7 +953,7 @@ static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int 
     seg_rows = std::max(2, seg_rows + (seg_rows & 1));
     const int nseg = ceil_div(H, seg_rows);
     const long units = (long)N * strips * nseg;   // of every chunk
-    if ((units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");
+    if (units > 0x7fffffffL || (units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");
     MBU_LAUNCH(stem_rows_kernel, dim3((unsigned)((units + 3) / 4 * nchunks)), dim3(256), 0, s, img, bytes, H, W, w, Co,
                nchunks, strips, nseg, seg_rows, (int)units, out_bits);
     return check_launch("stem_rows");
