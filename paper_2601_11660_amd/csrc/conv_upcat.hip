@@ -408,7 +408,7 @@ struct UpSplitGeo {
 };
 
 template <int NC, int TWC>
-__global__ __launch_bounds__(512) void conv_mfma_upcat_kernel(
+__global__ __launch_bounds__(512) void conv_mfma_upcat_split_kernel(
     const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int ksA, int ksL,
     const uint4 *__restrict__ wfrag, const uint4 *__restrict__ wup, int Cout, int log_s, int tiles_y,
     const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum, uint32_t *__restrict__ out_bits)
@@ -724,7 +724,7 @@ static int launch_upcat_split(int log_s, const uint32_t *act, int Ca, const uint
 {
     using G = UpSplitGeo<NC, TWC>;
     const int tiles_x = ceil_div(W / 2, TWC), tiles_y = ceil_div(H / 2, G::RS);
-    MBU_LAUNCH((conv_mfma_upcat_kernel<NC, TWC>),
+    MBU_LAUNCH((conv_mfma_upcat_split_kernel<NC, TWC>),
                dim3((unsigned)(L.cout >> 5), (unsigned)(tiles_x * (4 / NC)), (unsigned)(N * tiles_y)), dim3(64 << log_s),
                (size_t)G::lds_bytes(1 << log_s), s, act, low, N, H, W, Ca / 64, Clow / 64, wfrag, wup, L.cout, log_s,
                tiles_y, thresh, wsum, out_bits);

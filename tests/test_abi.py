@@ -210,6 +210,9 @@ def test_unet_plan_validation_and_workspace():
     assert kern["enc1a"] == "conv_mfma_rows_kernel" and kern["dec1a"] == "conv_mfma_upcat_kernel"
     assert kern["enc4b"] == "conv_mfma_block_kernel" and kern["cat1"] == "" and kern["pool1"] == ""
     k = ctypes.c_char_p()
+    # the same step of a small frame runs another kernel, under another name
+    assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 64, 128, 25, ctypes.byref(k)) == 0
+    assert k.value.decode() == "conv_mfma_upcat_split_kernel"
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 75, 131, 25, ctypes.byref(k)) == 0   # dec1a, padded
     assert k.value.decode() == "conv_mfma_block_kernel"
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 64, 128, 99, ctypes.byref(k)) == B.MBU_ERR_ARG

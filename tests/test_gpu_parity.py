@@ -1323,7 +1323,7 @@ def test_blob_sections():
     case = synth.unet_case(2, 3, 1, 64, 96, base=64, levels=2, n_classes=5)
     lean = build_unet(case, True)
     assert lean.sections == [B.BLOB_MATRIX] * 6 + [B.BLOB_MATRIX | B.BLOB_SUMMED_TAPS, B.BLOB_MATRIX] * 2
-    assert [lean.step_kernel(1, 64, 96, s) for s in (10, 13)] == ["conv_mfma_upcat_kernel"] * 2
+    assert [lean.step_kernel(1, 64, 96, s) for s in (10, 13)] == ["conv_mfma_upcat_split_kernel"] * 2
     full = B.UNet(dev(case.stem_w), [(dev(w), dev(t)) for w, t in case.convs], dev(case.cls_w),
                   dev(case.cls_b), levels=2, all_sections=True)
     assert sum(b.numel() for b in lean.blobs) < 0.5 * sum(b.numel() for b in full.blobs)
