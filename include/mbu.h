@@ -60,6 +60,11 @@ typedef enum mbu_conv_path {
  * owned by the library, valid until the next failing call on the thread. */
 const char *mbu_last_error(void);
 
+/* The kernel, with its template arguments, that the last call of this thread launched last (or, after
+ * mbu_unet_step_kernel, that the step would launch), for tests and profiles; "" if none.  Host pointer, owned by the library, valid until the next call of this
+ * function on the thread. */
+const char *mbu_last_kernel(void);
+
 /* Select the convolution implementation process-wide.  MBU_ERR_ARG on a bad value.
  * Thread safety of this and the other setters (mbu_set_conv_tuning, mbu_set_stem_path): the
  * settings are process-wide atomics; every other entry point reads them ONCE when it is

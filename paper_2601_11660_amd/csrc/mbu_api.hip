@@ -1,7 +1,10 @@
 // C-ABI entry points: argument validation, dispatch, and the network walk.
+#include <cxxabi.h>
+#include <dlfcn.h>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 #include "mbu_internal.h"
@@ -19,7 +22,7 @@ static std::atomic<int> g_conv_path{MBU_PATH_AUTO};
 static std::atomic<int> g_stem_path{MBU_STEM_AUTO};
 static std::atomic<int> g_tune_rw{0};
 
-thread_local CallCfg t_cfg = {MBU_PATH_AUTO, MBU_STEM_AUTO, 0, false, ""};
+thread_local CallCfg t_cfg = {MBU_PATH_AUTO, MBU_STEM_AUTO, 0, false, "", nullptr};
 
 void begin_call(bool dry_run)
 {
@@ -28,6 +31,7 @@ void begin_call(bool dry_run)
     t_cfg.tune_rw = g_tune_rw.load(std::memory_order_relaxed);
     t_cfg.dry_run = dry_run;
     t_cfg.kernel = "";
+    t_cfg.kernel_fn = nullptr;
 }
 
 int fail(int code, const char *fmt, ...)
@@ -228,6 +232,21 @@ static const char *kernel_base_name(const char *written)
     return name;
 }
 
+// handle of a kernel -> "conv_mfma_block_kernel<2, 1, 4, true, false, true>", from the library's symbols
+static const char *kernel_instance_name(const void *fn)
+{
+    static thread_local char name[160];
+    name[0] = 0;
+    Dl_info info;
+    if (!fn || !dladdr(fn, &info) || info.dli_saddr != fn || !info.dli_sname) return name;
+    char *full = abi::__cxa_demangle(info.dli_sname, nullptr, nullptr, nullptr);   // void mbu::kernel<...>(...)
+    if (!full) return name;
+    const char *p = strstr(full, "mbu::");
+    snprintf(name, sizeof(name), "%.*s", p ? (int)strcspn(p + 5, "(") : 0, p ? p + 5 : "");
+    free(full);
+    return name;
+}
+
 static int run_conv(const uint32_t *act, int N, int H, int W, const BlobLayout &L, const void *packed_w,
                     const int32_t *thresh, uint32_t *out_bits, int32_t *out_acc, hipStream_t s)
 {
@@ -256,6 +275,8 @@ using namespace mbu;
 extern "C" {
 
 const char *mbu_last_error(void) { return g_err; }
+
+const char *mbu_last_kernel(void) { return kernel_instance_name(t_cfg.kernel_fn); }
 
 int mbu_set_conv_path(int path)
 {
@@ -634,11 +655,15 @@ namespace mbu {
 
 // The network walk shared by mbu_unet_forward and mbu_unet_step_kernel.  With t_cfg.dry_run
 // set nothing is launched and no event is recorded; the launchers still make their choices and
-// leave the chosen kernel's name in t_cfg.kernel, which is copied to kernel_of_step[i] for every
-// step that launches one ("" for a step folded into a neighbouring layer).
+// leave the chosen kernel in t_cfg, from where it is copied to kernel_of_step[i] for every
+// step that launches one (name "" for a step folded into a neighbouring layer).
+struct StepKernel {
+    const char *name;
+    const void *fn;
+};
 static int walk(const mbu_unet_desc *d, const std::vector<Step> &steps, const float *image_nchw,
                 int N, int H, int W, float *logits_nchw, uint8_t *ws, hipStream_t s,
-                const char **kernel_of_step)
+                StepKernel *kernel_of_step)
 {
     const char *fn = "mbu_unet_forward";
     const bool dry = t_cfg.dry_run;
@@ -652,6 +677,7 @@ static int walk(const mbu_unet_desc *d, const std::vector<Step> &steps, const fl
             hipEventRecord((hipEvent_t)d->step_events[i], s) != hipSuccess)
             return fail(MBU_ERR_HIP, "%s: hipEventRecord failed", fn);
         t_cfg.kernel = "";
+        t_cfg.kernel_fn = nullptr;
         switch (st.kind) {
         case Step::STEM:
             rc = run_stem(image_nchw, N, d->in_channels, H, W, d->stem_w, d->base, buf((int)i), nullptr, s);
@@ -705,7 +731,7 @@ static int walk(const mbu_unet_desc *d, const std::vector<Step> &steps, const fl
             break;
         }
         if (rc) return rc;
-        if (kernel_of_step) kernel_of_step[i] = t_cfg.kernel;
+        if (kernel_of_step) kernel_of_step[i] = StepKernel{t_cfg.kernel, t_cfg.kernel_fn};
     }
     if (!dry && d->step_events && hipEventRecord((hipEvent_t)d->step_events[steps.size()], s) != hipSuccess)
         return fail(MBU_ERR_HIP, "%s: hipEventRecord failed", fn);
@@ -794,12 +820,13 @@ int mbu_unet_step_kernel(const mbu_unet_desc *d, int N, int H, int W, int step, 
     int rc = build_plan(d, N, H, W, steps, nullptr);
     if (rc) return rc;
     if (step < 0 || step >= (int)steps.size()) return fail(MBU_ERR_ARG, "%s: step %d out of range", fn, step);
-    std::vector<const char *> names(steps.size(), "");
+    std::vector<StepKernel> chosen(steps.size(), StepKernel{"", nullptr});
     // a dry run dereferences no device pointer; the workspace is only an address base
-    rc = walk(d, steps, nullptr, N, H, W, nullptr, (uint8_t *)256, nullptr, names.data());
+    rc = walk(d, steps, nullptr, N, H, W, nullptr, (uint8_t *)256, nullptr, chosen.data());
     t_cfg.dry_run = false;
     if (rc) return rc;
-    *kernel = kernel_base_name(names[step]);
+    *kernel = kernel_base_name(chosen[step].name);
+    t_cfg.kernel_fn = chosen[step].fn;
     return MBU_OK;
 }
 

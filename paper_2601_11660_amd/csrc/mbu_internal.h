@@ -22,6 +22,7 @@ struct CallCfg {
     int tune_rw;        // kernel variant of the matrix-path convolution, 0 = automatic
     bool dry_run;       // true: launchers choose their kernel and record its name, launch nothing
     const char *kernel; // source name of the last kernel chosen by a launcher on this thread
+    const void *kernel_fn; // ... and its handle, which differs between instances of a template
 };
 extern thread_local CallCfg t_cfg;
 void begin_call(bool dry_run = false);
@@ -32,6 +33,7 @@ void begin_call(bool dry_run = false);
 #define MBU_LAUNCH(KERNEL_, grid, block, shmem, stream, ...)                         \
     do {                                                                            \
         mbu::t_cfg.kernel = #KERNEL_;                                               \
+        mbu::t_cfg.kernel_fn = reinterpret_cast<const void *>(KERNEL_);              \
         if (!mbu::t_cfg.dry_run) {                                                  \
             (void)hipGetLastError();                                                \
             hipLaunchKernelGGL(KERNEL_, grid, block, shmem, stream, __VA_ARGS__);    \

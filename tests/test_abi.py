@@ -206,6 +206,7 @@ def test_unet_plan_validation_and_workspace():
         k = ctypes.c_char_p()
         assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 1024, 2048, s, ctypes.byref(k)) == 0
         kern[names[s] if s < 27 else "classifier"] = k.value.decode()
+    assert B.last_kernel() == "classifier_kernel<2>"
     assert kern["stem"] == "stem_rows_kernel" and kern["classifier"].startswith("classifier_kernel")
     assert kern["enc1a"] == "conv_mfma_rows_kernel" and kern["dec1a"] == "conv_mfma_upcat_kernel"
     assert kern["enc4b"] == "conv_mfma_block_kernel" and kern["cat1"] == "" and kern["pool1"] == ""
@@ -213,6 +214,7 @@ def test_unet_plan_validation_and_workspace():
     # the same step of a small frame runs another kernel, under another name
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 64, 128, 25, ctypes.byref(k)) == 0
     assert k.value.decode() == "conv_mfma_upcat_split_kernel"
+    assert B.last_kernel() == "conv_mfma_upcat_split_kernel<1, 8>"       # the instance behind the name
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 75, 131, 25, ctypes.byref(k)) == 0   # dec1a, padded
     assert k.value.decode() == "conv_mfma_block_kernel"
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 64, 128, 99, ctypes.byref(k)) == B.MBU_ERR_ARG
