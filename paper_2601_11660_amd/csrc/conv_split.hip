@@ -239,16 +239,22 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
 }
 
 
-// When, and with which tile.  Both sides measured with a kernel trace, caches flushed between launches:
-//  - The other kernels run waves of 4 rows x 32 pixels x 64 channels (x 4 parity classes of low pixels for an
-//    up-sampled second input).  Below 512 such waves this kernel wins (256 waves: 512->512 at 64x64 10.0
-//    against 14.1 us; 320: 1024->1024 at 40x59 16.9 against 23.5), at 512 they are even (256->256 at
-//    128x128 9.9 against 9.8 us), beyond they win (640: 512->512 at 80x119 17.0 against 13.3 us).
-//  - Tile: a unit is 9 matrix instructions (one group, 32 channels, one step).  Up to 4096 units a wave
+// When, and with which tile.  Both sides measured with a kernel trace, caches flushed between launches; a unit
+// is 9 matrix instructions (one group, 32 channels, one step):
+//  - The block kernel with two rows per wave takes about 4.3 us + 0.8 per input step while its blocks have a
+//    compute unit each; this kernel's time grows with groups x channel tiles.  They meet at 2048 of these, two
+//    for a SIMD.  Block -> here: 4 steps 53x128, 1696, 7.2 -> 6.2 us; 64x64, 2048, 7.0 -> 6.8; 192x96, 2304,
+//    7.3 -> 7.2; 142x160, 2840, 7.2 -> 8.0.  8 steps 81x32, 1296, 10.2 -> 7.2; 64x64, 2048, 10.1 -> 8.5; 111x96,
+//    2664, 10.4 -> 11.7.  16 steps 32x32, 1024, 16.8 -> 8.3; 64x128, 2048, 16.1 -> 14.1; 96x48, 2304, 16.5 -> 16.8.
+//    With two steps, where the fixed part is most of the time, at 1536 (75x128, 1200, 5.5 -> 5.2; 109x60, 1744,
+//    5.8 -> 6.0).
+//  - Tile: up to 4096 units a wave
 //    takes a single group (every fragment is used once, but all waves run at once: [256 | 512 up]->256 at
 //    16x24, 1152 units, 4.8 us against 5.6 with two groups); up to 12288 two groups
 //    (512->1024 at 32x32, 8192 units, 6.5 us against 7.1 with one and 7.4 with four); then four, which
-//    halve the weight traffic again (1024->1024 at 32x32, 16384 units, 9.8 against 10.5 us).
+//    halve the weight traffic again (1024->1024 at 32x32, 16384 units, 9.8 against 10.5 us), as long as the
+//    blocks of four slices are resident at once, two on a compute unit (1024->512 at 42x96, 528 blocks, 17.7 us
+//    against 15.9 with two groups).
 //    Tiles 32 wide only where they leave little more of the frame's width empty than tiles 16 wide, and a
 //    frame of 8 columns or fewer stays with single groups 8 wide.
 //  - One input step: nothing to split, but tiles of one group still spread a small layer further than the
@@ -256,15 +262,15 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
 //    5.3; even from 1200 units on, 64->128 at 128x128, 2048 units, 5.6 against 5.2).
 //  - An up-sampled second input with fewer than eight input steps stays with the kernels that take it
 //    otherwise, which callers can rely on by name (mbu_unet_step_kernel).
-//  - Slices: as many as give 2048 waves (two per SIMD), at most 8 and at most one per step.
+//  - Slices: as many as give 2048 waves (two per SIMD), at most 8 and at most one per step.  Eight slices of
+//    four groups take 129 KiB of LDS, one block on a compute unit: four, where there are more blocks than units
+//    (512->128 at 106x128, 432 blocks, 11.0 -> 8.8 us).
 SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool up, bool pool)
 {
     SplitPlan p{0, 0, 0};
-    const long tiles64 = L.cout_pad64 / 64, ctiles = L.cout >> 5;
-    const long other = up ? 4L * ceil_div((H + 1) / 2, 4) * ceil_div((W + 1) / 2, 32)
-                          : (long)ceil_div(H, 4) * ceil_div(W, 32);
+    const long ctiles = L.cout >> 5;
     if (up && L.ksteps < 8) return p;
-    if (N * other * tiles64 >= 512 || (double)N * H * W * L.cin_words * 4 >= 1073741824.0) return p;
+    if ((double)N * H * W * L.cin_words * 4 >= 1073741824.0) return p;
     long best = 0;
     for (int tw : {32, 16, 8}) {   // fewest groups; the widest of equals
         if (tw == 32 && pool) continue;   // a single row
@@ -272,16 +278,18 @@ SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool up, boo
         if (!p.tw || g < best) { p.tw = tw; best = g; }
     }
     const long units = best * ctiles * L.ksteps;
-    if (L.ksteps == 1 && units > 1200) return SplitPlan{0, 0, 0};
+    if (best * ctiles > (L.ksteps <= 2 ? 1536 : 2048) || (L.ksteps == 1 && units > 1200)) return SplitPlan{0, 0, 0};
     p.r = 1;
     if (units > 4096 && W > 8) {
         p.r = 2;
         p.tw = 16;
-        if (units > 12288 && 7 * round_up(W, 32) <= 8 * round_up(W, 16)) { p.r = 4; p.tw = 32; }
+        if (units > 12288 && 7 * round_up(W, 32) <= 8 * round_up(W, 16) &&
+            (long)N * ceil_div(W, 32) * ceil_div(H, 4) * ctiles <= 512) { p.r = 4; p.tw = 32; }
     }
     const long tiles = (long)N * ceil_div(W, p.tw) * ceil_div(H, p.r * 32 / p.tw) * ctiles;
+    const int most = p.r == 4 && tiles > 256 ? 2 : 3;
     p.log_s = 0;
-    while (p.log_s < 3 && 2 << p.log_s <= L.ksteps && tiles << p.log_s < 2048) ++p.log_s;
+    while (p.log_s < most && 2 << p.log_s <= L.ksteps && tiles << p.log_s < 2048) ++p.log_s;
     // the grid's second and third dimension end at 65535
     if (ceil_div(W, p.tw) > 65535 || (long)N * ceil_div(H, p.r * 32 / p.tw) > 65535) return SplitPlan{0, 0, 0};
     return p;

@@ -1,0 +1,54 @@
+"""Which kernel, and which instance of it, the automatic choice takes for single layers (no GPU needed: a
+dry run of a one-level network that has the layer in it)."""
+import ctypes
+
+import pytest
+
+from paper_2601_11660_amd import binding as B
+
+
+def choice(convs, n, h, w, step, up=None):
+    d = B.UNetDesc()
+    layers = (B.ConvLayer * len(convs))()
+    for c, (cin, cout) in zip(layers, convs):
+        c.cin, c.cout, c.packed_w, c.thresh = cin, cout, 0x10000, 0x20000
+    d.levels, d.base, d.in_channels, d.n_classes, d.convs, d.fuse = 1, 32, 3, 19, layers, 1
+    if up:
+        d.up_convs = (B.ConvLayer * 1)(B.ConvLayer(0x10000, 0x20000, up[0], up[1], 0))
+    name = ctypes.c_char_p()
+    assert B.lib().mbu_unet_step_kernel(ctypes.byref(d), n, h, w, step, ctypes.byref(name)) == 0, B.last_error()
+    return B.last_kernel()
+
+
+def layer(h, w, cin, cout, n=1):
+    """Second encoder layer, with the pooled output."""
+    return choice([(32, cin), (cin, cout), (cout, 32), (32, 32), (cout + 32, 32), (32, 32)], n, h, w, 2)
+
+
+def up_sampled(h, w, ca, cb, cout, n=1):
+    """Decoder layer over [skip | 2x up-sampled feature]."""
+    return choice([(32, ca), (ca, ca), (ca, cb), (cb, cb), (ca + cb, cout), (cout, 32)], n, h, w, 7)
+
+
+def concat(h, w, ca, cb, cout, n=1):
+    """Decoder layer over [skip | feature of the transposed layer]."""
+    return choice([(32, ca), (ca, ca), (ca, ca), (ca, ca), (ca + cb, cout), (cout, 32)], n, h, w, 8, (ca, cb))
+
+
+SPLIT, BLOCK = "conv_mfma_split_kernel", "conv_mfma_block_kernel"
+
+
+@pytest.mark.parametrize("h, w, cin, cout, kernel", [
+    (64, 64, 512, 512, SPLIT + "<4, 32, true, false>"),      # 2048 groups x channel tiles
+    (64, 66, 512, 512, BLOCK + "<2, 1, 4, true, false, true>"),
+    (112, 128, 256, 256, BLOCK + "<2, 1, 4, true, false, true>"),
+    (128, 128, 256, 256, BLOCK + "<2, 1, 4, true, false, true>"),
+    (128, 64, 256, 256, SPLIT + "<2, 16, true, false>"),
+    (42, 96, 1024, 512, SPLIT + "<2, 16, true, false>"),     # 528 blocks of four groups: not resident at once
+    (40, 96, 1024, 512, SPLIT + "<4, 32, true, false>"),
+    (96, 64, 128, 256, SPLIT + "<1, 16, true, false>"),      # two steps: 1536
+    (98, 64, 128, 256, BLOCK + "<2, 1, 4, true, false, true>"),
+    (4, 6, 1024, 1024, SPLIT + "<1, 8, true, false>"),
+])
+def test_small_layers_up_to_the_line(h, w, cin, cout, kernel):
+    assert layer(h, w, cin, cout) == kernel
