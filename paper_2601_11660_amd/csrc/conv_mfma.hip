@@ -916,7 +916,7 @@ int launch_conv_mfma_two(const uint32_t *act, int Ca, const uint32_t *low, int C
         conv_upcat_supported(Ca, Clow, N, H, W, L, out_bits, out_pool))
         return launch_conv_mfma_upcat(act, Ca, low, Clow, N, H, W, L, blob, thresh, out_bits, s);
     if (t_cfg.tune_rw == 0) {
-        const SplitPlan p = conv_split_plan(N, H, W, L, low && low_shift, out_pool != nullptr);
+        const SplitPlan p = conv_split_plan(N, H, W, L, low != nullptr, out_pool != nullptr);
         if (p.r)
             return launch_conv_mfma_split(p, act, ceil_div(Ca, 32), low, low ? ceil_div(Clow, 32) : 0, low ? low_shift : 0,
                                           low ? Hb : 0, low ? Wb : 0, N, H, W, L, blob, thresh, out_bits, out_pool, s);

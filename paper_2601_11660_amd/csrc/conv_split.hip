@@ -260,16 +260,19 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
 //  - One input step: nothing to split, but tiles of one group still spread a small layer further than the
 //    row-streaming kernel's strips (64->64 at 64x64 4.3 against 5.4 us, 128x128, 1024 units, 4.8 against
 //    5.3; even from 1200 units on, 64->128 at 128x128, 2048 units, 5.6 against 5.2).
-//  - An up-sampled second input with fewer than eight input steps stays with the kernels that take it
-//    otherwise, which callers can rely on by name (mbu_unet_step_kernel).
+//    Two inputs go to the block kernel otherwise, and are taken up to the line ([32 | 32]->64 at 75x131, 5.8 ->
+//    4.2 us, [32 | 32]->32 at 151x263 5.4 -> 4.7).
+//  - An up-sampled second input comes here where conv_upcat.hip does not take the layer (odd frames, skips
+//    that are not a multiple of 64 channels, no summed taps), with any number of steps: [32 | 64]->32 at 64x96
+//    6.9 -> 3.8 us, [64 | 128]->64 at 75x131 6.8 -> 4.8, [96 | 192]->96 at 64x96 8.2 -> 6.0, at 101x151, 1482,
+//    8.5 -> 7.7, [128 | 256]->128 at 101x151, 1976, 9.0 -> 8.7.
 //  - Slices: as many as give 2048 waves (two per SIMD), at most 8 and at most one per step.  Eight slices of
 //    four groups take 129 KiB of LDS, one block on a compute unit: four, where there are more blocks than units
 //    (512->128 at 106x128, 432 blocks, 11.0 -> 8.8 us).
-SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool up, bool pool)
+SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool two, bool pool)
 {
     SplitPlan p{0, 0, 0};
     const long ctiles = L.cout >> 5;
-    if (up && L.ksteps < 8) return p;
     if ((double)N * H * W * L.cin_words * 4 >= 1073741824.0) return p;
     long best = 0;
     for (int tw : {32, 16, 8}) {   // fewest groups; the widest of equals
@@ -278,7 +281,7 @@ SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool up, boo
         if (!p.tw || g < best) { p.tw = tw; best = g; }
     }
     const long units = best * ctiles * L.ksteps;
-    if (best * ctiles > (L.ksteps <= 2 ? 1536 : 2048) || (L.ksteps == 1 && units > 1200)) return SplitPlan{0, 0, 0};
+    if (best * ctiles > (L.ksteps <= 2 ? 1536 : 2048) || (L.ksteps == 1 && !two && units > 1200)) return SplitPlan{0, 0, 0};
     p.r = 1;
     if (units > 4096 && W > 8) {
         p.r = 2;

@@ -128,12 +128,12 @@ int launch_conv_mfma_upcat(const uint32_t *act, int Ca, const uint32_t *low, int
                            const BlobLayout &L, const void *blob, const int32_t *thresh, uint32_t *out_bits,
                            hipStream_t s);
 // small layers: the waves of a block split the input channels of one tile (r groups of 32 pixels,
-// tw columns wide, x 32 output channels) 2^log_s ways; r = 0: another kernel is better.  up: the layer has a
-// 2x up-sampled second input
+// tw columns wide, x 32 output channels) 2^log_s ways; r = 0: another kernel is better.  two: the layer has a
+// second input
 struct SplitPlan {
     int r, tw, log_s;
 };
-SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool up, bool pool);
+SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool two, bool pool);
 // cwa / cwb: words per pixel of act / low; the other arguments as for launch_conv_mfma_two
 int launch_conv_mfma_split(const SplitPlan &p, const uint32_t *act, int cwa, const uint32_t *low, int cwb,
                            int low_shift, int hb, int wb, int N, int H, int W, const BlobLayout &L, const void *blob,

@@ -216,7 +216,7 @@ def test_unet_plan_validation_and_workspace():
     assert k.value.decode() == "conv_mfma_upcat_split_kernel"
     assert B.last_kernel() == "conv_mfma_upcat_split_kernel<1, 8>"       # the instance behind the name
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 75, 131, 25, ctypes.byref(k)) == 0   # dec1a, padded
-    assert k.value.decode() == "conv_mfma_block_kernel"
+    assert k.value.decode() == "conv_mfma_split_kernel"
     assert L.mbu_unet_step_kernel(ctypes.byref(d), 1, 64, 128, 99, ctypes.byref(k)) == B.MBU_ERR_ARG
     d.fuse = 0
     # inconsistent channel plan

@@ -290,6 +290,11 @@ SPLIT_SHAPES = [
     (2, 9, 7, 64, 96, 0, 64),
     (1, 21, 19, 512, 1024, 1, 64),    # up-sampled second input, a row and a column short
     (1, 16, 12, 256, 320, 1, 32),
+    (1, 13, 21, 32, 32, 1, 64),       # one step that straddles the inputs
+    (1, 27, 39, 32, 64, 1, 32),       # up-sampled, fewer than eight steps
+    (2, 16, 24, 96, 192, 1, 96),
+    (1, 75, 131, 64, 128, 1, 64),
+    (1, 101, 151, 128, 256, 1, 128),  # just below the line
 ]
 
 
@@ -1339,7 +1344,7 @@ def test_blob_sections():
     for i, blob in enumerate(keep):
         none._layers[i].sections = B.BLOB_MATRIX
         none._layers[i].packed_w = blob.data_ptr()
-    assert none.step_kernel(1, 64, 96, 10) == "conv_mfma_block_kernel"
+    assert none.step_kernel(1, 64, 96, 10) == "conv_mfma_split_kernel"
     c = none.forward(dev(case.image))
     torch.cuda.synchronize()
     assert np.array_equal(host(c), host(b))

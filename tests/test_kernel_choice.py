@@ -52,3 +52,16 @@ SPLIT, BLOCK = "conv_mfma_split_kernel", "conv_mfma_block_kernel"
 ])
 def test_small_layers_up_to_the_line(h, w, cin, cout, kernel):
     assert layer(h, w, cin, cout) == kernel
+
+
+@pytest.mark.parametrize("h, w, ca, cb, cout, kernel", [
+    (64, 96, 32, 64, 32, SPLIT + "<1, 32, false, true>"),    # not for the low-resolution kernel: 32 channels
+    (75, 131, 64, 128, 64, SPLIT + "<1, 8, true, true>"),    # odd frame
+    (13, 21, 32, 32, 64, SPLIT + "<1, 8, false, true>"),     # one step
+    (101, 151, 96, 192, 96, SPLIT + "<2, 16, false, true>"),
+    (151, 263, 96, 192, 96, BLOCK + "<4, 2, 2, false, true, false>"),
+    (75, 131, 256, 512, 256, BLOCK + "<2, 1, 4, true, true, false>"),
+    (64, 96, 64, 128, 64, "conv_mfma_upcat_split_kernel<1, 8>"),
+])
+def test_small_up_sampled_layers(h, w, ca, cb, cout, kernel):
+    assert up_sampled(h, w, ca, cb, cout) == kernel
