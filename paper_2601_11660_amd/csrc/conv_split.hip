@@ -25,7 +25,7 @@ namespace mbu {
 //   512->512 at 8x12 13.2 -> 4.2, at 64x64 14.1 -> 10.0;  256->512 at 64x64 9.1 -> 7.0;
 //   256->256 at 16x24 8.7 -> 3.8;  128->128 at 32x48 7.3 -> 3.7;
 //   [512 | 512]->512 at 64x64 24.2 -> 13.8
-// (before: block kernel).  Up-sampled second inputs come here only where conv_upcat.hip does not take them.
+// (before: block kernel with four rows per wave; its two-row form stands at the rule below).  Up-sampled second inputs come here only where conv_upcat.hip does not take them.
 // Measured and not kept: the whole window of all steps staged by the block in one go (coalesced, but a
 // barrier and 2-3 dependent LDS passes before the first matrix instruction: 0.5-1 us slower on the tiny
 // shapes, no faster on the others); 64 output channels per wave (no faster: the reduction doubles).
@@ -244,10 +244,9 @@ __global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
 //  - The block kernel with two rows per wave takes about 4.3 us + 0.8 per input step while its blocks have a
 //    compute unit each; this kernel's time grows with groups x channel tiles.  They meet at 2048 of these, two
 //    for a SIMD.  Block -> here: 4 steps 53x128, 1696, 7.2 -> 6.2 us; 64x64, 2048, 7.0 -> 6.8; 192x96, 2304,
-//    7.3 -> 7.2; 142x160, 2840, 7.2 -> 8.0.  8 steps 81x32, 1296, 10.2 -> 7.2; 64x64, 2048, 10.1 -> 8.5; 111x96,
+//    7.3 -> 7.2; 135x160, 2700, 7.2 -> 8.0.  8 steps 81x32, 1296, 10.2 -> 7.2; 64x64, 2048, 10.1 -> 8.5; 111x96,
 //    2664, 10.4 -> 11.7.  16 steps 32x32, 1024, 16.8 -> 8.3; 64x128, 2048, 16.1 -> 14.1; 96x48, 2304, 16.5 -> 16.8.
-//    With two steps, where the fixed part is most of the time, at 1536 (75x128, 1200, 5.5 -> 5.2; 109x60, 1744,
-//    5.8 -> 6.0).
+//    2 steps (sixty shapes, sides in turn): 0.77 at 1000, 0.91 at 1500, 0.95 at 1750, 1.01 at 2000, 1.03 at 2250.
 //  - Tile: up to 4096 units a wave
 //    takes a single group (every fragment is used once, but all waves run at once: [256 | 512 up]->256 at
 //    16x24, 1152 units, 4.8 us against 5.6 with two groups); up to 12288 two groups
@@ -281,7 +280,7 @@ SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool two, bo
         if (!p.tw || g < best) { p.tw = tw; best = g; }
     }
     const long units = best * ctiles * L.ksteps;
-    if (best * ctiles > (L.ksteps <= 2 ? 1536 : 2048) || (L.ksteps == 1 && !two && units > 1200)) return SplitPlan{0, 0, 0};
+    if (best * ctiles > 2048 || (L.ksteps == 1 && !two && units > 1200)) return SplitPlan{0, 0, 0};
     p.r = 1;
     if (units > 4096 && W > 8) {
         p.r = 2;
