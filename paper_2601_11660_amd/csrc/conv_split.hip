@@ -44,7 +44,7 @@ struct SplitGeo {
 };
 
 template <int R, int TWC, bool EVEN, bool TWO>
-__global__ __launch_bounds__(R == 1 ? 1024 : 512) void conv_mfma_split_kernel(
+__global__ __launch_bounds__(512) void conv_mfma_split_kernel(
     const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int Cwa, int Cwb,
     int low_shift, int Hb, int Wb, int ksteps, const uint4 *__restrict__ wfrag, int Cout, int log_s, int tiles_y,
     const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum,
