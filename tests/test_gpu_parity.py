@@ -275,26 +275,36 @@ def test_fused_concat_upsample_pool(shape):
 
 
 SPLIT_SHAPES = [
-    # N, H, W, Ca, Cb, upsample, Cout: Cb = 0 is a single input
-    (1, 1, 1, 64, 0, 0, 32),          # one pixel, one step, one slice
-    (1, 2, 3, 1024, 0, 0, 32),        # tiles 8 wide, eight slices of two steps
-    (3, 7, 6, 320, 0, 0, 96),         # five steps in four slices, three images
-    (1, 9, 17, 96, 0, 0, 64),         # tiles 16 wide (with the pooled output too), half a step at the end
-    (1, 5, 65, 40, 0, 0, 160),        # tiles 32 wide, Cin not a multiple of 32
-    (2, 33, 31, 128, 0, 0, 64),
-    (1, 31, 33, 512, 0, 0, 320),      # two groups per wave, ragged both ways
-    (1, 66, 63, 512, 0, 0, 512),      # four groups, S = 4
-    (1, 31, 32, 1024, 0, 0, 1024),    # four groups, S = 8
-    (1, 20, 8, 1024, 0, 0, 1024),     # no wider than the narrowest tile
-    (1, 5, 13, 32, 32, 0, 32),        # a step straddles the two inputs
-    (2, 9, 7, 64, 96, 0, 64),
-    (1, 21, 19, 512, 1024, 1, 64),    # up-sampled second input, a row and a column short
-    (1, 16, 12, 256, 320, 1, 32),
-    (1, 13, 21, 32, 32, 1, 64),       # one step that straddles the inputs
-    (1, 27, 39, 32, 64, 1, 32),       # up-sampled, fewer than eight steps
-    (2, 16, 24, 96, 192, 1, 96),
-    (1, 75, 131, 64, 128, 1, 64),
-    (1, 101, 151, 128, 256, 1, 128),  # just below the line
+    # N, H, W, Ca, Cb, upsample, Cout: Cb = 0 is a single input; groups per wave and width of a tile without
+    # the pooled output (with it, tiles of one group are at most 16 wide)
+    (1, 1, 1, 64, 0, 0, 32, "1, 32"),          # one pixel, one step, one slice
+    (1, 2, 3, 1024, 0, 0, 32, "1, 16"),        # eight slices of two steps
+    (3, 7, 6, 320, 0, 0, 96, "1, 8"),          # five steps in four slices, three images
+    (1, 9, 17, 96, 0, 0, 64, "1, 32"),         # half a step at the end
+    (1, 5, 65, 40, 0, 0, 160, "1, 32"),        # Cin not a multiple of 32
+    (1, 6, 15, 96, 0, 0, 32, "1, 16"),
+    (2, 33, 31, 128, 0, 0, 64, "1, 32"),
+    (1, 31, 33, 512, 0, 0, 320, "1, 8"),
+    (1, 51, 47, 512, 0, 0, 320, "2, 16"),      # two groups per wave, ragged both ways
+    (1, 40, 31, 480, 0, 0, 512, "2, 16"),
+    (1, 66, 63, 512, 0, 0, 512, None),         # just beyond the line: the block kernel
+    (1, 62, 63, 512, 0, 0, 512, "4, 32"),      # four groups, S = 4
+    (1, 60, 62, 480, 0, 0, 512, "4, 32"),      # the same, half a step at the end
+    (1, 31, 32, 1024, 0, 0, 1024, "4, 32"),    # four groups, S = 8
+    (1, 20, 8, 1024, 0, 0, 1024, "1, 8"),      # no wider than the narrowest tile
+    (1, 5, 13, 32, 32, 0, 32, "1, 16"),        # a step straddles the two inputs
+    (2, 9, 7, 64, 96, 0, 64, "1, 8"),
+    (1, 33, 95, 256, 256, 0, 256, "2, 16"),    # two inputs, two groups
+    (1, 33, 95, 224, 256, 0, 256, "2, 16"),
+    (1, 60, 62, 256, 256, 0, 512, "4, 32"),    # two inputs, four groups
+    (1, 60, 61, 256, 224, 0, 512, "4, 32"),
+    (1, 21, 19, 512, 1024, 1, 64, "1, 8"),     # up-sampled second input, a row and a column short
+    (1, 16, 12, 256, 320, 1, 32, "1, 16"),
+    (1, 13, 21, 32, 32, 1, 64, "1, 8"),        # one step that straddles the inputs
+    (1, 27, 39, 32, 64, 1, 32, "1, 8"),        # up-sampled, fewer than eight steps
+    (2, 16, 24, 96, 192, 1, 96, "1, 8"),
+    (1, 75, 131, 64, 128, 1, 64, "1, 8"),
+    (1, 101, 151, 128, 256, 1, 128, "2, 16"),  # just below the line
 ]
 
 
@@ -303,7 +313,7 @@ def test_small_layers_split_over_their_input_channels(shape):
     """Shapes for which the automatic choice is the kernel that splits the input channels over a
     block's waves, at the edges of its tiles and slices, with and without the pooled output;
     tuning 7 runs the kernels for larger layers on the same calls."""
-    N, H, W, Ca, Cb, up, Cout = shape
+    N, H, W, Ca, Cb, up, Cout, tile = shape
     say(f"conv split N={N} H={H} W={W} Ca={Ca} Cb={Cb} up={up} Cout={Cout}")
     rng = np.random.default_rng(H * 100 + W)
     a = synth.pm1_bits(rng, (N, H, W, Ca))
@@ -327,6 +337,9 @@ def test_small_layers_split_over_their_input_channels(shape):
                 bits, pooled = B.conv3x3_masked_binary_fused(pa, Ca, None, 0, blob, Cout, thd, True, True)
             else:
                 bits, pooled = B.conv3x3_masked_binary(pa, Ca, blob, Cout, thd)
+            if mode == 0:
+                instance = "conv_mfma_split_kernel<" + ("" if pool else tile + ", ") if tile else "conv_mfma_block_kernel<2,"
+                assert B.last_kernel().startswith(instance), (B.last_kernel(), pool)
             torch.cuda.synchronize()
             assert np.array_equal(host_u32(bits), ref), (mode, pool)
             if pool:
@@ -334,17 +347,24 @@ def test_small_layers_split_over_their_input_channels(shape):
 
 
 @pytest.mark.parametrize("shape", [
-    # N, H, W, Ca, Cb, Cout: waves over channels, over both, over rows; ragged last rows and columns
-    (1, 127, 127, 128, 0, 256), (1, 126, 33, 96, 0, 512),
-    (1, 250, 131, 128, 0, 128), (1, 299, 330, 128, 0, 128),
-    (1, 509, 130, 128, 0, 64), (2, 333, 63, 96, 0, 64),
-    (1, 129, 123, 64, 96, 256), (1, 253, 127, 96, 64, 128), (1, 515, 129, 64, 64, 64),
+    # N, H, W, Ca, Cb, Cout; instance (rows per wave, waves over rows, over channels).  Two rows while every
+    # block has a compute unit of its own:
+    (1, 127, 127, 128, 0, 256, "block_kernel<2, 1, 4, true, false"), (1, 126, 33, 96, 0, 512, "block_kernel<2, 1, 4, false, false"),
+    (1, 250, 70, 192, 0, 128, "block_kernel<2, 2, 2, true, false"), (1, 253, 127, 96, 64, 128, "block_kernel<2, 2, 2, false, true"),
+    (2, 333, 63, 96, 0, 64, "block_kernel<2, 4, 1, false, false"), (1, 500, 70, 64, 96, 64, "block_kernel<2, 4, 1, false, true"),
+    # with 257 to 384 blocks of four rows and at most four steps:
+    (1, 133, 300, 192, 0, 256, "block_kernel<2, 1, 4, true, false"), (1, 240, 320, 192, 0, 128, "block_kernel<2, 2, 2, true, false"),
+    (1, 500, 300, 192, 0, 64, "block_kernel<2, 4, 1, true, false"), (1, 490, 300, 64, 96, 64, "block_kernel<2, 4, 1, false, true"),
+    # neighbours outside: between the two, and the row-streaming kernel
+    (1, 250, 131, 128, 0, 128, "block_kernel<4, 2, 2, true, false"), (1, 509, 130, 128, 0, 64, "block_kernel<4, 4, 1, true, false"),
+    (1, 129, 123, 64, 96, 256, "block_kernel<4, 1, 4, false, true"), (1, 515, 129, 64, 64, 64, "block_kernel<4, 4, 1, true, true"),
+    (1, 299, 330, 128, 0, 128, "rows2k_kernel<true, true, false"),
 ])
 def test_block_kernel_with_two_rows_per_wave(shape):
     """Layers whose block count makes the block-cooperative kernel take two rows per wave (and
-    neighbours just outside), with the pooled output, against the four-row form of tuning 1 and, on
-    the smaller ones, the oracle."""
-    N, H, W, Ca, Cb, Cout = shape
+    neighbours just outside), with the pooled output and ragged last rows and columns, against the
+    four-row form of tuning 1 and, on the smaller ones, the oracle."""
+    N, H, W, Ca, Cb, Cout, instance = shape
     say(f"conv block rows N={N} H={H} W={W} Ca={Ca} Cb={Cb} Cout={Cout}")
     rng = np.random.default_rng(H + W)
     a = synth.pm1_bits(rng, (N, H, W, Ca))
@@ -360,6 +380,7 @@ def test_block_kernel_with_two_rows_per_wave(shape):
             o = B.conv3x3_masked_binary_two_inputs(pa, Ca, pb, Cb, False, blob, Cout, thd, True)
         else:
             o = B.conv3x3_masked_binary_fused(pa, Ca, None, 0, blob, Cout, thd, True, True)
+        assert B.last_kernel().startswith("conv_mfma_" + (instance if mode == 0 else "block_kernel<4")), B.last_kernel()
         torch.cuda.synchronize()
         outs.append([host_u32(t) for t in o])
     assert all(np.array_equal(x, y) for x, y in zip(*outs))
@@ -416,19 +437,21 @@ def test_upsampled_decoder_kernel_matches_oracle(shape):
 
 
 @pytest.mark.parametrize("shape", [
-    # N, H, W, Ca, Clow, Cout
-    (1, 2, 2, 64, 128, 32),           # one low pixel, one class per wave
-    (2, 10, 18, 64, 128, 96),         # tiles 8 wide, ragged; slices that begin with a low step
-    (1, 4, 34, 192, 128, 64),         # tiles 16 wide; a slice of skip steps only
-    (1, 14, 30, 512, 1024, 512),      # all classes per wave, eight slices
-    (1, 2, 200, 256, 512, 512),       # the same, 16 wide
-    (1, 62, 62, 512, 1024, 512),      # four slices
+    # N, H, W, Ca, Clow, Cout; classes per wave and width of a tile
+    (1, 2, 2, 64, 128, 32, "1, 8"),           # one low pixel
+    (2, 10, 14, 64, 128, 96, "1, 8"),         # ragged both ways
+    (2, 10, 18, 64, 128, 96, "1, 16"),        # ragged; slices that begin with a low step
+    (1, 4, 34, 192, 128, 64, "1, 16"),        # a slice of skip steps only
+    (1, 14, 30, 512, 1024, 512, "1, 8"),      # eight slices
+    (1, 2, 200, 256, 512, 512, "1, 16"),      # four slices
+    (1, 62, 62, 512, 1024, 512, "4, 8"),      # all classes per wave, four slices
+    (1, 2, 130, 512, 1024, 512, "4, 16"),     # all classes per wave, eight slices
 ])
 def test_small_upsampled_decoder_layers(shape):
     """Decoder layers over [skip | 2x up-sampled low] small enough for the kernel whose waves split
     the input steps, with every summed tap at its extreme too; tuning 7 takes the kernel for larger
     layers on the same call."""
-    N, H, W, Ca, Clow, Cout = shape
+    N, H, W, Ca, Clow, Cout, tile = shape
     say(f"conv upcat split N={N} H={H} W={W} Ca={Ca} Clow={Clow} Cout={Cout}")
     rng = np.random.default_rng(H * 100 + W)
     skip = synth.pm1_bits(rng, (N, H, W, Ca))
@@ -445,6 +468,8 @@ def test_small_upsampled_decoder_layers(shape):
         for mode in (0, 7):
             B.set_conv_tuning(mode)
             bits, _ = B.conv3x3_masked_binary_fused(pa, Ca, pl, Clow, blob, Cout, dev(th), True, False)
+            instance = "conv_mfma_upcat_split_kernel<" + tile + ">" if mode == 0 else "conv_mfma_upcat_kernel"
+            assert B.last_kernel() == instance
             torch.cuda.synchronize()
             assert np.array_equal(host_u32(bits), ref), mode
 
