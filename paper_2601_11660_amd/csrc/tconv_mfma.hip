@@ -643,20 +643,23 @@ int launch_tconv_mfma(const uint32_t *act, int N, int H, int W, const TconvLayou
     const int tiles64 = L.cout_pad64 / 64;
     const double GiB = 1073741824.0;
     const bool small = (double)N * H * W * L.cin_words * 4 < GiB && (double)N * H * W * 4 * (L.cout >> 5) * 4 < GiB;
-    // 64 ... 1024 input channels where a group divides evenly over the block: weights resident.  Against the
+    // Up to 1024 input channels (16 steps of weights fit in registers) where a group of 1, 2 or 4 rows divides
+    // evenly over the block, at most five words of one pixel per thread: weights resident.  Against the
     // kernels below: 64->64 at 8x160x239 18.5 -> 10.4 us, 192->96 at 2x160x239 11.2 -> 8.3, 320->512 at
-    // 20x872 16.2 -> 10.3, 384->192 at 4x80x80 12.5 -> 8.6, 768->512 at 64x64 10.5 -> 7.0.
-    if (!out_acc && small && L.cin_words == 2 * L.ksteps) {
-        if (L.ksteps == 1) return launch_tconv_res<1, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 3) return launch_tconv_res<3, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 5) return launch_tconv_res<5, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 6) return launch_tconv_res<6, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 12) return launch_tconv_res<12, 1>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 2) return launch_tconv_res<2, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 4) return launch_tconv_res<4, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 8) return launch_tconv_res<8, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-        if (L.ksteps == 16) return launch_tconv_res<16, 1>(act, N, H, W, L, wfrag, thresh, out_bits, s);
-    }
+    // 20x872 16.2 -> 10.3, 384->192 at 4x80x80 12.5 -> 8.6, 640->320 at 8x80x119 56.9 -> 31.6 and at 16x16
+    // 8.1 -> 4.2, 768->512 at 64x64 10.5 -> 7.0.
+    if (!out_acc && small && L.cin_words == 2 * L.ksteps) switch (L.ksteps) {
+        case 1: return launch_tconv_res<1, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 2: return launch_tconv_res<2, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 3: return launch_tconv_res<3, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 4: return launch_tconv_res<4, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 5: return launch_tconv_res<5, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 6: return launch_tconv_res<6, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 8: return launch_tconv_res<8, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 10: return launch_tconv_res<10, 2>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 12: return launch_tconv_res<12, 1>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 16: return launch_tconv_res<16, 1>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        }
     if (!out_acc && L.ksteps >= 2 && small && (double)L.ksteps * 8 * 1024 < GiB) {
         constexpr int RGF = RG;
         const int gy2 = ceil_div(H, RGF);

@@ -491,6 +491,7 @@ TCONV_SHAPES = [
     (2, 6, 33, 320, 96),
     (1, 5, 34, 384, 64),
     (1, 3, 40, 768, 64),
+    (2, 5, 37, 640, 96),      # ten steps, groups of two rows with a ragged last one
     (1, 7, 50, 448, 64),      # seven: not resident
 ]
 

@@ -65,3 +65,11 @@ def test_small_layers_up_to_the_line(h, w, cin, cout, kernel):
 ])
 def test_small_up_sampled_layers(h, w, ca, cb, cout, kernel):
     assert up_sampled(h, w, ca, cb, cout) == kernel
+
+
+@pytest.mark.parametrize("cin, kernel", [(64 * k, f"tconv_res_kernel<{k}, {rows}>") for k, rows in
+                                         ((1, 4), (2, 4), (3, 4), (4, 4), (5, 4), (6, 2), (8, 2), (10, 2), (12, 1), (16, 1))]
+                         + [(448, "tconv_bits_kernel<4>"), (1088, "tconv_bits_kernel<4>"), (32, "tconv_mfma_kernel<false>")])
+def test_transposed_layers(cin, kernel):
+    """Weights resident for every width up to 1024 channels whose groups divide evenly over a block."""
+    assert choice([(32, 32), (32, 32), (32, cin), (cin, cin), (64, 32), (32, 32)], 1, 40, 60, 6, (cin, 32)) == kernel
