@@ -850,12 +850,15 @@ static int launch_block_auto(const ConvIO &io, int N, int H, int W, const BlobLa
     // 128x128 10.1 -> 8.1 us, 128->256 7.4 -> 6.0; 75 -> 145: 9.9 -> 7.0), and where the larger blocks leave
     // most units one and a few two (300 -> 600 blocks: 128->128 at 240x320 10.7 -> 9.5; 360: 15.4 -> 14.7).
     // The latter with few input steps only: the weights cost twice as much (264 blocks, 24 steps: 75 us with two
-    // rows, 64 with four).  In between and beyond four rows win (150 blocks: 10.0 against 11.5 us; 256: 26.4
-    // against 32.0; 1024: 27.5 against 31.6).
+    // rows, 64 with four), and only where one group of channel tiles makes up the layer: with several, the tiles
+    // beyond the resident blocks fall to the first blocks of every group, which likely share compute units (two:
+    // 128->512 at 210x96, 318 blocks, 10.4 us with four rows, 12.0 with two; 192->512 at 159x128 12.4, 14.4).  In
+    // between and beyond four rows win (150 blocks: 10.0 against 11.5 us; 256: 26.4 against 32.0; 1024: 27.5 against
+    // 31.6).
     const int wn = tiles64 % 4 == 0 ? 4 : tiles64 % 2 == 0 ? 2 : 1, wm = 4 / wn;
     const long blocks4 = (long)N * ceil_div(H, 4 * wm) * ceil_div(W, TW) * (tiles64 / wn);
     const long blocks2 = (long)N * ceil_div(H, 2 * wm) * ceil_div(W, TW) * (tiles64 / wn);
-    if (t_cfg.tune_rw == 0 && (blocks2 <= 256 || (blocks4 > 256 && blocks4 <= 384 && L.ksteps <= 4))) {
+    if (t_cfg.tune_rw == 0 && (blocks2 <= 256 || (blocks4 > 256 && blocks4 <= 384 && L.ksteps <= 4 && tiles64 == wn))) {
         if (wn == 4) return launch_block<2, 1, 4>(io, N, H, W, L, wfrag, thresh, s);
         if (wn == 2) return launch_block<2, 2, 2>(io, N, H, W, L, wfrag, thresh, s);
         return launch_block<2, 4, 1>(io, N, H, W, L, wfrag, thresh, s);

@@ -54,6 +54,15 @@ def test_small_layers_up_to_the_line(h, w, cin, cout, kernel):
     assert layer(h, w, cin, cout) == kernel
 
 
+@pytest.mark.parametrize("h, w, cin, cout, rows", [
+    (210, 96, 128, 512, 4), (159, 128, 192, 512, 4), (127, 128, 192, 768, 4),    # 257 to 384 blocks, several channel groups
+    (320, 128, 192, 256, 2), (240, 320, 192, 128, 2), (500, 300, 192, 64, 2),    # one group
+    (66, 64, 512, 512, 2),                                                       # at most 256 blocks of two rows
+])
+def test_rows_per_wave_of_the_block_kernel(h, w, cin, cout, rows):
+    assert layer(h, w, cin, cout).startswith(f"{BLOCK}<{rows}, ")
+
+
 @pytest.mark.parametrize("h, w, ca, cb, cout, kernel", [
     (64, 96, 32, 64, 32, SPLIT + "<1, 32, false, true>"),    # not for the low-resolution kernel: 32 channels
     (75, 131, 64, 128, 64, SPLIT + "<1, 8, true, true>"),    # odd frame
