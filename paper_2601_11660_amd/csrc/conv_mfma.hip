@@ -909,8 +909,8 @@ int launch_conv_mfma(const uint32_t *act, int N, int H, int W, const BlobLayout 
 
 // Fused form: input = [act (Ca channels) | low (Clow channels)] when low is given - Hb x Wb
 // pixels, read up-sampled 2x when low_shift = 1, zeros where its extent falls short of H x W -
-// plus an optional 2x2-pooled second output.  The low-resolution decoder kernel, the
-// row-streaming kernels for a single source, else the block-cooperative kernel.
+// plus an optional 2x2-pooled second output.  The low-resolution decoder kernel, the kernel that
+// splits the input channels for small layers, the row-streaming kernels, else the block-cooperative one.
 int launch_conv_mfma_two(const uint32_t *act, int Ca, const uint32_t *low, int Clow, int low_shift,
                          int Hb, int Wb, int N, int H, int W, const BlobLayout &L, const void *blob,
                          const int32_t *thresh, uint32_t *out_bits, uint32_t *out_pool, hipStream_t s)

@@ -468,12 +468,12 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 // Bound by the vector ALU: about 180 vector instructions a tile, prologue included, against 12 matrix
 // instructions, which it does not overlap (counters at 1024x2048: matrix 34 %, vector 63 % of the SIMD
 // cycles).  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
-// taps of a sum fetched at once, and a block's waves share the preparation of the weights, behind the
-// fetches of the first image rows: 41.0 -> 37.1 us at 1024x2048, 315 -> 306 us at 32x640x959.  A tile with
-// many undecided outputs (non-finite or tiny windows, a weight row out of range, dense ties) sums them in the
-// lanes that hold them, a pixel's patch fetched once for all of them: with every output undecided 512x1024 x 64
-// takes 124 us, with 200 NaN pixels 50, ordinary data 15.2 (a patch fetched again for every output, a kernel
-// row at a time: 560 and 392).
+// taps of a sum fetched at once from one base offset, and a block's waves share the preparation of the
+// weights, behind the fetches of the first image rows: 41.0 -> 37.1 us at 1024x2048 back to back; in a trace with
+// flushed caches 50.3 -> 44.5, 358 -> 335 at 32x640x959, 8.2 -> 6.2 at 64x96.  A tile with many undecided outputs
+// (non-finite or tiny windows, a weight row out of range, dense ties) sums them in the lanes that hold them, a
+// pixel's patch fetched once for all of them: with every output undecided 512x1024 x 64 takes 124 us, with 200
+// NaN pixels 50, ordinary data 15.2 (a patch fetched again for every output, a kernel row at a time: 560 and 392).
 constexpr int SR_HW = 34;                    // halo pixels of a strip
 constexpr int SR_ARR = 36;                   // dwords per LDS array (34 used)
 constexpr int SR_PLANE = 5 * SR_ARR;         // arrays P0 P1 R01 P2 R2 of one plane (hi or lo)
