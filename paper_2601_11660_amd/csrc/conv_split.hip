@@ -242,18 +242,21 @@ __global__ __launch_bounds__(512) void conv_mfma_split_kernel(
 // When, and with which tile.  Both sides measured with a kernel trace, caches flushed between launches; a unit
 // is 9 matrix instructions (one group, 32 channels, one step):
 //  - The block kernel with two rows per wave takes about 4.3 us + 0.8 per input step while its blocks have a
-//    compute unit each; this kernel's time grows with groups x channel tiles.  They meet at 2048 of these, two
-//    for a SIMD.  Block -> here: 4 steps 53x128, 1696, 7.2 -> 6.2 us; 64x64, 2048, 7.0 -> 6.8; 192x96, 2304,
-//    7.3 -> 7.2; 135x160, 2700, 7.2 -> 8.0.  8 steps 81x32, 1296, 10.2 -> 7.2; 64x64, 2048, 10.1 -> 8.5; 111x96,
-//    2664, 10.4 -> 11.7.  16 steps 32x32, 1024, 16.8 -> 8.3; 64x128, 2048, 16.1 -> 14.1; 96x48, 2304, 16.5 -> 16.8.
-//    2 steps (sixty shapes, sides in turn): 0.77 at 1000, 0.91 at 1500, 0.95 at 1750, 1.01 at 2000, 1.03 at 2250.
+//    compute unit each; this kernel's time grows with groups x channel tiles, what its tiles cover beyond the
+//    frame included.  They meet at 2048 of these, two for a SIMD.  Block -> here: 4 steps 53x128, 1792, 7.2 ->
+//    6.2 us; 64x64, 2048, 7.0 -> 6.8; 192x96, 2304, 7.3 -> 7.2; 135x160, 2720, 7.2 -> 8.0.  8 steps 81x32, 1344,
+//    10.2 -> 7.2; 64x64, 2048, 10.1 -> 8.5; 111x96, 2688, 10.4 -> 11.7.  16 steps 32x32, 1024, 16.8 -> 8.3; 64x128,
+//    2048, 16.1 -> 14.1; 96x48, 2304, 16.5 -> 16.8.  Back to back with warm caches, 3 to 16 steps: 0.74-1.04 of
+//    the block kernel's time at 1400 to 2048; 112x24, 256->768, 2688 of which 2016 in the frame, 6.1 us with the block
+//    kernel, 7.4 here.  With two steps at 1792: 0.91 at 1500, 0.95 at 1750, 1.01 at 2000 with flushed caches, 1.05, 1.05
+//    and 1.06 with warm ones.
 //  - Tile: up to 4096 units a wave
 //    takes a single group (every fragment is used once, but all waves run at once: [256 | 512 up]->256 at
 //    16x24, 1152 units, 4.8 us against 5.6 with two groups); up to 12288 two groups
 //    (512->1024 at 32x32, 8192 units, 6.5 us against 7.1 with one and 7.4 with four); then four, which
 //    halve the weight traffic again (1024->1024 at 32x32, 16384 units, 9.8 against 10.5 us), as long as the
 //    blocks of four slices are resident at once, two on a compute unit (1024->512 at 42x96, 528 blocks, 17.7 us
-//    against 15.9 with two groups).
+//    against 15.9 with two groups): up to the same line.
 //    Tiles 32 wide only where they leave little more of the frame's width empty than tiles 16 wide, and a
 //    frame of 8 columns or fewer stays with single groups 8 wide.
 //  - One input step: nothing to split, but tiles of one group still spread a small layer further than the
@@ -280,7 +283,7 @@ SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool two, bo
         if (!p.tw || g < best) { p.tw = tw; best = g; }
     }
     const long units = best * ctiles * L.ksteps;
-    if (best * ctiles > 2048 || (L.ksteps == 1 && !two && units > 1200)) return SplitPlan{0, 0, 0};
+    if (L.ksteps == 1 && !two && units > 1200) return SplitPlan{0, 0, 0};
     p.r = 1;
     if (units > 4096 && W > 8) {
         p.r = 2;
@@ -289,6 +292,7 @@ SplitPlan conv_split_plan(int N, int H, int W, const BlobLayout &L, bool two, bo
             (long)N * ceil_div(W, 32) * ceil_div(H, 4) * ctiles <= 512) { p.r = 4; p.tw = 32; }
     }
     const long tiles = (long)N * ceil_div(W, p.tw) * ceil_div(H, p.r * 32 / p.tw) * ctiles;
+    if (tiles * p.r > (L.ksteps <= 2 ? 1792 : 2048)) return SplitPlan{0, 0, 0};
     const int most = p.r == 4 && tiles > 256 ? 2 : 3;
     p.log_s = 0;
     while (p.log_s < most && 2 << p.log_s <= L.ksteps && tiles << p.log_s < 2048) ++p.log_s;

@@ -465,8 +465,8 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 //     h = 1:  P2[j] P2[j+1] P2[j+2] R2[j]  |  R2[j+1] R2[j+2] R01[j+2] (1.0, 0)
 // The last dword is the constant that gives an all-zero weight row a decidable estimate (see
 // the kernel above).  The weights are loaded in the same order.
-// Bound by the vector ALU: about 180 vector instructions a tile, prologue included, against 12 matrix
-// instructions, which it does not overlap (counters at 1024x2048: matrix 34 %, vector 63 % of the SIMD
+// Bound by the vector ALU: about 175 vector instructions a tile, prologue included, against 12 matrix
+// instructions, which it does not overlap (counters at 1024x2048: matrix 35 %, vector 64 % of the SIMD
 // cycles).  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
 // taps of a sum fetched at once from one base offset, and a block's waves share the preparation of the
 // weights, behind the fetches of the first image rows: 41.0 -> 37.1 us at 1024x2048 back to back; in a trace with

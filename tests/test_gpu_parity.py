@@ -304,7 +304,7 @@ SPLIT_SHAPES = [
     (1, 27, 39, 32, 64, 1, 32, "1, 8"),        # up-sampled, fewer than eight steps
     (2, 16, 24, 96, 192, 1, 96, "1, 8"),
     (1, 75, 131, 64, 128, 1, 64, "1, 8"),
-    (1, 101, 151, 128, 256, 1, 128, "2, 16"),  # just below the line
+    (1, 99, 151, 128, 256, 1, 128, "2, 16"),   # just below the line
 ]
 
 

@@ -44,10 +44,11 @@ SPLIT, BLOCK = "conv_mfma_split_kernel", "conv_mfma_block_kernel"
     (112, 128, 256, 256, BLOCK + "<2, 1, 4, true, false, true>"),
     (128, 128, 256, 256, BLOCK + "<2, 1, 4, true, false, true>"),
     (128, 64, 256, 256, SPLIT + "<2, 16, true, false>"),
-    (42, 96, 1024, 512, SPLIT + "<2, 16, true, false>"),     # 528 blocks of four groups: not resident at once
+    (36, 112, 1024, 512, SPLIT + "<2, 16, true, false>"),    # 576 blocks of four groups: not resident at once
+    (112, 24, 256, 768, BLOCK + "<2, 1, 4, true, false, true>"),     # 2016 in the frame, 2688 with two 16-wide tiles
     (40, 96, 1024, 512, SPLIT + "<4, 32, true, false>"),
-    (128, 64, 128, 256, SPLIT + "<1, 16, true, false>"),
-    (130, 64, 128, 256, BLOCK + "<2, 1, 4, true, false, true>"),
+    (112, 64, 128, 256, SPLIT + "<1, 16, true, false>"),     # two steps: 1792
+    (114, 64, 128, 256, BLOCK + "<2, 1, 4, true, false, true>"),
     (4, 6, 1024, 1024, SPLIT + "<1, 8, true, false>"),
 ])
 def test_small_layers_up_to_the_line(h, w, cin, cout, kernel):
