@@ -40,6 +40,7 @@
 #include "mbu_internal.h"
 #include "mfma_common.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace mbu {
 
@@ -438,48 +439,56 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 // Row-walking variant for three image channels.
 //
 // The kernel above gathers and splits all 27 values of every patch although a value belongs
-// to nine patches.  Here a wave walks down a strip of 32 pixel columns; for every image row it
-// keeps the three rows of the 3x3 window as raw floats (lane p = halo pixel p of the strip:
-// 9 values), scales and splits them ONCE per tile and hands them to the 32 patches of the row
-// through wave-private LDS.  Sharing the split values means sharing the scale: instead of one
-// power of two per patch the whole window (3 rows x 34 pixels x 3 channels) is scaled by one
-// power of two s that brings its largest magnitude into [2^13, 2^14).  The error budget of the
+// to nine patches.  Here a wave walks down a strip of 32 pixel columns; lane p owns halo pixel p, and
+// a row is scaled and split ONCE, when it enters the window, and handed through wave-private LDS (four
+// slots of one row) to the patches of the three rows it belongs to.  Sharing the split values means
+// sharing the scale: instead of one power of two per patch the strip has one power of two s.  It is
+// chosen to bring the largest magnitude of a window (3 rows x 34 pixels x 3 channels) into [2^11, 2^12)
+// and kept while every row that enters stays below 2^15 (fp16 does not overflow) and one of three
+// reaches 2^3, scaled; otherwise the wave chooses again and stages the window's older rows once more (a
+// fetch of two rows, about 1 us; ordinary images do it a few times at most).  The error budget of the
 // estimate changes in one place: the remainder of the split is bounded by 2^-22 |v| + 2^-25
 // (the second term is the spacing of fp16 subnormals), and with a patch that is small against
 // its window the absolute term no longer vanishes against the patch norm.  It is therefore part
 // of the decision threshold:
 //     T = kappa * max_o ||w_o|| * ||s x_patch||  +  2^-9
 // (sum_k |w_k| 2^-25 <= sqrt(27) 2^13 2^-25 = 1.3e-3 < 2^-9 for rows scaled to a norm below
-// 2^13).  Outputs with |estimate| <= T take the sequential route as before, so the bits are
+// 2^13, whatever s).  Outputs with |estimate| <= T take the sequential route as before, so the bits are
 // those of the definition whatever the data; a window that holds values more than ~2^17
-// apart merely sends more of its small patches down that route.  Windows with a non-finite
-// value, or with a largest magnitude below 2^-111, get T = +inf.  The squared patch norm is the
-// sum of three per-pixel column sums exchanged through LDS; a NaN in it makes T NaN and the
+// apart merely sends more of its small patches down that route.  Windows with an infinity, or with a
+// largest magnitude below 2^-111, get T = +inf.  The squared patch norm is the
+// sum of three per-pixel sums of three rows exchanged through LDS; a NaN in it makes T NaN and the
 // comparison fail, which is the sequential route again.
 //
 // K order of the matrix instruction (32 terms = 16 dwords of two fp16 values; lane (j, h) of a
-// B operand supplies dwords 8t + 4h + d of block t): the LDS arrays hold one dword per halo
-// pixel p - P_r[p] = channels (0, 1) of window row r, R01[p] = channel 2 of rows (0, 1),
-// R2[p] = (channel 2 of row 2, 0) - and pixel j reads entries j, j + 1, j + 2 (kx = 0, 1, 2):
-//     h = 0:  P0[j] P0[j+1] P0[j+2] P1[j]  |  P1[j+1] P1[j+2] R01[j]   R01[j+1]
-//     h = 1:  P2[j] P2[j+1] P2[j+2] R2[j]  |  R2[j+1] R2[j+2] R01[j+2] (1.0, 0)
-// The last dword is the constant that gives an all-zero weight row a decidable estimate (see
-// the kernel above).  The weights are loaded in the same order.
-// Bound by the vector ALU: about 175 vector instructions a tile, prologue included, against 12 matrix
-// instructions, which it does not overlap (counters at 1024x2048: matrix 35 %, vector 64 % of the SIMD
-// cycles).  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
+// B operand supplies dwords 8t + 4h + d of block t): a slot holds two dwords per halo pixel p and plane -
+// P[p] = channels (0, 1), Z[p] = channel 2 of pixels (p, p + 1) - and pixel j reads, for window rows 0 .. 2,
+//     h = 0:  P0[j] P0[j+1] Z0[j] Z0[j+1]  |  P0[j+2] P1[j+2]    P1[j] P1[j+1]
+//     h = 1:  P2[j] P2[j+1] Z2[j] Z2[j+1]  |  P2[j+2] (1.0, 0)   Z1[j] Z1[j+1]
+// (the first value of a Z[j+1] meets weight 0).  The constant gives an all-zero weight row a decidable
+// estimate (see the kernel above).  The weights are loaded in the same order, and no value moves between
+// registers: every dword is read where the matrix instruction wants it.
+//
+// What bounds it: about 107 vector and 12 matrix instructions a tile, which overlap by a tenth (counters at
+// 32x640x959: matrix 53 %, vector 59 % of the SIMD cycles, at 1.7 GHz).  Staging a row once instead of three
+// times took 175 -> 107 vector instructions; four waves per SIMD where they get eight rows each, three
+// otherwise (9.2 against 10.4 us at 512x512).  1024x2048 36.6 -> 32.4 us back to back, 32x640x959
+// 303 -> 257, 8x1024x1024 to 128 channels 254 -> 223, 512x512 9.9 -> 9.2.  Measured and not kept: the decision of
+// row y - 1 between the matrix instructions of row y (a second set of accumulators, two waves per SIMD):
+// 38.4 us.  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
 // taps of a sum fetched at once from one base offset, and a block's waves share the preparation of the
-// weights, behind the fetches of the first image rows: 41.0 -> 37.1 us at 1024x2048 back to back; in a trace with
-// flushed caches 50.3 -> 44.5, 358 -> 335 at 32x640x959, 8.2 -> 6.2 at 64x96.  A tile with many undecided outputs
+// weights, behind the fetches of the first image rows.  A tile with many undecided outputs
 // (non-finite or tiny windows, a weight row out of range, dense ties) sums them in the lanes that hold them, a
 // pixel's patch fetched once for all of them: with every output undecided 512x1024 x 64 takes 124 us, with 200
-// NaN pixels 50, ordinary data 15.2 (a patch fetched again for every output, a kernel row at a time: 560 and 392).
+// NaN pixels 46, ordinary data 14.5 (a patch fetched again for every output, a kernel row at a time: 560 and 392).
 constexpr int SR_HW = 34;                    // halo pixels of a strip
 constexpr int SR_ARR = 36;                   // dwords per LDS array (34 used)
-constexpr int SR_PLANE = 5 * SR_ARR;         // arrays P0 P1 R01 P2 R2 of one plane (hi or lo)
-constexpr int SR_CONST = SR_PLANE - 1;       // spare dword of R2: the constant entry
-constexpr int SR_N = 2 * SR_PLANE;           // per halo pixel: squared column norm, OR of the bits
-constexpr int SR_Q = SR_N + 2 * SR_ARR;       // undecided outputs that wait for their sequential sums
+constexpr int SR_Z = SR_ARR;                 // from P of a plane to its Z
+constexpr int SR_LO = 2 * SR_ARR;            // from the plane of the leading terms to that of the remainders
+constexpr int SR_SLOT = 4 * SR_ARR;          // P and Z of both planes: one image row
+constexpr int SR_CONST = SR_ARR - 1;         // spare dword of P: the constant entry
+constexpr int SR_N = 4 * SR_SLOT;            // per halo pixel: squared norm of its three rows
+constexpr int SR_Q = SR_N + SR_ARR;          // undecided outputs that wait for their sequential sums
 constexpr int SR_QCAP = 192;
 constexpr int SR_WAVE = SR_Q + SR_QCAP;      // dwords per wave
 constexpr float SR_FLOOR = 0x1p-9f;
@@ -488,15 +497,14 @@ constexpr float SR_FLOOR = 0x1p-9f;
 // -1: no term (weight 0), -2: the constant term
 __host__ __device__ constexpr int sr_term(int h, int dh, int e)
 {
-    if (h == 0) {
-        if (dh < 3) return (0 * 3 + dh) * 3 + e;
-        if (dh < 6) return (1 * 3 + (dh - 3)) * 3 + e;
-        return (e * 3 + (dh - 6)) * 3 + 2;
-    }
-    if (dh < 3) return (2 * 3 + dh) * 3 + e;
-    if (dh < 6) return e == 0 ? (2 * 3 + (dh - 3)) * 3 + 2 : -1;
-    if (dh == 6) return (e * 3 + 2) * 3 + 2;
-    return e == 0 ? -2 : -1;
+    const int ky = h == 0 ? 0 : 2;                                   // window row of dwords 0 .. 4
+    if (dh < 2 || dh == 4) return (ky * 3 + (dh < 2 ? dh : 2)) * 3 + e;
+    if (dh == 2) return (ky * 3 + e) * 3 + 2;
+    if (dh == 3) return e ? (ky * 3 + 2) * 3 + 2 : -1;
+    if (h == 0) return (1 * 3 + (dh == 5 ? 2 : dh - 6)) * 3 + e;
+    if (dh == 5) return e == 0 ? -2 : -1;
+    if (dh == 6) return (1 * 3 + e) * 3 + 2;
+    return e ? (1 * 3 + 2) * 3 + 2 : -1;
 }
 
 // maximum over the wave of a value that is the same non-negative number in no particular lane
@@ -513,7 +521,7 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t x)
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-__global__ __launch_bounds__(256, 3) void stem_rows_kernel(
+__global__ __launch_bounds__(256, 4) void stem_rows_kernel(
     const float *__restrict__ img, uint32_t img_bytes, int H, int W, const float *__restrict__ w, int Co,
     int nchunks, int strips, int nseg, int seg_rows, int units, uint32_t *__restrict__ out)
 {
@@ -531,7 +539,6 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const int sg = q % nseg;                       // segment of seg_rows image rows
     const int n = q / nseg;
     const int col = lane & 31, half = lane >> 5;
-    const bool tile1 = chunk * 64 + 32 < Co;       // second 32-channel tile exists (Co % 32 == 0)
     const int y0 = sg * seg_rows;
     const int rows = min(H, y0 + seg_rows) - y0;
     const int x0 = sx * 32;
@@ -545,13 +552,15 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const int xs = x0 - 1 + p;
     const uint32_t xoff = (xs >= 0 && xs < W) ? (uint32_t)xs * 4u : OOB;
     uint32_t *const ldsw = lds[wave];
+    // image row y0 - 1 + k of the strip lives in slot k % 4
     uint32_t *const wr = ldsw + p;
-    const uint32_t *const q0 = ldsw + (half ? 3 * SR_ARR : 0) + col;            // P0 | P2, then P1 | R2
-    const uint32_t *const q2 = ldsw + 2 * SR_ARR + col + (half ? 2 : 0);        // R01[j] | R01[j+2]
-    const uint32_t *const q3 = ldsw + (half ? SR_CONST : 2 * SR_ARR + col + 1); // R01[j+1] | constant
-    if (lane == 0) {
-        ldsw[SR_CONST] = 0x3c00u;              // (1.0, 0) in the hi plane, 0 in the lo plane
-        ldsw[SR_CONST + SR_PLANE] = 0u;
+    // row y - 1 (lower half) and row y + 1 (upper half), two slots further: [first slot even / 2]
+    const uint32_t *const qa[2] = {ldsw + col + (half ? 2 * SR_SLOT : 0), ldsw + col + (half ? 0 : 2 * SR_SLOT)};
+    const uint32_t *const qb = ldsw + col + (half ? SR_Z : 0);               // row y: P | Z
+    const uint32_t *const qc = ldsw + (half ? SR_CONST : col + 2);           // row y: P[j + 2] | the constant
+    if (lane < 4) {
+        ldsw[lane * SR_SLOT + SR_CONST] = 0x3c00u;       // (1.0, 0) in the leading plane, 0 in the other
+        ldsw[lane * SR_SLOT + SR_CONST + SR_LO] = 0u;
     }
 
     const int Cow = Co >> 5;
@@ -565,7 +574,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     // (validity goes into the row offset alone: two out-of-range marks would add up to 0)
     const uint32_t out_voff = (uint32_t)(xo * Cow + widx) * 4u;
 
-    struct Planes { uint4 h[2], l[2]; float ns[3]; uint32_t ob[3]; bool ok; };
+    struct Planes { uint4 h[2], l[2]; float ns[3]; bool ok; };   // operands of a tile, norms of its columns
 
     // one image row of the strip: three floats per lane
     auto fetch = [&](int yy, float (&v)[3]) {
@@ -604,7 +613,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         const float nrm = __builtin_sqrtf(swap_add(part));
         const bool in_range = nrm >= 0x1p-60f && nrm <= 0x1p60f;
         const float sc = in_range ? norm_scale(nrm) : 1.0f;
-        if (nrm == 0.0f && ch < Co && half == 1) v[14] = 0x1p13f;   // the constant term (dword 7)
+        if (nrm == 0.0f && half == 1) v[10] = ch < Co ? 0x1p13f : 0x1p15f;   // the constant term (dword 5)
         uint32_t h4[4], l4[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
@@ -620,29 +629,39 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     }
     __syncthreads();
     if (gw >= units) return;                   // whole wave leaves; nothing is shared from here on
+    // The rare routes read the weights again behind them, so that their registers are free meanwhile (with
+    // 128 of them the sums' operands spill otherwise: 124 -> 269 us with every output undecided).
     uint4 Wh[2][2], Wl[2][2];
+    auto load_weights = [&]() {
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            Wh[m][t] = wts[0][m][t][lane];
-            Wl[m][t] = wts[1][m][t][lane];
-        }
+            for (int t = 0; t < 2; ++t) {
+                Wh[m][t] = wts[0][m][t][lane];
+                Wl[m][t] = wts[1][m][t][lane];
+            }
+    };
+    load_weights();
     // (margin: the patch norm is good to 2^-10)
     const float KW = STEM_KAPPA * 1.002f * __uint_as_float(max(wnorm[0], wnorm[1]));
     const bool w_sane = (winsane[0] | winsane[1]) == 0;
 
-    // largest magnitude of a row over the wave, as the bit pattern of a non-negative float
-    auto row_max = [&](const float (&v)[3]) {
-        const uint32_t a = __float_as_uint(v[0]) & 0x7fffffffu, b = __float_as_uint(v[1]) & 0x7fffffffu,
-                       c = __float_as_uint(v[2]) & 0x7fffffffu;
-        return wave_umax(max(max(a, b), c));
+    // ---- the strip's power of two: s brings the largest magnitude of a window into [2^11, 2^12).  It stays
+    // while every row that enters is below `hi` (2^15 scaled) and one of three reaches `lo` (2^3 scaled)
+    float sc_s = 1.0f, sc_hi = 0.0f, sc_lo = 0.0f;
+    bool sc_ok = false;
+    auto pick_scale = [&](uint32_t rm) {       // rm: largest magnitude, as bits
+        const uint32_t e = rm >> 23;
+        const bool in_range = e >= 16u && e <= 254u;
+        sc_ok = in_range || rm == 0u;          // (all zero: any scale)
+        sc_s = in_range ? __uint_as_float((265u - e) << 23) : 1.0f;
+        sc_hi = in_range ? __uint_as_float(min(e + 4u, 255u) << 23) : 0x1p-110f;
+        sc_lo = in_range ? __uint_as_float((e - 8u) << 23) : 0.0f;
     };
-
-    // Staging of a window (rows a[0..2], their maxima rm[0..2]) in pieces; piece k of STAGE_PIECES.
-    // The scaled values are kept as the pairs that are split together: channels (0, 1) of a
-    // row, channel 2 of rows (0, 1), channel 2 of row 2.
-    struct Stage { v2f pr[3], z01, z2; float s; uint32_t orb; bool ok; uint32_t sh[5], sl[5]; };
+    auto row_bits = [](const float (&v)[3]) {
+        return max(max(__float_as_uint(v[0]) & 0x7fffffffu, __float_as_uint(v[1]) & 0x7fffffffu),
+                   __float_as_uint(v[2]) & 0x7fffffffu);
+    };
     auto split2 = [](v2f f, uint32_t &hi, uint32_t &lo) {
         hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2h));
         // f - hi (exact: the difference has at most 24 bits) with the fp16 operand converted by
@@ -652,84 +671,70 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r[1]) : "v"(hi), "v"(f[1]));
         lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2h));
     };
-    constexpr int STAGE_PIECES = 12;
-    auto stage_piece = [&](int slot, const float (&a)[3][3], const uint32_t (&rm)[3], Stage &st, Planes &Bn) {
-        // order of the pieces: scale (0, 1), OR (3), splits (4..8), column norm (2), LDS (9..11)
-        constexpr int ORDER[12] = {0, 1, 3, 4, 5, 6, 7, 8, 2, 9, 10, 11};
-        const int k = ORDER[slot];
-        if (k == 0) {
-            uint32_t mb = max(rm[0], rm[1]);
-            asm volatile("" : "+s"(mb));       // wave-uniform: keeps the scale arithmetic on the scalar unit
-            mb = max(mb, rm[2]);
-            const uint32_t e = mb >> 23;
-            st.ok = e >= 16u && e <= 254u;
-            st.s = st.ok ? __uint_as_float((267u - e) << 23) : 1.0f;
-            st.pr[0] = (v2f){a[0][0] * st.s, a[0][1] * st.s};
-            st.pr[1] = (v2f){a[1][0] * st.s, a[1][1] * st.s};
-            asm volatile("" : "+v"(st.pr[0]), "+v"(st.pr[1]));
-        } else if (k == 1) {
-            st.pr[2] = (v2f){a[2][0] * st.s, a[2][1] * st.s};
-            st.z01 = (v2f){a[0][2] * st.s, a[1][2] * st.s};
-            st.z2 = (v2f){a[2][2] * st.s, 0.0f};
-            asm volatile("" : "+v"(st.pr[2]), "+v"(st.z01), "+v"(st.z2));
-        } else if (k == 3) {
-            uint32_t o[3];
+    // One row: scaled, split, written to its slot; returns the squared norm of this pixel's values (channels 0
+    // and 1 from the leading fp16 terms: 2^-10 relative, covered by the margin in KW; what rounds to zero there
+    // is below 2^-24 and covered by the constant part of the threshold).  Zero only if the three values are.
+    struct Stage { float x[4], m; uint32_t ph, pl, zh, zl; };
+    auto scale_row = [&](const float (&v)[3], float m, Stage &st) {
+        st.m = m;
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
-                o[r] = __float_as_uint(a[r][0]) | __float_as_uint(a[r][1]) | __float_as_uint(a[r][2]);
-            st.orb = o[0] | o[1] | o[2];
-            asm volatile("" : "+v"(st.orb));
-        } else if (k == 4) {
-            split2(st.pr[0], st.sh[0], st.sl[0]);
-            asm volatile("" : "+v"(st.sh[0]), "+v"(st.sl[0]));
-        } else if (k == 5) {
-            split2(st.pr[1], st.sh[1], st.sl[1]);
-            asm volatile("" : "+v"(st.sh[1]), "+v"(st.sl[1]));
-        } else if (k == 6) {
-            split2(st.z01, st.sh[2], st.sl[2]);
-            asm volatile("" : "+v"(st.sh[2]), "+v"(st.sl[2]));
-        } else if (k == 7) {
-            split2(st.pr[2], st.sh[3], st.sl[3]);
-            asm volatile("" : "+v"(st.sh[3]), "+v"(st.sl[3]));
-        } else if (k == 8) {
-            split2(st.z2, st.sh[4], st.sl[4]);
-            asm volatile("" : "+v"(st.sh[4]), "+v"(st.sl[4]));
-        } else if (k == 2) {
-            // squared norm of this pixel's column from the leading fp16 terms (2^-10 relative,
-            // covered by the margin in KW; what rounds to zero there is below 2^-24 and covered
-            // by the constant part of the threshold), and its OR, for the three patches the
-            // column belongs to
-            float n2 = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                const v2h h = __builtin_bit_cast(v2h, st.sh[i]);
-                n2 = __builtin_amdgcn_fdot2(h, h, n2, false);
-            }
-            ldsw[SR_N + 2 * p] = __float_as_uint(n2);
-            ldsw[SR_N + 2 * p + 1] = st.orb;
-        } else if (k == 9) {
-            // array order in LDS: P0 P1 R01 P2 R2
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                wr[i * SR_ARR] = st.sh[i];
-                wr[i * SR_ARR + SR_PLANE] = st.sl[i];
-            }
+        for (int c = 0; c < 3; ++c) st.x[c] = v[c] * sc_s;
+        // channel 2 of the next pixel (lanes beyond the halo repeat its last pixel: nobody reads what they write)
+        st.x[3] = __uint_as_float(
+            (uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(st.x[2]), 0x130, 0xf, 0xf, true));
+        asm volatile("" : "+v"(st.x[0]), "+v"(st.x[1]), "+v"(st.x[2]), "+v"(st.x[3]));
+    };
+    auto write_row = [&](const Stage &st, uint32_t *dst) {
+        dst[0] = st.ph;
+        dst[SR_Z] = st.zh;
+        dst[SR_LO] = st.pl;
+        dst[SR_LO + SR_Z] = st.zl;
+        const v2h h = __builtin_bit_cast(v2h, st.ph);
+        const float n2 = __builtin_fmaf(st.x[2], st.x[2], __builtin_amdgcn_fdot2(h, h, 0.0f, false));
+        return __uint_as_float(max(__float_as_uint(n2), min(__float_as_uint(st.m), 0x0d800000u)));   // 2^-100
+    };
+    float n_prev = 0.0f, n_pair = 0.0f;        // norm of the row that entered last, and of the last two together
+    auto stage_row = [&](const float (&v)[3], uint32_t *dst) {
+        Stage st;
+        scale_row(v, __uint_as_float(row_bits(v)), st);
+        split2((v2f){st.x[0], st.x[1]}, st.ph, st.pl);
+        split2((v2f){st.x[2], st.x[3]}, st.zh, st.zl);
+        return write_row(st, dst);
+    };
+
+    // Staging of the row that enters (it completes the window of the next tile, whose first row is in slot K)
+    // and the next tile's operands, in pieces
+    constexpr int STAGE_PIECES = 7;
+    auto stage_piece = [&](auto kk, int slot, const float (&v)[3], float m, Stage &st, Planes &Bn) {
+        constexpr int K = decltype(kk)::value;
+        if (slot == 0) {
+            scale_row(v, m, st);
+        } else if (slot == 1) {
+            split2((v2f){st.x[0], st.x[1]}, st.ph, st.pl);
+            asm volatile("" : "+v"(st.ph), "+v"(st.pl));
+        } else if (slot == 2) {
+            split2((v2f){st.x[2], st.x[3]}, st.zh, st.zl);
+            asm volatile("" : "+v"(st.zh), "+v"(st.zl));
+        } else if (slot == 3) {
+            const float n = write_row(st, wr + (K + 2) % 4 * SR_SLOT);
+            ldsw[SR_N + p] = __float_as_uint(n_pair + n);
+            n_pair = n_prev + n;
+            n_prev = n;
             __builtin_amdgcn_wave_barrier();
-        } else if (k == 10) {
+        } else if (slot < 6) {
             // LDS instructions of a wave execute in order: these reads see the writes above
-            Bn.h[0] = make_uint4(q0[0], q0[1], q0[2], q0[SR_ARR]);
-            Bn.h[1] = make_uint4(q0[SR_ARR + 1], q0[SR_ARR + 2], q2[0], q3[0]);
-            Bn.l[0] = make_uint4(q0[SR_PLANE], q0[SR_PLANE + 1], q0[SR_PLANE + 2], q0[SR_PLANE + SR_ARR]);
-            Bn.l[1] = make_uint4(q0[SR_PLANE + SR_ARR + 1], q0[SR_PLANE + SR_ARR + 2], q2[SR_PLANE], q3[SR_PLANE]);
+            const int pl = (slot - 4) * SR_LO;
+            const uint32_t *const a = qa[K / 2] + K % 2 * SR_SLOT + pl;
+            const uint32_t *const b = qb + (K + 1) % 4 * SR_SLOT + pl, *const c = qc + (K + 1) % 4 * SR_SLOT + pl;
+            uint4(&out)[2] = slot == 4 ? Bn.h : Bn.l;
+            out[0] = make_uint4(a[0], a[1], a[SR_Z], a[SR_Z + 1]);
+            out[1] = make_uint4(a[2], c[0], b[0], b[1]);
         } else {
             // the three columns of this lane's patch; the threshold is formed where it is used
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                Bn.ns[d] = __uint_as_float(ldsw[SR_N + 2 * (col + d)]);
-                Bn.ob[d] = ldsw[SR_N + 2 * (col + d) + 1];
-            }
-            Bn.ok = st.ok;
-            __builtin_amdgcn_wave_barrier();   // the next window is written after these reads
+            for (int d = 0; d < 3; ++d) Bn.ns[d] = __uint_as_float(ldsw[SR_N + col + d]);
+            Bn.ok = sc_ok;
+            __builtin_amdgcn_wave_barrier();   // the next row is written after these reads
         }
     };
 
@@ -765,7 +770,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     int qn = 0;   // entries of the list of undecided outputs
     // ---- decision and store of a finished row
     struct Done { float T; bool zero; int i; };
-    struct Epi { float mn; uint32_t sg[2]; };
+    struct Epi { float mn; uint32_t sg; };     // bit b of sg: sign of register b % 16 of tile b / 16
     constexpr int EPI_PIECES = 7;
     auto epi_piece = [&](int k, const v16f (&acc)[2], const Done &dn, Epi &ep) {
         if (k == 0) {
@@ -773,24 +778,20 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 #pragma unroll
             for (int e = 2; e < 16; ++e) mn = __builtin_fminf(mn, __builtin_fabsf(acc[0][e]));
             ep.mn = mn;
-            ep.sg[0] = ep.sg[1] = 0u;
+            ep.sg = 0u;
             asm volatile("" : "+v"(ep.mn));
         } else if (k == 1) {
-            if (tile1) {
-                float mn = ep.mn;
+            float mn = ep.mn;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) mn = __builtin_fminf(mn, __builtin_fabsf(acc[1][e]));
-                ep.mn = mn;
-            }
+            for (int e = 0; e < 16; ++e) mn = __builtin_fminf(mn, __builtin_fabsf(acc[1][e]));
+            ep.mn = mn;
             asm volatile("" : "+v"(ep.mn));
         } else if (k < 6) {
-            // sign bits (1 = negative) of the 2 x 16 channels of this lane, four per tile and piece
+            // sign bits (1 = negative) of the 2 x 16 channels of this lane, eight per piece
 #pragma unroll
-            for (int e = 15 - 4 * (k - 2); e > 11 - 4 * (k - 2); --e)
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-                    ep.sg[m] = __builtin_amdgcn_alignbit(ep.sg[m], __float_as_uint(acc[m][e]), 31);
-            asm volatile("" : "+v"(ep.sg[0]), "+v"(ep.sg[1]));
+            for (int e = 31 - 8 * (k - 2); e > 23 - 8 * (k - 2); --e)
+                ep.sg = __builtin_amdgcn_alignbit(ep.sg, __float_as_uint(acc[e >> 4][e & 15]), 31);
+            asm volatile("" : "+v"(ep.sg));
         } else {
             const int y = y0 + dn.i;
             const float T = dn.T;
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
             // ---- sequential route for the undecided outputs (rare): a few of them are put on the wave's
             // list and summed later, one per lane, instead of in the lane that found them with 63 idle
             // (their bits are provisional until then); a tile with many (unusual data) sums in place
-            if (__builtin_amdgcn_ballot_w64(flag) != 0) {
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(flag) != 0, 0)) {
                 uint32_t fl[2] = {0, 0};
                 if (flag)
 #pragma unroll
@@ -836,36 +837,44 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                         const float sum = chain(px, pv, chunk * 64 + (b >> 4) * 32 + 16 * half + (b & 15));
                         neg |= (sum >= 0.0f ? 0u : 1u) << b;   // NaN -> bit 0
                     }
-                    ep.sg[0] = (ep.sg[0] & ~todo) | (neg & 0xffffu);
-                    ep.sg[1] = (ep.sg[1] & ~(todo >> 16)) | (neg >> 16);
+                    ep.sg = (ep.sg & ~todo) | neg;
                 }
+                load_weights();
             }
-            if (dn.zero) { ep.sg[0] = 0u; ep.sg[1] = 0u; }   // a chain of zero terms ends at +0.0f
-            const uint32_t word = finish_word64(ep.sg[0], ep.sg[1], psel);
+            const uint32_t mine = dn.zero ? ~0u : ~ep.sg;   // a chain of zero terms ends at +0.0f
+            const auto sw = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
+            const uint32_t word = __builtin_amdgcn_perm(sw[1], sw[0], psel);
             const uint32_t roff = live && widx < Cow ? (uint32_t)y * out_row_bytes : OOB;
             __builtin_amdgcn_raw_buffer_store_b32(word, orsrc, out_voff + roff, 0, 0);
         }
     };
 
-    // ---- one tile: matrix instructions of row y on planes B, between them the staging of row
-    // y + 1 (rows a[1], a[2] and the row fetched two tiles ago); then decision and store.
+    // ---- one tile: matrix instructions of row y on planes B, between them the staging of row y + 2 (fetched
+    // two tiles ago) for the tile below; then decision and store.  K: slot of row y, the first of the next window.
     // (Running the decision of row y - 1 between the matrix instructions as well, with a second
     // set of accumulators, measured no faster: the kernel is bound by the vector instruction
-    // count, and three waves per SIMD - which the smaller register count allows - hide more.)
-    auto tile = [&](const int i, const Planes &B, Planes &Bn, float (&a)[3][3], uint32_t (&rm)[3],
-                    float (&ld)[3]) {
+    // count, and the waves that the smaller register count allows hide more.)
+    int low = 0;                               // rows in a row that did not reach sc_lo
+    auto tile = [&](auto kk, const int i, const Planes &B, Planes &Bn, float (&ld)[3]) {
+        constexpr int K = decltype(kk)::value;
         const int y = y0 + i;
-        // the window moves down one row
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            a[0][c] = a[1][c];
-            a[1][c] = a[2][c];
-            a[2][c] = ld[c];
+        const float m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(ld[0]), __builtin_fabsf(ld[1])),
+                                        __builtin_fabsf(ld[2]));
+        low = __builtin_amdgcn_ballot_w64(m >= sc_lo) != 0 ? 0 : low + 1;
+        if (__builtin_expect(!sc_ok || low >= 3 || __builtin_amdgcn_ballot_w64(!(m < sc_hi)) != 0, 0)) {
+            // another scale: the window's other two rows once more (unless this row has none either)
+            const uint32_t own = wave_umax(row_bits(ld)) >> 23;
+            if (sc_ok || own == 0u || (own >= 16u && own <= 254u)) {
+                float r0[3], r1[3];
+                fetch(y, r0);
+                fetch(y + 1, r1);
+                pick_scale(wave_umax(max(max(row_bits(r0), row_bits(r1)), row_bits(ld))));
+                n_pair = stage_row(r0, wr + K * SR_SLOT);
+                n_prev = stage_row(r1, wr + (K + 1) % 4 * SR_SLOT);
+                n_pair += n_prev;
+                low = 0;
+            }
         }
-        rm[0] = rm[1];
-        rm[1] = rm[2];
-        rm[2] = row_max(a[2]);
-        fetch(y + 4, ld);
 
         v16f acc[2];
 #pragma unroll
@@ -880,10 +889,11 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_v8h(WP[m][t]), as_v8h(BP[t]), acc[m], 0, 0, 0);
+                for (int mm = 0; mm < 2; ++mm) {
+                    acc[mm] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_v8h(WP[mm][t]), as_v8h(BP[t]), acc[mm], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (slot < STAGE_PIECES) stage_piece(slot, a, rm, st, Bn);
+                    if (slot < STAGE_PIECES) stage_piece(kk, slot, ld, m, st, Bn);
+                    if (slot == 0) fetch(y + 4, ld);
                     ++slot;
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -891,26 +901,28 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         mma(Wl, B.h);      // small terms first
         mma(Wh, B.l);
         mma(Wh, B.h);
-        static_assert(STAGE_PIECES <= 12 && EPI_PIECES <= 12, "one piece of each kind per matrix instruction");
+        static_assert(STAGE_PIECES <= 12, "one piece per matrix instruction");
 
-        dn.zero = ((B.ob[0] | B.ob[1] | B.ob[2]) << 1) == 0;          // every patch value is +-0
+        const float n2 = B.ns[0] + B.ns[1] + B.ns[2];
+        dn.zero = __float_as_uint(n2) == 0u;                          // every patch value is +-0
         // (the hardware square root is good to 1 ulp; KW carries the margin)
-        dn.T = (B.ok && w_sane) ? __builtin_fmaf(KW, __builtin_amdgcn_sqrtf(B.ns[0] + B.ns[1] + B.ns[2]), SR_FLOOR)
-                                : __builtin_inff();
+        dn.T = (B.ok && w_sane) ? __builtin_fmaf(KW, __builtin_amdgcn_sqrtf(n2), SR_FLOOR) : __builtin_inff();
         dn.i = i;
 #pragma unroll
         for (int k = 0; k < EPI_PIECES; ++k) epi_piece(k, acc, dn, ep);
     };
 
     // ---- prologue: rows y0 - 1 .. y0 + 1 staged for the first tile
-    uint32_t rm[3];
     Planes B0, B1;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) rm[r] = row_max(a[r]);
     {
+        pick_scale(wave_umax(max(max(row_bits(a[0]), row_bits(a[1])), row_bits(a[2]))));
+        n_pair = stage_row(a[0], wr);
+        n_prev = stage_row(a[1], wr + SR_SLOT);
+        n_pair += n_prev;
         Stage st;
+        const float m = __uint_as_float(row_bits(a[2]));
 #pragma unroll
-        for (int k = 0; k < STAGE_PIECES; ++k) stage_piece(k, a, rm, st, B0);
+        for (int k = 0; k < STAGE_PIECES; ++k) stage_piece(std::integral_constant<int, 0>{}, k, a[2], m, st, B0);
     }
     // the listed outputs, one per lane
     auto flush = [&]() {
@@ -928,14 +940,21 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                 else atomicAnd(word, ~(1u << (ch & 31)));   // NaN -> bit 0
             }
         qn = 0;
+        load_weights();
     };
-    // two rows per trip (operand planes and fetch registers alternate); with an odd row count the
-    // second row of the last trip is computed and dropped.  A row lists at most 64 outputs.
+    // four rows per trip: operand planes and fetch registers alternate, the slots rotate.  A row lists at most
+    // 64 outputs.
 #pragma unroll 1
-    for (int i = 0; i < rows; i += 2) {
-        if (qn > SR_QCAP - 128) flush();
-        tile(i, B0, B1, a, rm, ld0);
-        tile(i + 1, B1, B0, a, rm, ld1);
+    for (int i = 0; i < rows; i += 4) {
+        if (__builtin_expect(qn > SR_QCAP - 128, 0)) flush();
+        tile(std::integral_constant<int, 1>{}, i, B0, B1, ld0);
+        if (i + 1 >= rows) break;
+        tile(std::integral_constant<int, 2>{}, i + 1, B1, B0, ld1);
+        if (i + 2 >= rows) break;
+        if (__builtin_expect(qn > SR_QCAP - 128, 0)) flush();
+        tile(std::integral_constant<int, 3>{}, i + 2, B0, B1, ld0);
+        if (i + 3 >= rows) break;
+        tile(std::integral_constant<int, 0>{}, i + 3, B1, B0, ld1);
     }
     if (qn) flush();
 }
@@ -946,11 +965,14 @@ static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int 
     const int nchunks = ceil_div(Co, 64);
     const int strips = ceil_div(W, 32);
     const long base = (long)N * strips * nchunks;
-    // as many row segments as it takes to give every wave slot of the chip (three per SIMD) one unit
-    const long slots = 3L * 4 * 256;
-    const int want = (int)std::max(1L, slots / base);
-    int seg_rows = ceil_div(H, want);
-    seg_rows = std::max(2, seg_rows + (seg_rows & 1));
+    // as many row segments as it takes to give every wave slot of the chip one unit: four per SIMD, or three
+    // where four would leave fewer than eight rows each, whose first two cost as much as two more (512x512: 2 rows
+    // 10.4 us, 4 rows 9.2; 301x777 twice, 96 channels: 8 rows 19.1, 12 rows 19.9)
+    int seg_rows = ceil_div(H, (int)std::max(1L, 4L * 4 * 256 / base));
+    if (seg_rows < 8) {
+        seg_rows = ceil_div(H, (int)std::max(1L, 3L * 4 * 256 / base));
+        seg_rows = std::max(2, seg_rows + (seg_rows & 1));
+    }
     const int nseg = ceil_div(H, seg_rows);
     const long units = (long)N * strips * nseg;   // of every chunk
     if (units > 0x7fffffffL || (units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");

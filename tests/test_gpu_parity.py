@@ -1134,6 +1134,42 @@ def test_stem_lists_of_undecided_outputs(ties):
     assert torch.equal(bits, ref)
 
 
+@pytest.mark.parametrize("w,co", [(1024, 64), (999, 32), (1000, 96)])
+def test_stem_scale_kept_from_row_to_row(w, co):
+    """Row-walking kernel on segments of a whole image whose magnitude steps up and down from row to row:
+    the strip's scale is kept, chosen again at every position of the row slots, and survives rows of
+    zeros, of NaN and of infinities.  Against the chain kernel."""
+    say(f"stem scale kept from row to row w={w} Co={co}")
+    rng = np.random.default_rng(w)
+    n, h = 64, 131
+    img = rng.standard_normal((n, 3, h, w), dtype=np.float32)
+    for i in range(n):
+        y = 0
+        while y < h:
+            run = int(rng.integers(1, 9))
+            kind = i % 8 and int(rng.integers(0, 12))       # every eighth image is an ordinary one
+            if kind:
+                rows = img[i, :, y:y + run]
+                if kind == 1:
+                    rows[:] = 0.0
+                elif kind == 2 and i % 4 == 1:
+                    rows[:, :1, 40:42] = np.nan
+                elif kind == 3 and i % 4 == 2:
+                    rows[:, :1, 70] = np.inf
+                else:
+                    rows *= np.float32(2.0 ** int(rng.choice([-125, -40, -9, -7, -4, 3, 4, 5, 20, 60])))
+            y += run
+    x, wd = dev(img), dev(rng.standard_normal((co, 3, 3, 3), dtype=np.float32))
+    bits, _ = B.stem_fp32(x, wd)
+    B.set_stem_path(B.STEM_VALU)
+    try:
+        ref, _ = B.stem_fp32(x, wd)
+        torch.cuda.synchronize()
+    finally:
+        B.set_stem_path(B.STEM_AUTO)
+    assert torch.equal(bits, ref)
+
+
 def test_stem_tiles_with_many_undecided_outputs():
     """Row-walking kernel on data that leaves whole tiles undecided: the bits of the chain kernel, at a
     price per output that shares the fetches of a patch among the outputs of a pixel.  Measured against
