@@ -613,6 +613,229 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
     }
 }
 
+// One wave, all four positions.  In the kernel above each of the four position waves expands the same words,
+// and a wave's sign collection follows its matrix instructions.  Here a wave owns RGX rows of 32 pixels and
+// contracts them for all four positions: the words are fetched once, 4 KS bytes per lane (the lower lane half
+// takes the first KS words of a pixel, the upper half the others: which words pair up in a step is free), and
+// expanded once into registers that eight phases (position, 32-channel tile) read.  The weights of all positions
+// stay in LDS, shared by the eight waves of a block; a fragment feeds RGX matrix instructions, and its register
+// is refilled for a later phase as soon as the last of them has issued.  Pairs of rows alternate between two sets of
+// accumulators, so the signs of one pair are collected between the matrix instructions of the next.  Output
+// pixels 2x and 2x + 1 end in one wave: a lane half takes one of them and stores both words of the channel tile.
+// No barrier behind the weights.  Needs an even word count.
+// What bounds it: the matrix pipe, 75 % busy at 1.86 GHz (32x160x239, 256->128: 59 us = 5.4 PFLOP/s, the four position
+// waves above 79), next to 5.4 vector instructions per matrix instruction: 4 sign collections, 0.9 expansion (3.5
+// there), 0.5 words and stores.
+template <int KS, int RGX, int WV, bool EVEN>
+__global__ __launch_bounds__(64 * WV, WV / 4) void tconv_wave_kernel(
+    const uint32_t *__restrict__ act, int N, int H, int W, const uint4 *__restrict__ wfrag, int Cout, int units,
+    TileStep step, const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum, int cout_pad64,
+    uint32_t *__restrict__ out_bits)
+{
+    constexpr uint32_t BAD = 0x40000000u;      // beyond any tensor this kernel accepts (< 2^30 bytes)
+    constexpr int CW = 2 * KS;                 // words per pixel
+    constexpr int NP = RGX / 2;                // pairs of rows
+    constexpr int NW = NP == 1 && KS > 4 ? 4 : KS;   // weight fragments in registers
+    constexpr int NF = 8 * KS;                 // weight fragments of the channel tile
+    __shared__ uint4 wts[NF * 64];             // [position][tile 1, tile 0][step][lane]
+    __shared__ float4 start[8][2][4];          // [position, tile 1 and 0][half][4 x 4 channels]: -(theta + sum w) / 2
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ct = blockIdx.y;                 // 64-channel output tile
+    const int col = lane & 31, half = lane >> 5;
+    const int Cow = Cout >> 5;
+
+    const __amdgpu_buffer_rsrc_t ars =
+        __builtin_amdgcn_make_buffer_rsrc((void *)act, 0, N * H * W * CW * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ors =
+        __builtin_amdgcn_make_buffer_rsrc((void *)out_bits, 0, N * H * W * 4 * Cow * 4, 0x00020000);
+
+    // units: consecutive ones go to different blocks, so that a last round that is not full leaves every
+    // compute unit some of its waves
+    const int stride = (int)gridDim.x * WV;
+    int u = wave * (int)gridDim.x + (int)blockIdx.x;
+    TilePos cur = tile_pos(u < units ? u : 0, step.tiles_x, step.tiles_y);
+    uint32_t wd[RGX][KS];
+    auto fetch = [&](const TilePos &tp) {
+        const uint32_t off = tp.tx * 32 + col < W ? (uint32_t)((col * CW + half * KS) * 4) : BAD;   // (reads 0)
+#pragma unroll
+        for (int r = 0; r < RGX; ++r) {
+            const int y = min(tp.ty * RGX + r, H - 1);       // (a row beyond the image: not stored)
+            const int row = (((tp.n * H + y) * W) + tp.tx * 32) * CW * 4;
+#pragma unroll
+            for (int i = 0; i < KS; i += 4) {
+                if (KS - i >= 4) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(ars, off, row + 4 * i, 0);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) wd[r][min(i + k, KS - 1)] = v[k];
+                } else {
+                    if (KS - i >= 2) {
+                        const auto v = __builtin_amdgcn_raw_buffer_load_b64(ars, off, row + 4 * i, 0);
+                        wd[r][i] = v[0];
+                        wd[r][min(i + 1, KS - 1)] = v[1];
+                    }
+                    if ((KS - i) & 1) wd[r][KS - 1] = __builtin_amdgcn_raw_buffer_load_b32(ars, off, row + 4 * (KS - 1), 0);
+                }
+            }
+        }
+    };
+    fetch(cur);
+
+    // ---- weights: step ks takes word ks of the lower and word KS + ks of the upper lane half; in the blob
+    // ([tile64][step][position][m][lane]) the words 2 k and 2 k + 1 share a fragment
+#pragma unroll
+    for (int f = wave; f < NF; f += WV) {      // position, tile, step
+        const int ks = f % KS, pm = f / KS;
+        const int word = half * KS + ks;
+        wts[f * 64 + lane] =
+            wfrag[((((size_t)ct * KS + (word >> 1)) * 4 + (pm >> 1)) * 2 + (1 - (pm & 1))) * 64 + 32 * (word & 1) + col];
+    }
+    if (tid < 64) {
+        const int pm = tid >> 3, h = (tid >> 2) & 1, q = tid & 3;
+        const int cbase = ct * 64 + (1 - (pm & 1)) * 32 + 16 * h + 4 * q;
+        int4 t = make_int4(0, 0, 0, 0), v = make_int4(0, 0, 0, 0);
+        if (cbase < Cout) {
+            t = *reinterpret_cast<const int4 *>(thresh + cbase);
+            v = *reinterpret_cast<const int4 *>(wsum + (size_t)(pm >> 1) * cout_pad64 + cbase);
+        }
+        start[pm][h][q] = make_float4(start_value(t.x, v.x), start_value(t.y, v.y), start_value(t.z, v.z),
+                                      start_value(t.w, v.w));
+    }
+    __syncthreads();
+    if (u >= units) return;                    // whole wave leaves; nothing is shared from here on
+
+    const uint32_t out_lane = (uint32_t)(((2 * col + half) * Cow + ct * 2) * 4);
+    const int out_row = 2 * W * Cow * 4;       // bytes of a row of output pixels
+    // where a unit's outputs go: offset of its first row, rows inside the image, lane offset in a row
+    struct Out { uint32_t base, lane; int rows; };
+    auto outputs = [&](const TilePos &tp) {
+        return Out{(uint32_t)(((tp.n * H + tp.ty * RGX) * 2 * W + tp.tx * 32) * 2 * Cow * 4),
+                   tp.tx * 32 + col < W ? out_lane : BAD, H - tp.ty * RGX};
+    };
+    v4i Wf[NW];
+    auto load_w = [&](int f) {                 // fragment f of the unit's sequence into its register
+        const uint4 a = wts[f % NF * 64 + lane];
+        Wf[f % NW] = (v4i){(int)a.x, (int)a.y, (int)a.z, (int)a.w};
+    };
+    v16f init;
+    auto load_init = [&](int pm) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = start[pm][half][q];
+            init[4 * q] = f.x; init[4 * q + 1] = f.y; init[4 * q + 2] = f.z; init[4 * q + 3] = f.w;
+        }
+    };
+#pragma unroll
+    for (int f = 0; f < NW; ++f) load_w(f);
+    load_init(0);
+
+    v16f acc[2][2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q >> 1][q & 1] = (v16f)(0.0f);
+    uint32_t sg[2][RGX] = {};                  // signs of the row's outputs at dx = 0, 1: bit k = register k % 16 of tile k / 16
+    // what phase t of a unit leaves in its accumulators: signs [from, to) of its two rows
+    auto collect = [&](int t, int from, int to) {
+        const int pm = t / NP, dx = pm >> 1 & 1, r0 = t % NP * 2;
+#pragma unroll
+        for (int i = from; i < to; ++i) {
+            const int j = i & 1, e = 15 - (i >> 1);
+            const uint32_t before = (pm & 1) == 0 && e == 15 ? 0u : sg[dx][r0 + j];
+            sg[dx][r0 + j] = __builtin_amdgcn_alignbit(before, __float_as_uint(acc[t & 1][j][e]), 31);
+        }
+    };
+    // rows of the pair whose phase t was the last of two neighbouring output pixels
+    auto store = [&](int t, const Out &o) {
+        const int dy = t / NP >> 2, r0 = t % NP * 2;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int r = r0 + j;
+            const auto sw = __builtin_amdgcn_permlane32_swap(~sg[0][r], ~sg[1][r], false, false);
+            const uint32_t w0 = __builtin_amdgcn_perm(sw[1], sw[0], 0x05040100u);
+            const uint32_t w1 = __builtin_amdgcn_perm(sw[1], sw[0], 0x07060302u);
+            const uint32_t at = o.lane + (r < o.rows ? o.base + (uint32_t)((2 * r + dy) * out_row) : BAD);
+            if (EVEN) {
+                typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+                __builtin_amdgcn_raw_buffer_store_b64((v2u){w0, w1}, ors, at, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b32(w0, ors, at, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(w1, ors, ct * 2 + 1 < Cow ? at + 4 : 3 * BAD, 0, 0);
+            }
+        }
+    };
+
+    Out prev{0, BAD, RGX};                     // (nothing waits before the first unit)
+#pragma unroll 1
+    for (;;) {
+        asm volatile("" ::: "memory");         // (weights and start values are not to be kept from unit to unit)
+        v4i B[RGX][KS];
+#pragma unroll
+        for (int r = 0; r < RGX; ++r)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const uint4 e = expand_word(wd[r][ks]);
+                B[r][ks] = (v4i){(int)e.x, (int)e.y, (int)e.z, (int)e.w};
+                asm volatile("" : "+v"(B[r][ks]));
+            }
+        const Out here = outputs(cur);
+        u += stride;
+        TilePos nxt = cur;
+        if (u < units) nxt.advance(step);
+        fetch(nxt);                            // (the same unit again, unused, after the last)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < 8 * NP; ++t) {
+            const int pm = t / NP, r0 = t % NP * 2, before = t ? t - 1 : 8 * NP - 1;
+            const bool last_pair = t % NP == NP - 1;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int slot = 2 * ks + j;
+                    acc[t & 1][j] = mfma_f4(Wf[(pm * KS + ks) % NW], B[r0 + j][ks], ks == 0 ? init : acc[t & 1][j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (last_pair && j == 1) {
+                        load_w(pm * KS + ks + NW);
+                        if (ks == 0) load_init((pm + 1) % 8);
+                    }
+                    collect(before, 32 * slot / (2 * KS), 32 * (slot + 1) / (2 * KS));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            if (before / NP % 4 == 3) {        // dx = 1, tile 0
+                store(before, t ? here : prev);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        prev = here;
+        cur = nxt;
+        if (u >= units) break;
+    }
+    collect(8 * NP - 1, 0, 32);
+    store(8 * NP - 1, prev);
+}
+
+template <int KS, int RGX, int WV>
+static int launch_tconv_wave(const uint32_t *act, int N, int H, int W, const TconvLayout &L, const uint4 *wfrag,
+                             const int32_t *thresh, uint32_t *out_bits, hipStream_t s)
+{
+    const int tiles_x = ceil_div(W, 32), tiles_y = ceil_div(H, RGX);
+    const long units = (long)N * tiles_y * tiles_x;
+    if (units > 0x3fffffffL) return fail(MBU_ERR_SHAPE, "too many pixel groups for one launch");
+    const int tiles64 = L.cout_pad64 / 64;
+    // one block of eight waves per compute unit in total, spread over the 64-channel tiles
+    const int per_tile = (int)std::min((units + WV - 1) / WV, (long)std::max(1, 256 / tiles64));
+    const int32_t *wsum = (const int32_t *)((const uint8_t *)wfrag - L.off_f4 + L.off_sum);
+    const dim3 grid((unsigned)per_tile, (unsigned)tiles64), block(64 * WV);
+    const TileStep step = tile_step(per_tile * WV, tiles_x, tiles_y);
+    if (L.cout % 64 == 0)
+        MBU_LAUNCH((tconv_wave_kernel<KS, RGX, WV, true>), grid, block, 0, s, act, N, H, W, wfrag, L.cout, (int)units, step,
+                   thresh, wsum, L.cout_pad64, out_bits);
+    else
+        MBU_LAUNCH((tconv_wave_kernel<KS, RGX, WV, false>), grid, block, 0, s, act, N, H, W, wfrag, L.cout, (int)units, step,
+                   thresh, wsum, L.cout_pad64, out_bits);
+    return check_launch("tconv2x2_masked_binary");
+}
+
 template <int KS, int RGX>
 static int launch_tconv_res(const uint32_t *act, int N, int H, int W, const TconvLayout &L, const uint4 *wfrag,
                             const int32_t *thresh, uint32_t *out_bits, hipStream_t s)
@@ -643,11 +866,37 @@ int launch_tconv_mfma(const uint32_t *act, int N, int H, int W, const TconvLayou
     const int tiles64 = L.cout_pad64 / 64;
     const double GiB = 1073741824.0;
     const bool small = (double)N * H * W * L.cin_words * 4 < GiB && (double)N * H * W * 4 * (L.cout >> 5) * 4 < GiB;
-    // Up to 1024 input channels (16 steps of weights fit in registers) where a group of 1, 2 or 4 rows divides
+    // Else up to 1024 input channels (16 steps of weights fit in registers) where a group of 1, 2 or 4 rows divides
     // evenly over the block, at most five words of one pixel per thread: weights resident.  Against the
     // kernels below: 64->64 at 8x160x239 18.5 -> 10.4 us, 192->96 at 2x160x239 11.2 -> 8.3, 320->512 at
     // 20x872 16.2 -> 10.3, 384->192 at 4x80x80 12.5 -> 8.6, 640->320 at 8x80x119 56.9 -> 31.6 and at 16x16
     // 8.1 -> 4.2, 768->512 at 64x64 10.5 -> 7.0.
+    // Large layers: a wave for all four positions.  It pays once the wave slots (two or three per SIMD) have more
+    // than one unit of two rows each: block of four position waves -> here, us in a kernel trace: 64->128 at 256x320, 2560
+    // units, 7.3 -> 6.8, 128->128 at 256x320, 2560, 7.9 -> 7.8, at 3x160x239, 3840, 9.8 -> 6.9, 256->128 at 256x320, 2560,
+    // 9.8 -> 7.6, at 160x160 twice, 1600, 7.0 -> 7.4, 384->192 at 160x160 twice, 2400, 12.3 -> 11.4; below it the
+    // position waves are four times as many (256->128 at 64x64, 128 units, 3.8 -> 5.4).  With eight steps the
+    // weights of a block are 64 KB and two rounds are wanted (512->256 at 160x160 twice, 3200, 14.0 -> 14.7, 512->512 at
+    // 128x256, 4096, 17.0 -> 16.1).  640 and more channels gain nothing (640->320 at 8x80x119 31.5 -> 31.0).
+    // Units of four rows halve the reads of the weights where there are enough of them: 32x160x239, 256->128,
+    // 61.0 -> 59.2 (four position waves 79.5), 32x320x479, 128->64, 79.0 -> 76.7 (98.0).
+    const long units2 = (long)N * ceil_div(H, 2) * groups_x * tiles64;
+    if (!out_acc && small && L.cin_words == 2 * L.ksteps && units2 >= (L.ksteps == 8 ? 4096 : 2560)) {
+        const bool four = units2 >= 16384;
+        switch (L.ksteps) {
+        case 1: return four ? launch_tconv_wave<1, 4, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s)
+                            : launch_tconv_wave<1, 2, 12>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 2: return four ? launch_tconv_wave<2, 4, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s)
+                            : launch_tconv_wave<2, 2, 12>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 3: return four ? launch_tconv_wave<3, 4, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s)
+                            : launch_tconv_wave<3, 2, 12>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 4: return four ? launch_tconv_wave<4, 4, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s)
+                            : launch_tconv_wave<4, 2, 12>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 5: return launch_tconv_wave<5, 2, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 6: return launch_tconv_wave<6, 2, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        case 8: return launch_tconv_wave<8, 2, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s);
+        }
+    }
     if (!out_acc && small && L.cin_words == 2 * L.ksteps) switch (L.ksteps) {
         case 1: return launch_tconv_res<1, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
         case 2: return launch_tconv_res<2, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);

@@ -521,6 +521,33 @@ def test_tconv_matches_oracle_elementwise(shape):
     assert not host(az).any()
 
 
+# one wave for all four positions: layers above its line (2560 units of two rows, 4096 with eight steps) and units
+# of four rows (16384), with ragged rows and columns and an odd count of output words
+@pytest.mark.parametrize("shape, instance", [
+    ((3, 213, 255, 64, 128), "1, 2, 12, true"), ((5, 206, 321, 64, 32), "1, 2, 12, false"),
+    ((1, 255, 160, 128, 256), "2, 2, 12, true"), ((2, 129, 321, 192, 96), "3, 2, 12, false"),
+    ((1, 512, 320, 256, 64), "4, 2, 12, true"), ((10, 87, 63, 256, 160), "4, 2, 12, false"),
+    ((2, 143, 161, 320, 192), "5, 2, 8, true"), ((1, 127, 350, 384, 224), "6, 2, 8, false"),
+    ((1, 127, 257, 512, 512), "8, 2, 8, true"), ((1, 201, 161, 512, 480), "8, 2, 8, false"),
+    ((4, 513, 1001, 64, 32), "1, 4, 8, false"), ((1, 1023, 513, 128, 128), "2, 4, 8, true"),
+    ((2, 511, 350, 192, 160), "3, 4, 8, false"), ((3, 341, 319, 256, 256), "4, 4, 8, true"),
+])
+def test_tconv_one_wave_for_all_positions(shape, instance):
+    """Against the kernel that writes the accumulators (compared with the oracle above)."""
+    N, H, W, Cin, Cout = shape
+    say(f"tconv wave N={N} H={H} W={W} Cin={Cin} Cout={Cout}")
+    rng = np.random.default_rng(H * W)
+    words = Cin // 32
+    act = dev(rng.integers(-2 ** 31, 2 ** 31, (N, H, W, words)).astype(np.int32))
+    blob = B.pack_tconv_weights(dev(synth.ternary_tconv_weights(10, 0, 0, Cout, Cin, 0.6)))
+    th = dev(synth.thresholds(10, 0, 0, Cout, max(1, Cin // 8)))
+    bits, _ = B.tconv2x2_masked_binary(act, Cin, blob, Cout, th, True, False)
+    assert B.last_kernel() == f"tconv_wave_kernel<{instance}>"
+    ref, _ = B.tconv2x2_masked_binary(act, Cin, blob, Cout, th, True, True)
+    torch.cuda.synchronize()
+    assert torch.equal(bits, ref)
+
+
 @pytest.mark.parametrize("shape", [(1, 12, 40, 64, 64, 64), (2, 9, 33, 96, 160, 96),
                                    (1, 8, 34, 32, 40, 64)])
 def test_conv_on_plain_concatenation(shape):

@@ -83,3 +83,20 @@ def test_small_up_sampled_layers(h, w, ca, cb, cout, kernel):
 def test_transposed_layers(cin, kernel):
     """Weights resident for every width up to 1024 channels whose groups divide evenly over a block."""
     assert choice([(32, 32), (32, 32), (32, cin), (cin, cin), (64, 32), (32, 32)], 1, 40, 60, 6, (cin, 32)) == kernel
+
+
+@pytest.mark.parametrize("n, h, w, cin, cout, kernel", [
+    (1, 64, 1280, 256, 128, "tconv_wave_kernel<4, 2, 12, true>"),      # 2560 units of two rows
+    (1, 62, 1280, 256, 128, "tconv_res_kernel<4, 4>"),
+    (8, 62, 1024, 256, 128, "tconv_wave_kernel<4, 2, 12, true>"),      # 15872
+    (8, 64, 1024, 256, 128, "tconv_wave_kernel<4, 4, 8, true>"),      # 16384
+    (1, 128, 512, 512, 256, "tconv_wave_kernel<8, 2, 8, true>"),       # 4096
+    (1, 126, 512, 512, 256, "tconv_res_kernel<8, 2>"),
+    (8, 126, 1024, 64, 32, "tconv_wave_kernel<1, 2, 12, false>"),
+    (8, 80, 119, 640, 320, "tconv_res_kernel<10, 2>"),
+    (32, 40, 59, 1024, 512, "tconv_res_kernel<16, 1>"),
+    (8, 128, 1024, 96, 64, "tconv_bits_kernel<4>"),
+])
+def test_transposed_layers(n, h, w, cin, cout, kernel):
+    convs = [(32, 32), (32, 32), (32, cin), (cin, cin), (32 + cout, 32), (32, 32)]
+    assert choice(convs, n, 2 * h, 2 * w, 6, (cin, cout)) == kernel
