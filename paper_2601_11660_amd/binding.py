@@ -1,4 +1,5 @@
-"""Thin ctypes binding over the C ABI declared in include/mbu.h.
+"""Thin binding over the C ABI declared in include/mbu.h: ctypes, and for the plain form of the
+single-layer calls a native module (csrc/native_calls.cpp) that checks, allocates and calls.
 
 Argument marshalling only: every step of the path runs in the HIP kernels of
 libmbu_hip.so.  PyTorch supplies device memory and the current stream, nothing else.
@@ -6,6 +7,8 @@ There is no CPU fallback: if the library has not been built, importing the entry
 points raises.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import List, Optional, Sequence, Tuple
 
@@ -13,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmbu_hip.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 MBU_OK = 0
 MBU_ERR_NULL, MBU_ERR_SHAPE, MBU_ERR_ALIGN, MBU_ERR_WORKSPACE, MBU_ERR_HIP, MBU_ERR_ARG = -1, -2, -3, -4, -5, -6
@@ -58,15 +62,17 @@ class UNetDesc(ctypes.Structure):
 
 
 _lib = None
+_calls = None
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises if it has not been built."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is missing: build it first "
-                               "(python -m paper_2601_11660_amd.build); there is no fallback path")
+        for path in (LIB_PATH, NATIVE_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError(f"{path} is missing: build it first "
+                                   "(python -m paper_2601_11660_amd.build); there is no fallback path")
         L = ctypes.CDLL(LIB_PATH)
         L.mbu_last_error.restype = ctypes.c_char_p
         L.mbu_last_kernel.restype = ctypes.c_char_p
@@ -110,8 +116,25 @@ def lib() -> ctypes.CDLL:
         L.mbu_event_destroy.argtypes = [vp]
         L.mbu_event_record.argtypes = [vp, vp]
         L.mbu_event_elapsed_ms.argtypes = [vp, vp, ctypes.POINTER(ctypes.c_float)]
-        _lib = L
+        loader = importlib.machinery.ExtensionFileLoader(__package__ + "._native", NATIVE_PATH)
+        spec = importlib.util.spec_from_loader(loader.name, loader)
+        native = importlib.util.module_from_spec(spec)
+        loader.exec_module(native)
+        if _raw_stream is not None:     # (without it the native calls leave everything to the code below)
+            native.bind(*(ctypes.cast(f, vp).value for f in (
+                L.mbu_conv3x3_masked_binary, L.mbu_conv3x3_masked_binary_fused, L.mbu_conv3x3_masked_binary_concat,
+                L.mbu_conv3x3_masked_binary_two_inputs, L.mbu_tconv2x2_masked_binary, L.mbu_pack_act,
+                L.mbu_stem_fp32, L.mbu_classifier_fp32)), torch._C._cuda_getDevice, _raw_stream)
+        _calls, _lib = native, L
     return _lib
+
+
+def _native():
+    """The native calls.  Each takes the plain case - contiguous device tensors of the expected dtype, whole
+    numbers, no mode or subclass - and returns the outputs or an error code; None leaves the call to the
+    general code, which allocates, checks and raises in Python."""
+    lib()
+    return _calls
 
 
 def last_error() -> str:
@@ -174,6 +197,12 @@ def stem_fp32(image: torch.Tensor, w: torch.Tensor, want_pre: bool = False
               ) -> Tuple[torch.Tensor, Optional[torch.Tensor]]:
     """mbu_stem_fp32: image float32 NCHW, w float32 [Co,3,3,Ci] -> (packed bits [N,H,W,Co/32],
     float32 NHWC pre-activations or None)."""
+    if not want_pre:
+        r = (_calls or _native()).stem(image, w)
+        if r.__class__ is tuple:
+            return r
+        if r is not None:
+            check(r)
     N, Ci, H, W = image.shape
     Co = w.shape[0]
     bits = torch.empty((N, H, W, Co // 32), dtype=torch.int32, device=image.device)
@@ -186,6 +215,11 @@ def stem_fp32(image: torch.Tensor, w: torch.Tensor, want_pre: bool = False
 
 def classifier_fp32(act: torch.Tensor, c: int, w: torch.Tensor, b: torch.Tensor) -> torch.Tensor:
     """mbu_classifier_fp32: packed bits [N,H,W,C/32], w [K,C], b [K] -> float32 logits NCHW."""
+    r = (_calls or _native()).classifier(act, c, w, b)
+    if r.__class__ is torch.Tensor:
+        return r
+    if r is not None:
+        check(r)
     N, H, W, _ = act.shape
     K = w.shape[0]
     out = torch.empty((N, K, H, W), dtype=torch.float32, device=act.device)
@@ -235,6 +269,11 @@ def cost_rank(n_ops, n_params, w_op: float = 0.5):
 # Packed words are stored in int32 tensors (same bits as the ABI's uint32).
 def pack_act(x: torch.Tensor) -> torch.Tensor:
     """mbu_pack_act: NHWC int8 (bit = v > 0) or float32 (bit = v >= 0) -> [N,H,W,ceil(C/32)]."""
+    r = (_calls or _native()).pack(x)
+    if r.__class__ is torch.Tensor:
+        return r
+    if r is not None:
+        check(r)
     N, H, W, C = x.shape
     dt = 0 if x.dtype == torch.int8 else 1
     out = torch.empty((N, H, W, (C + 31) // 32), dtype=torch.int32, device=x.device)
@@ -266,6 +305,12 @@ def conv3x3_masked_binary(act: torch.Tensor, cin: int, packed_w: torch.Tensor, c
                           out_acc: Optional[torch.Tensor] = None
                           ) -> Tuple[Optional[torch.Tensor], Optional[torch.Tensor]]:
     """mbu_conv3x3_masked_binary -> (packed bits [N,H,W,Cout/32] or None, int32 acc NHWC or None)."""
+    if want_bits and not want_acc and out_bits is None and out_acc is None:
+        r = (_calls or _native()).conv(act, cin, packed_w, cout, thresh)
+        if r.__class__ is tuple:
+            return r
+        if r is not None:
+            check(r)
     N, H, W, _ = act.shape
     if want_bits and out_bits is None:
         out_bits = torch.empty((N, H, W, cout // 32), dtype=torch.int32, device=act.device)
@@ -284,6 +329,12 @@ def conv3x3_masked_binary_fused(act: torch.Tensor, ca: int, low: Optional[torch.
                                 want_bits: bool = True, want_pool: bool = False
                                 ) -> Tuple[Optional[torch.Tensor], Optional[torch.Tensor]]:
     """mbu_conv3x3_masked_binary_fused -> (packed bits or None, 2x2-pooled packed bits or None)."""
+    if want_bits:
+        r = (_calls or _native()).fused(act, ca, low, clow, False, packed_w, cout, thresh, bool(want_pool))
+        if r.__class__ is tuple:
+            return r
+        if r is not None:
+            check(r)
     N, H, W, _ = act.shape
     out_bits = (torch.empty((N, H, W, cout // 32), dtype=torch.int32, device=act.device)
                 if want_bits else None)
@@ -301,6 +352,11 @@ def conv3x3_masked_binary_concat(a: torch.Tensor, ca: int, b: torch.Tensor, cb: 
                                  packed_w: torch.Tensor, cout: int, thresh: torch.Tensor,
                                  want_pool: bool = False):
     """mbu_conv3x3_masked_binary_concat -> (packed bits, pooled packed bits or None)."""
+    r = (_calls or _native()).concat(a, ca, b, cb, False, packed_w, cout, thresh, bool(want_pool))
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        check(r)
     N, H, W, _ = a.shape
     out_bits = torch.empty((N, H, W, cout // 32), dtype=torch.int32, device=a.device)
     out_pool = (torch.empty((N, H // 2, W // 2, cout // 32), dtype=torch.int32, device=a.device)
@@ -317,6 +373,11 @@ def conv3x3_masked_binary_two_inputs(a: torch.Tensor, ca: int, b: torch.Tensor, 
                                      thresh: torch.Tensor, want_pool: bool = False):
     """mbu_conv3x3_masked_binary_two_inputs: b [N,Hb,Wb,ceil(cb/32)] may cover less than the
     frame of a -> (packed bits, pooled packed bits or None)."""
+    r = (_calls or _native()).two_inputs(a, ca, b, cb, bool(upsample), packed_w, cout, thresh, bool(want_pool))
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        check(r)
     N, H, W, _ = a.shape
     out_bits = torch.empty((N, H, W, cout // 32), dtype=torch.int32, device=a.device)
     out_pool = (torch.empty((N, H // 2, W // 2, cout // 32), dtype=torch.int32, device=a.device)
@@ -343,6 +404,12 @@ def pack_tconv_weights(w: torch.Tensor) -> torch.Tensor:
 def tconv2x2_masked_binary(act: torch.Tensor, cin: int, packed_w: torch.Tensor, cout: int,
                            thresh: torch.Tensor, want_bits: bool = True, want_acc: bool = False):
     """mbu_tconv2x2_masked_binary -> (packed bits [N,2H,2W,Cout/32] or None, int32 acc or None)."""
+    if want_bits and not want_acc:
+        r = (_calls or _native()).tconv(act, cin, packed_w, cout, thresh)
+        if r.__class__ is tuple:
+            return r
+        if r is not None:
+            check(r)
     N, H, W, _ = act.shape
     out_bits = (torch.empty((N, 2 * H, 2 * W, cout // 32), dtype=torch.int32, device=act.device)
                 if want_bits else None)

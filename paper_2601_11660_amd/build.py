@@ -1,13 +1,16 @@
-"""Builds the HIP library in-tree: paper_2601_11660_amd/libmbu_hip.so (gfx950 only)."""
+"""Builds the HIP library in-tree, paper_2601_11660_amd/libmbu_hip.so (gfx950 only), and the module of the
+binding's calls, paper_2601_11660_amd/_native.so (host code)."""
 import concurrent.futures
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmbu_hip.so")
+NATIVE = os.path.join(HERE, "_native.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
 
 HIPCC_FLAGS = [
@@ -33,8 +36,26 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def build_native(verbose: bool = False) -> str:
+    """Compile csrc/native_calls.cpp against the installed torch (always recompiles)."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(t, "include"),
+           "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           os.path.join(CSRC, "native_calls.cpp"), "-o", NATIVE,
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return NATIVE
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every HIP source and link the shared library (always recompiles)."""
+    """Compile every HIP source, link the shared library, and build the module of the binding's calls
+    (always recompiles)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
@@ -49,7 +70,9 @@ def build(verbose: bool = False) -> str:
 
     workers = min(8, len(os.sched_getaffinity(0)))
     with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
+        native = pool.submit(build_native, verbose)
         objs = list(pool.map(compile_one, sources()))
+        native.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
