@@ -206,18 +206,11 @@ __global__ __launch_bounds__(512) void conv_mfma_split_kernel(
             part[(r * 4 + q) * 64 + lane] =
                 make_float4(acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]);
     __syncthreads();
-    for (int u = wave; u < R * 4; u += S) {
-        const int q = u & 3;
-        float4 v = *reinterpret_cast<const float4 *>(start + 16 * half + 4 * q);
-        const float4 *src = reinterpret_cast<const float4 *>(body) + u * 64 + lane;
-        for (int s = 0; s < S; ++s) {
-            const float4 t = src[s * G::WAVE];
-            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-        }
-        const uint32_t nib = (v.x >= 0.0f ? 1u : 0u) | (v.y >= 0.0f ? 2u : 0u) | (v.z >= 0.0f ? 4u : 0u) |
-                             (v.w >= 0.0f ? 8u : 0u);
-        atomicOr(&words[(u >> 2) * 32 + col], nib << (16 * half + 4 * q));
-    }
+    const float4 *const sums = reinterpret_cast<const float4 *>(body);
+    if (log_s == 3) reduce_slices<8, R>(sums, G::WAVE, start, words, wave, lane);
+    else if (log_s == 2) reduce_slices<4, R>(sums, G::WAVE, start, words, wave, lane);
+    else if (log_s == 1) reduce_slices<2, R>(sums, G::WAVE, start, words, wave, lane);
+    else reduce_slices<1, R>(sums, G::WAVE, start, words, wave, lane);
     __syncthreads();
     const int Cow = Cout >> 5;
     if (out_bits)

@@ -79,6 +79,38 @@ __device__ __forceinline__ uint32_t finish_word32(uint32_t s0)
     return sw[0] | (sw[1] << 16);
 }
 
+// Sum over the S waves of a block that split the input channels of one tile: G groups of 32 pixels, whose 16
+// accumulators per lane lie in LDS as [wave][group][4 x float4][lane], `stride` float4 from wave to wave.  The
+// waves share the sums, Q channels of a group at a time; all S partial sums of a unit are read before the first is
+// added (with a run-time S each read waited for the one before).  Sets the bits of words[group * 32 + pixel].
+template <int S, int G>
+__device__ __forceinline__ void reduce_slices(const float4 *body, int stride, const float *start, uint32_t *words,
+                                              int wave, int lane)
+{
+    constexpr int Q = 4 * G >= S ? 4 : 2;            // channels of a unit
+    constexpr int UNITS = 16 / Q * G;
+    const int col = lane & 31, half = lane >> 5;
+    typedef float vq __attribute__((ext_vector_type(Q)));
+#pragma unroll
+    for (int i = 0; i < (UNITS + S - 1) / S; ++i) {
+        const int u = wave + i * S;
+        if (UNITS % S == 0 || u < UNITS) {
+            const int g = u / (16 / Q), c = u % (16 / Q) * Q;        // first of the unit's channels in its lane half
+            const float *src = reinterpret_cast<const float *>(body) + ((g * 4 + c / 4) * 64 + lane) * 4 + c % 4;
+            vq t[S];
+#pragma unroll
+            for (int s = 0; s < S; ++s) t[s] = *reinterpret_cast<const vq *>(src + s * stride * 4);
+            vq v = *reinterpret_cast<const vq *>(start + 16 * half + c);
+#pragma unroll
+            for (int s = 0; s < S; ++s) v += t[s];
+            uint32_t bits = 0;
+#pragma unroll
+            for (int k = 0; k < Q; ++k) bits |= (v[k] >= 0.0f ? 1u : 0u) << k;
+            atomicOr(&words[g * 32 + col], bits << (16 * half + c));
+        }
+    }
+}
+
 // Position of a pixel tile, advanced by a fixed stride without divisions: the stride is
 // split on the host into (dx, dy, dn) = stride mod tiles_x, (stride / tiles_x) mod tiles_y,
 // stride / (tiles_x * tiles_y).
