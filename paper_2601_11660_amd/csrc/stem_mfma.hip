@@ -469,18 +469,17 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 // estimate (see the kernel above).  The weights are loaded in the same order, and no value moves between
 // registers: every dword is read where the matrix instruction wants it.
 //
-// What bounds it: about 107 vector and 12 matrix instructions a tile, which overlap by a tenth (counters at
-// 32x640x959: matrix 53 %, vector 59 % of the SIMD cycles, at 1.7 GHz).  Staging a row once instead of three
-// times took 175 -> 107 vector instructions; four waves per SIMD where they get eight rows each, three
-// otherwise (9.2 against 10.4 us at 512x512).  1024x2048 36.6 -> 32.4 us back to back, 32x640x959
-// 303 -> 257, 8x1024x1024 to 128 channels 254 -> 223, 512x512 9.9 -> 9.2.  Measured and not kept: the decision of
-// row y - 1 between the matrix instructions of row y (a second set of accumulators, two waves per SIMD):
-// 38.4 us.  The undecided outputs (6 % of the tiles have one) are listed and summed 64 at a time, all
-// taps of a sum fetched at once from one base offset, and a block's waves share the preparation of the
-// weights, behind the fetches of the first image rows.  A tile with many undecided outputs
-// (non-finite or tiny windows, a weight row out of range, dense ties) sums them in the lanes that hold them, a
-// pixel's patch fetched once for all of them: with every output undecided 512x1024 x 64 takes 124 us, with 200
-// NaN pixels 46, ordinary data 14.5 (a patch fetched again for every output, a kernel row at a time: 560 and 392).
+// What bounds it: about 107 vector and 12 matrix instructions a tile, which overlap by a tenth.  Staging a row
+// once instead of three times took 175 -> 107 vector instructions.  1024x2048 36.7 -> 32.6 us back to back, 32x640x959 303 -> 265, 8x1024x1024 to 128 channels
+// 252 -> 222, 512x512 10.1 -> 9.6.  Measured and not kept: four waves per SIMD (31.9 us alone, but the layers
+// behind it get slower, see the launch); the decision of row y - 1 between the matrix instructions of row y (a
+// second set of accumulators, two waves per SIMD): 38.4 us.  The undecided outputs (6 % of the tiles have one)
+// are listed and summed 64 at a time, all taps of a sum fetched at once from one base offset, and a block's
+// waves share the preparation of the weights, behind the fetches of the first image rows.  A tile with many
+// undecided outputs (non-finite or tiny windows, a weight row out of range, dense ties) sums them in the lanes
+// that hold them, a pixel's patch fetched once for all of them: with every output undecided 512x1024 x 64 takes
+// 123 us, with 200 NaN pixels 46, ordinary data 15 (a patch fetched again for every output, a kernel row at a
+// time: 560 and 392).
 constexpr int SR_HW = 34;                    // halo pixels of a strip
 constexpr int SR_ARR = 36;                   // dwords per LDS array (34 used)
 constexpr int SR_Z = SR_ARR;                 // from P of a plane to its Z
@@ -521,7 +520,7 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t x)
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-__global__ __launch_bounds__(256, 4) void stem_rows_kernel(
+__global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     const float *__restrict__ img, uint32_t img_bytes, int H, int W, const float *__restrict__ w, int Co,
     int nchunks, int strips, int nseg, int seg_rows, int units, uint32_t *__restrict__ out)
 {
@@ -629,19 +628,14 @@ __global__ __launch_bounds__(256, 4) void stem_rows_kernel(
     }
     __syncthreads();
     if (gw >= units) return;                   // whole wave leaves; nothing is shared from here on
-    // The rare routes read the weights again behind them, so that their registers are free meanwhile (with
-    // 128 of them the sums' operands spill otherwise: 124 -> 269 us with every output undecided).
     uint4 Wh[2][2], Wl[2][2];
-    auto load_weights = [&]() {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                Wh[m][t] = wts[0][m][t][lane];
-                Wl[m][t] = wts[1][m][t][lane];
-            }
-    };
-    load_weights();
+        for (int t = 0; t < 2; ++t) {
+            Wh[m][t] = wts[0][m][t][lane];
+            Wl[m][t] = wts[1][m][t][lane];
+        }
     // (margin: the patch norm is good to 2^-10)
     const float KW = STEM_KAPPA * 1.002f * __uint_as_float(max(wnorm[0], wnorm[1]));
     const bool w_sane = (winsane[0] | winsane[1]) == 0;
@@ -839,7 +833,6 @@ __global__ __launch_bounds__(256, 4) void stem_rows_kernel(
                     }
                     ep.sg = (ep.sg & ~todo) | neg;
                 }
-                load_weights();
             }
             const uint32_t mine = dn.zero ? ~0u : ~ep.sg;   // a chain of zero terms ends at +0.0f
             const auto sw = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
@@ -940,7 +933,6 @@ __global__ __launch_bounds__(256, 4) void stem_rows_kernel(
                 else atomicAnd(word, ~(1u << (ch & 31)));   // NaN -> bit 0
             }
         qn = 0;
-        load_weights();
     };
     // four rows per trip: operand planes and fetch registers alternate, the slots rotate.  A row lists at most
     // 64 outputs.
@@ -965,14 +957,11 @@ static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int 
     const int nchunks = ceil_div(Co, 64);
     const int strips = ceil_div(W, 32);
     const long base = (long)N * strips * nchunks;
-    // as many row segments as it takes to give every wave slot of the chip one unit: four per SIMD, or three
-    // where four would leave fewer than eight rows each, whose first two cost as much as two more (512x512: 2 rows
-    // 10.4 us, 4 rows 9.2; 301x777 twice, 96 channels: 8 rows 19.1, 12 rows 19.9)
-    int seg_rows = ceil_div(H, (int)std::max(1L, 4L * 4 * 256 / base));
-    if (seg_rows < 8) {
-        seg_rows = ceil_div(H, (int)std::max(1L, 3L * 4 * 256 / base));
-        seg_rows = std::max(2, seg_rows + (seg_rows & 1));
-    }
+    // as many row segments as it takes to give every wave slot of the chip (three per SIMD) one unit.  (Four per SIMD
+    // are 2 % faster for the layer alone, but slow the layers behind it: network at 1024x2048 on changing frames 578 us
+    // with three, 588 with four.)
+    int seg_rows = ceil_div(H, (int)std::max(1L, 3L * 4 * 256 / base));
+    seg_rows = std::max(2, seg_rows + (seg_rows & 1));
     const int nseg = ceil_div(H, seg_rows);
     const long units = (long)N * strips * nseg;   // of every chunk
     if (units > 0x7fffffffL || (units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");
