@@ -248,7 +248,7 @@ def issued_ops(kernel, n, h, w, cin, cout):
     """Operations the matrix cores execute for one 3x3 layer launch.  The low-resolution decoder
     kernel contracts the up-sampled channels (two thirds of its input) with 4 summed taps
     instead of 9; every other kernel issues the layer's nominal 2 * 9 * Cin per output."""
-    if kernel in ("conv_mfma_upcat_kernel", "conv_mfma_upcat_split_kernel"):
+    if kernel in ("conv_mfma_upcat_kernel", "conv_mfma_upcat_rows2_kernel", "conv_mfma_upcat_split_kernel"):
         ca = cin // 3                      # [skip | 2x up-sampled low], low has 2 * skip channels
         return 2.0 * n * h * w * cout * (9.0 * ca + 4.0 * (cin - ca))
     return 2.0 * n * h * w * cout * 9.0 * cin

@@ -38,25 +38,26 @@
 
 namespace mbu {
 
-constexpr int UC_RW = 4;                      // low rows per block tile = output rows per wave
-constexpr int UC_A_ROWS = 2 * UC_RW + 2;      // skip window: 10 rows
-constexpr int UC_A_COLS = 66;                 //              66 pixels, 33 per column parity
+constexpr int UC_A_COLS = 66;                 // skip window: 66 pixels a row, 33 per column parity
 constexpr int UC_A_ROW = 2 * 2 * 33;          // uint4 per window row: [half][parity][33]
-constexpr int UC_B_ROWS = UC_RW + 2;          // low window: 6 rows
-constexpr int UC_B_COLS = 34;
+constexpr int UC_B_COLS = 34;                 // low window
 constexpr int UC_B_ROW = 2 * 34;              // uint4 per window row: [half][34]
-constexpr int UC_B_SLICE = UC_B_ROWS * UC_B_ROW;   // one 64-channel slice of the low window
-constexpr int UC_TILE = UC_A_ROWS * UC_A_ROW; // the larger of the two windows (2 low slices: 816)
 
-__global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
+// RW: low rows per block tile = output rows per wave
+template <int RW>
+__device__ __forceinline__ void upcat_layer(
     const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int ksA,
     int ksL, const uint4 *__restrict__ wfrag, const uint4 *__restrict__ wup, int Cout, int tiles64,
     int ptiles, TileStep tstep, const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum,
     uint32_t *__restrict__ out_bits)
 {
-    constexpr int RW = UC_RW;
+    constexpr int UC_A_ROWS = 2 * RW + 2;       // skip window
+    constexpr int UC_B_ROWS = RW + 2;           // low window
+    constexpr int UC_B_SLICE = UC_B_ROWS * UC_B_ROW;   // one 64-channel slice of the low window
+    constexpr int UC_TILE = UC_A_ROWS * UC_A_ROW;      // the larger of the two windows (two low slices: 816 for RW = 4)
     constexpr int NB = 3;                       // activation fragments in flight per wave
-    constexpr int NLA = (UC_A_ROWS * UC_A_COLS + 255) / 256;   // 3 skip pixels per thread
+    constexpr int NLA = (UC_A_ROWS * UC_A_COLS + 255) / 256;   // skip pixels per thread: 3 for RW = 4, 2 for RW = 2
+    static_assert((NLA == 2 || NLA == 3) && 2 * NLA <= 2 * RW + 1 && 2 * UC_B_SLICE <= UC_TILE, "slots and buffers");
     __shared__ uint4 tile[2][UC_TILE];
     __shared__ float4 init_tab[4][2][2][4];     // [wave][half][m][4 x 4 channels]: start values
 
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
         const int p = tid < UC_B_ROWS * UC_B_COLS ? tid : 0;
         const int r = p / UC_B_COLS, c = p - r * UC_B_COLS;
         dst01 = (uint32_t)d[0] | ((uint32_t)d[1] << 16);
-        dst2b = (uint32_t)d[2] | ((uint32_t)(r * UC_B_ROW + c) << 16);
+        dst2b = (uint32_t)d[NLA - 1] | ((uint32_t)(r * UC_B_ROW + c) << 16);
     }
     uint32_t offa[NLA], offb;     // byte offsets of the (clamped) pixels
     uint32_t inside = 0;          // bits 0..2: skip pixels inside the image; bit 3: low pixel
@@ -261,16 +262,16 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
                 }
             }
 
-        // ---- skip steps: fragment (kx, t) is window row dy + t, t = 2 r + ky; 27 fragments
+        // ---- skip steps: fragment (kx, t) is window row dy + t, t = 2 r + ky
         auto skip_step = [&](int u, auto NEXT_SKIP) {
             const int un = u + 1;                   // a skip step or the first low unit
             const uint4 *tb = tile[buf];
             stage_issue(un);
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int NF = 27;
+            constexpr int NT = 2 * RW + 1, NF = 3 * NT;
             v4i fr[NB];
             auto frag = [&](int j) {
-                const int kx = j / 9, t = j % 9;
+                const int kx = j / NT, t = j % NT;
                 const uint4 b = tb[(kx == 1 ? baseY : baseX) + (kx == 2 ? 1 : 0) + t * UC_A_ROW];
                 return (v4i){(int)b.x, (int)b.y, (int)b.z, (int)b.w};
             };
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
             for (int j = 0; j < NB; ++j) fr[j] = frag(j);
 #pragma unroll
             for (int j = 0; j < NF; ++j) {
-                const int kx = j / 9, t = j % 9;
+                const int kx = j / NT, t = j % NT;
 #pragma unroll
                 for (int ky = 0; ky < 3; ++ky) {
                     const int r2 = t - ky;
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
                 if (t >= 2 * (RW - 1)) load_w(un, kx, t - 2 * (RW - 1));
                 // the next unit's window (fetched at the start of this one): one word per slot of
                 // the last tap column, before that column's weight fetches
-                if (j >= 18 && j < 24) commit_word(NEXT_SKIP, tile[buf ^ 1], j - 18);
+                if (j >= 2 * NT && j < 2 * NT + 2 * NLA) commit_word(NEXT_SKIP, tile[buf ^ 1], j - 2 * NT);
                 __builtin_amdgcn_sched_barrier(0);
             }
             buf ^= 1;
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
         };
         for (int u = 0; u + 1 < ksA; ++u) skip_step(u, std::true_type{});
         skip_step(ksA - 1, std::false_type{});
-        // ---- low units: fragment (q, b, t) is slice q, window row dy + t, t = r + a; 20 fragments
+        // ---- low units: fragment (q, b, t) is slice q, window row dy + t, t = r + a
         auto low_unit = [&](int u, auto LAST) {
             constexpr bool last = decltype(LAST)::value;
             const int un = last ? 0 : u + 1;        // a low unit, or the next tile's first skip step
@@ -314,10 +315,10 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
             const uint4 *tb = tile[buf];
             stage_issue(un);
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int NF = 20;
+            constexpr int NT = RW + 1, NF = 4 * NT;
             v4i fr[NB];
             auto frag = [&](int j) {
-                const int q = j / 10, b = (j % 10) / 5, t = j % 5;
+                const int q = j / (2 * NT), b = j / NT % 2, t = j % NT;
                 const uint4 v = tb[q * UC_B_SLICE + baseB + b + t * UC_B_ROW];
                 return (v4i){(int)v.x, (int)v.y, (int)v.z, (int)v.w};
             };
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
             for (int j = 0; j < NB; ++j) fr[j] = frag(j);
 #pragma unroll
             for (int j = 0; j < NF; ++j) {
-                const int q = j / 10, b = (j % 10) / 5, t = j % 5;
+                const int q = j / (2 * NT), b = j / NT % 2, t = j % NT;
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
                     const int r = t - a;
@@ -345,8 +346,8 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
                     load_w(un, q == 0 ? b : (b == 0 ? 2 : a), q == 0 ? a : (b == 0 ? a : 2));
                 }
                 if (j == 0 && last) load_w(un, 2, 2);
-                // the next unit's window, one word per slot (slots t = 0 .. 2 of the second slice)
-                if (j >= 10 && t < 3) commit_word(LAST, tile[buf ^ 1], (j >= 15 ? 3 : 0) + t);
+                // the next unit's window, one word per slot (the first slots of the second slice's columns)
+                if (q == 1 && t < NLA) commit_word(LAST, tile[buf ^ 1], b * NLA + t);
                 __builtin_amdgcn_sched_barrier(0);
             }
             buf ^= 1;
@@ -378,6 +379,20 @@ __global__ __launch_bounds__(256, 2) void conv_mfma_upcat_kernel(
         cur.advance(tstep);
     }
 }
+
+// Four low rows per wave, and two (launch_conv_mfma_upcat).
+#define MBU_UPCAT_KERNEL(NAME, RW)                                                                                   \
+    __global__ __launch_bounds__(256, 2) void NAME(                                                                  \
+        const uint32_t *__restrict__ act, const uint32_t *__restrict__ low, int N, int H, int W, int ksA, int ksL,    \
+        const uint4 *__restrict__ wfrag, const uint4 *__restrict__ wup, int Cout, int tiles64, int ptiles,            \
+        TileStep tstep, const int32_t *__restrict__ thresh, const int32_t *__restrict__ wsum,                         \
+        uint32_t *__restrict__ out_bits)                                                                              \
+    {                                                                                                                 \
+        upcat_layer<RW>(act, low, N, H, W, ksA, ksL, wfrag, wup, Cout, tiles64, ptiles, tstep, thresh, wsum, out_bits); \
+    }
+MBU_UPCAT_KERNEL(conv_mfma_upcat_kernel, 4)
+MBU_UPCAT_KERNEL(conv_mfma_upcat_rows2_kernel, 2)
+#undef MBU_UPCAT_KERNEL
 
 // ---------------------------------------------------------------------------------
 // The same contraction for small layers (a 512 x 512 frame's two deepest decoder levels, every level of a
@@ -679,12 +694,13 @@ bool conv_upcat_supported(int Ca, int Clow, int N, int H, int W, const BlobLayou
            (double)L.ksteps * 32 * 1024 < lim;
 }
 
-// When, and with which tile (kernel trace, caches flushed between launches, us with the large kernel -> with
-// the best tile here):
-//  - The large kernel runs waves of 4 x 32 low pixels x one class x 64 channels.  Below 512 of them this one
-//    wins ([512 | 1024]->512 at 64x64, 256 waves, 25.5 -> 15.6; [256 | 512]->256 at 80x120, 320, 16.0 -> 13.0;
-//    [128 | 256]->128 at 120x160, 360, 11.6 -> 10.6; [64 | 128]->64 at 120x160, 180, 8.4 -> 6.5); at 512 with
-//    many steps still (128x128, 12 steps, 16.0 -> 14.5), with few no more (256x256, 3 steps, 7.8 -> 8.4).
+// When, and with which tile (us in a kernel trace):
+//  - The large kernel with two rows per wave takes 5.5 us with 3 input steps, 7.1 with 6, 10 with 12 and 16.5 with
+//    24 while its blocks have a compute unit each; this one's time grows with tiles (a group of 32 low
+//    pixels x 32 channels).  They meet at 384 tiles + 16 per step.  Large kernel -> here: [64 | 128]->64 at 128x192,
+//    384 tiles, 5.7 -> 5.6, at 128x256, 512, 5.6 -> 6.2; [128 | 256]->128 at 96x128, 384, 7.0 -> 6.8, at 96x192, 576, 7.1 ->
+//    8.2; [256 | 512]->256 at 64x128, 512, 9.8 -> 8.9, at 96x128, 768, 10.4 -> 11.4; [512 | 1024]->512 at 64x64, 512,
+//    16.2 -> 13.2, at 64x96, 768, 16.8 -> 16.6, at 64x128, 1024, 16.8 -> 21.1.
 //  - One class per wave up to 40000 matrix instructions in all ([512 | 1024]->512 at 8x12, 8704, 26.0 -> 6.0
 //    against 8.3 with four; [64 | 128]->64 at 120x160, 20400, 6.5 against 7.7), four beyond
 //    (81600, [128 | 256]->128 at 120x160, 10.6 against 11.6; 104448, 30x40, 24.9 -> 8.6 against 12.0).
@@ -696,14 +712,13 @@ struct UpSplitPlan {
 static UpSplitPlan upcat_split_plan(int N, int Hl, int Wl, int ksA, int ksL, const BlobLayout &L)
 {
     UpSplitPlan p{0, 0, 0};
-    const long other = 4L * N * ceil_div(Hl, UC_RW) * ceil_div(Wl, 32) * (L.cout_pad64 / 64);
     const int ksteps = ksA + ksL;
-    if (other > 512 || (other == 512 && ksteps < 12)) return p;
     const long g8 = (long)N * ceil_div(Wl, 8) * ceil_div(Hl, 4), g16 = (long)N * ceil_div(Wl, 16) * ceil_div(Hl, 2);
     p.tw = g8 <= g16 ? 8 : 16;
     // the grid's second and third dimension end at 65535
     if (4L * ceil_div(Wl, p.tw) > 65535 || (long)N * ceil_div(Hl, 32 / p.tw) > 65535) return p;
     const long tiles = std::min(g8, g16) * (L.cout >> 5);
+    if (tiles > 384 + 16 * ksteps) return p;
     p.nc = tiles * (36 * ksA + 16 * ksL) <= 40000 ? 1 : 4;
     const long blocks = tiles * (4 / p.nc);
     while (p.log_s < 3 && 2 << p.log_s <= ksteps && blocks * 2 << p.log_s <= 2048) ++p.log_s;
@@ -744,14 +759,28 @@ int launch_conv_mfma_upcat(const uint32_t *act, int Ca, const uint32_t *low, int
 #undef MBU_GO
     }
     const int tiles64 = L.cout_pad64 / 64;
-    const int tiles_x = ceil_div(W / 2, 32), tiles_y = ceil_div(H / 2, UC_RW);
+    // Two low rows per wave instead of four where the blocks of four leave compute units empty or with one block: while
+    // those of two have a unit each ([64 | 128]->64 at 256x256, 128 -> 256 blocks, 7.8 -> 5.9 us; [128 | 256]->128 at
+    // 128x256 10.6 -> 7.7; [256 | 512]->256 at 128x128 14.3 -> 10.1; [512 | 1024]->512 at 64x128 23.8 -> 16.8), and with few
+    // input steps, whose weights then cost less than the second wave of a SIMD gains, while they have two (256 -> 512:
+    // [64 | 128]->64 at 256x512 8.5 -> 7.8, [256 | 512]->256 at 128x256 15.2 -> 15.0, but [512 | 1024]->512 at 128x128 26.2 ->
+    // 28.3).  Beyond, the weights are fetched twice as often for nothing ([256 | 512]->256 at 160x240 23.1 -> 25.1).
+    const int tiles_x = ceil_div(W / 2, 32);
+    const long blocks2 = (long)N * ceil_div(H / 2, 2) * tiles_x * tiles64;
+    const int rw = t_cfg.tune_rw == 0 && blocks2 <= ((Ca + Clow) / 64 <= 12 ? 512 : 256) ? 2 : 4;
+    const int tiles_y = ceil_div(H / 2, rw);
     const long tiles = (long)N * tiles_y * tiles_x;
     if (tiles > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "too many tiles for one launch");
     // persistent blocks: two per compute unit in total, spread over the 64-channel tiles
     const int gx = (int)std::min(tiles, (long)std::max(1, 512 / tiles64));
     const TileStep tstep = tile_step(gx, tiles_x, tiles_y);
-    MBU_LAUNCH(conv_mfma_upcat_kernel, dim3((unsigned)gx, (unsigned)tiles64), dim3(256), 0, s, act, low, N, H, W,
-               Ca / 64, Clow / 64, wfrag, wup, L.cout, tiles64, (int)tiles, tstep, thresh, wsum, out_bits);
+    const dim3 grid((unsigned)gx, (unsigned)tiles64), block(256);
+    if (rw == 2)
+        MBU_LAUNCH(conv_mfma_upcat_rows2_kernel, grid, block, 0, s, act, low, N, H, W, Ca / 64, Clow / 64, wfrag, wup, L.cout,
+                   tiles64, (int)tiles, tstep, thresh, wsum, out_bits);
+    else
+        MBU_LAUNCH(conv_mfma_upcat_kernel, grid, block, 0, s, act, low, N, H, W, Ca / 64, Clow / 64, wfrag, wup, L.cout,
+                   tiles64, (int)tiles, tstep, thresh, wsum, out_bits);
     return check_launch("conv_mfma_upcat");
 }
 

@@ -474,6 +474,41 @@ def test_small_upsampled_decoder_layers(shape):
             assert np.array_equal(host_u32(bits), ref), mode
 
 
+@pytest.mark.parametrize("shape", [
+    # N, H, W, Ca, Clow, Cout
+    (1, 130, 140, 64, 128, 192),      # ragged both ways, one skip step
+    (2, 66, 258, 128, 256, 96),       # half a channel tile
+    (1, 62, 200, 256, 512, 224),      # 256 blocks
+    (1, 60, 126, 512, 1024, 512),     # 24 steps
+])
+def test_upsampled_decoder_kernel_with_two_rows_per_wave(shape):
+    """... against the oracle on a part of the rows, and against the block kernel and the kernel with four rows
+    per wave on all of them."""
+    N, H, W, Ca, Clow, Cout = shape
+    say(f"conv upcat two rows N={N} H={H} W={W} Ca={Ca} Clow={Clow} Cout={Cout}")
+    rng = np.random.default_rng(H * 100 + W)
+    skip = synth.pm1_bits(rng, (N, H, W, Ca))
+    low = synth.pm1_bits(rng, (N, H // 2, W // 2, Clow))
+    th = synth.thresholds(16, 0, 0, Cout, (9 * (Ca + Clow)) // 16)
+    pa, pl = B.pack_act(dev(skip)), B.pack_act(dev(low))
+    for keep in (0.6, 1.0):
+        w = synth.ternary_weights(16, 0, 0, Cout, Ca + Clow, keep)
+        if keep == 1.0:
+            w[:] = 1                      # every summed tap at its extreme
+        blob, got = B.pack_weights(dev(w)), {}
+        for mode in (0, 7, 1):
+            B.set_conv_tuning(mode)
+            got[mode], _ = B.conv3x3_masked_binary_fused(pa, Ca, pl, Clow, blob, Cout, dev(th), True, False)
+            if mode != 1:
+                assert B.last_kernel() == ("conv_mfma_upcat_kernel" if mode else "conv_mfma_upcat_rows2_kernel")
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], got[7]) and torch.equal(got[0], got[1])
+        rows = 8                          # the last ones of the last image, where the tiles end
+        x = O.concat(skip[-1:, -rows:], O.upsample2x(low[-1:, -rows // 2:]))
+        _, out_ref = O.masked_binary_layer(x, w, th)
+        assert np.array_equal(host_u32(got[0])[-1:, 1 - rows:], bitref.pack_pm1(out_ref)[:, 1:])
+
+
 TCONV_SHAPES = [
     # N, H, W, Cin, Cout
     (1, 8, 32, 128, 64),

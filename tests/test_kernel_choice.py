@@ -97,6 +97,22 @@ def test_transposed_layers(cin, kernel):
     (32, 40, 59, 1024, 512, "tconv_res_kernel<16, 1>"),
     (8, 128, 1024, 96, 64, "tconv_bits_kernel<4>"),
 ])
-def test_transposed_layers(n, h, w, cin, cout, kernel):
+def test_large_transposed_layers(n, h, w, cin, cout, kernel):
     convs = [(32, 32), (32, 32), (32, cin), (cin, cin), (32 + cout, 32), (32, 32)]
     assert choice(convs, n, 2 * h, 2 * w, 6, (cin, cout)) == kernel
+
+
+@pytest.mark.parametrize("h, w, ca, cout, kernel", [
+    (128, 192, 64, 64, "conv_mfma_upcat_split_kernel<1, 8>"),       # 384 tiles, 3 steps
+    (128, 256, 64, 64, "conv_mfma_upcat_rows2_kernel"),             # 512
+    (64, 128, 256, 256, "conv_mfma_upcat_split_kernel<4, 8>"),      # 512 tiles, 12 steps
+    (128, 128, 256, 256, "conv_mfma_upcat_rows2_kernel"),           # 256 blocks of two rows
+    (256, 512, 64, 64, "conv_mfma_upcat_rows2_kernel"),             # 512
+    (260, 512, 64, 64, "conv_mfma_upcat_kernel"),
+    (64, 96, 512, 512, "conv_mfma_upcat_split_kernel<4, 8>"),       # 768 tiles, 24 steps
+    (64, 128, 512, 512, "conv_mfma_upcat_rows2_kernel"),            # 256 blocks
+    (68, 128, 512, 512, "conv_mfma_upcat_kernel"),
+    (512, 1024, 64, 64, "conv_mfma_upcat_kernel"),
+])
+def test_rows_per_wave_of_the_up_sampled_layers(h, w, ca, cout, kernel):
+    assert up_sampled(h, w, ca, 2 * ca, cout) == kernel
