@@ -92,6 +92,14 @@ __device__ __forceinline__ float swap_add(float v)
     return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
 }
 
+// whether the values of both lane halves are all +-0 (bits: OR of their bit patterns).  A norm of 0 does not say
+// so: the squares of values below 2^-75 round to 0
+__device__ __forceinline__ bool all_zero(uint32_t bits)
+{
+    const auto sw = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+    return ((sw[0] | sw[1]) << 1) == 0;
+}
+
 template <int CI, bool WRITE_PRE>
 __global__ __launch_bounds__(256) void stem_mfma_kernel(
     const float *__restrict__ img, uint32_t img_bytes, int N, int H, int W,
@@ -125,6 +133,7 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
         const int ch = chunk * 64 + m * 32 + tile_row_to_channel(col);
         float v[NS];
         float part = 0.0f;
+        uint32_t bits = 0;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int k = 16 * (s >> 3) + 8 * half + (s & 7);
@@ -132,15 +141,17 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
             const float wv = w[ok ? (size_t)ch * KV + k : 0];   // unconditional load
             v[s] = ok ? wv : 0.0f;
             part = __builtin_fmaf(v[s], v[s], part);
+            bits |= __float_as_uint(v[s]);
         }
         const float nrm = __builtin_sqrtf(swap_add(part));      // both halves: ||w_row||_2
         const bool in_range = nrm >= 0x1p-60f && nrm <= 0x1p60f;
-        if (!(in_range || nrm == 0.0f)) w_sane = false;
+        const bool zero_row = all_zero(bits);
+        if (!(in_range || zero_row)) w_sane = false;
         const float sc = in_range ? norm_scale(nrm) : 1.0f;
         // A row of zeros gives y = +0 for every pixel (bit 1), but its estimate 0 would never
         // be decided.  Such a row gets a weight on the first padded k, where every pixel
         // supplies the constant 1 (see BIAS_PAIR below): its estimate is 2^13, far above T.
-        if (nrm == 0.0f && ch < Co && KV == 16 * (BIAS_SLOT >> 3) + 8 * half + (BIAS_SLOT & 7))
+        if (zero_row && ch < Co && KV == 16 * (BIAS_SLOT >> 3) + 8 * half + (BIAS_SLOT & 7))
             v[BIAS_SLOT] = 0x1p13f;
         row_unscale[m] = 1.0f / sc;
         rb = max(rb, __float_as_uint(nrm * sc));
@@ -236,8 +247,7 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
             asm volatile("" : "+v"(st.orb));
         } else if (p == 3) {                // both halves of the patch; the patch's scale
             const float nrm = __builtin_sqrtf(swap_add(st.n2));
-            const auto sw = __builtin_amdgcn_permlane32_swap(st.orb, st.orb, false, false);
-            const bool zero = ((sw[0] | sw[1]) << 1) == 0;
+            const bool zero = all_zero(st.orb);
             const bool in_range = nrm >= 0x1p-60f && nrm <= 0x1p60f;
             st.sc = in_range ? norm_scale(nrm) : 1.0f;
             P.nx = zero ? 0.0f : (in_range ? nrm * st.sc : __builtin_inff());
@@ -600,6 +610,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         const int ch = chunk * 64 + m * 32 + tile_row_to_channel(col);
         float v[16];
         float part = 0.0f;
+        uint32_t bits = 0;
 #pragma unroll
         for (int s = 0; s < 16; ++s) {
             const int k0 = sr_term(0, s >> 1, s & 1), k1 = sr_term(1, s >> 1, s & 1);
@@ -608,11 +619,13 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
             const float wv = w[ok ? (size_t)ch * KV + k : 0];   // unconditional load
             v[s] = ok ? wv : 0.0f;
             part = __builtin_fmaf(v[s], v[s], part);
+            bits |= __float_as_uint(v[s]);
         }
         const float nrm = __builtin_sqrtf(swap_add(part));
+        const bool zero_row = all_zero(bits);
         const bool in_range = nrm >= 0x1p-60f && nrm <= 0x1p60f;
         const float sc = in_range ? norm_scale(nrm) : 1.0f;
-        if (nrm == 0.0f && half == 1) v[10] = ch < Co ? 0x1p13f : 0x1p15f;   // the constant term (dword 5)
+        if (zero_row && half == 1) v[10] = ch < Co ? 0x1p13f : 0x1p15f;   // the constant term (dword 5)
         uint32_t h4[4], l4[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
@@ -620,7 +633,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         wts[0][m][t][lane] = make_uint4(h4[0], h4[1], h4[2], h4[3]);
         wts[1][m][t][lane] = make_uint4(l4[0], l4[1], l4[2], l4[3]);
         const uint32_t rb = wave_umax(__float_as_uint(nrm * sc));
-        const bool insane = __builtin_amdgcn_ballot_w64(!(in_range || nrm == 0.0f)) != 0;
+        const bool insane = __builtin_amdgcn_ballot_w64(!(in_range || zero_row)) != 0;
         if (t == 0 && lane == 0) {
             wnorm[m] = rb;
             winsane[m] = insane ? 1u : 0u;

@@ -1171,6 +1171,20 @@ def test_stem_degenerate_inputs(path, pname):
     check_stem(img, rng.standard_normal((Co, 3, 3, 3), dtype=np.float32), path, pname, "non-finite")
 
 
+@pytest.mark.parametrize("ci", [3, 1])
+@pytest.mark.parametrize("path,pname", STEM_PATHS)
+def test_stem_weight_rows_whose_squares_underflow(path, pname, ci):
+    """A row of weights so small that its squared norm is 0 in 32 bits is not a row of zeros: its sums
+    have a sign.  Next to real zero rows and subnormal ones."""
+    rng = np.random.default_rng(17 + ci)
+    w = rng.standard_normal((64, 3, 3, ci), dtype=np.float32)
+    for o, scale in ((3, 1e-30), (20, 2.0 ** -80), (37, 1e-41), (45, 1e-25), (50, 0.0), (63, -0.0)):
+        w[o] *= np.float32(scale)
+    w[11] = 0.0
+    w[11, 1, 1, 0] = -1e-38
+    check_stem(rng.standard_normal((1, ci, 20, 70), dtype=np.float32), w, path, pname, "rows that underflow")
+
+
 @pytest.mark.parametrize("ties", [1, 8, 64])
 def test_stem_lists_of_undecided_outputs(ties):
     """Row-walking kernel: integer images and weight rows that are the difference of two taps give
