@@ -64,6 +64,8 @@ const char *mbu_last_error(void);
  * mbu_unet_step_kernel, that the step would launch), for tests and profiles; "" if none.  Host pointer, owned by the library, valid until the next call of this
  * function on the thread. */
 const char *mbu_last_kernel(void);
+/* ... and the blocks of that launch; 0 if none. */
+long long mbu_last_blocks(void);
 
 /* Select the convolution implementation process-wide.  MBU_ERR_ARG on a bad value.
  * Thread safety of this and the other setters (mbu_set_conv_tuning, mbu_set_stem_path): the

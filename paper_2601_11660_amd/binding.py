@@ -26,7 +26,7 @@ STATIC_WORKSPACE_BYTES = 32 << 20
 BLOB_BIT_PLANES, BLOB_SUMMED_TAPS, BLOB_MATRIX, BLOB_ALL = 1, 2, 4, 7
 
 EXPORTS = [
-    "mbu_last_error", "mbu_last_kernel", "mbu_set_conv_path", "mbu_get_conv_path", "mbu_set_conv_tuning", "mbu_pack_act",
+    "mbu_last_error", "mbu_last_kernel", "mbu_last_blocks", "mbu_set_conv_path", "mbu_get_conv_path", "mbu_set_conv_tuning", "mbu_pack_act",
     "mbu_set_stem_path", "mbu_get_stem_path", "mbu_stem_fp32", "mbu_classifier_fp32",
     "mbu_fold_batchnorm", "mbu_cost_rank",
     "mbu_packed_weights_bytes", "mbu_pack_weights", "mbu_conv3x3_masked_binary",
@@ -76,6 +76,7 @@ def lib() -> ctypes.CDLL:
         L = ctypes.CDLL(LIB_PATH)
         L.mbu_last_error.restype = ctypes.c_char_p
         L.mbu_last_kernel.restype = ctypes.c_char_p
+        L.mbu_last_blocks.restype = ctypes.c_longlong
         vp, ci = ctypes.c_void_p, ctypes.c_int
         L.mbu_pack_act.argtypes = [vp, ci, ci, ci, ci, ci, vp, vp]
         L.mbu_packed_weights_bytes.argtypes = [ci, ci, ctypes.POINTER(ctypes.c_size_t)]
@@ -144,6 +145,11 @@ def last_error() -> str:
 def last_kernel() -> str:
     """Kernel, with its template arguments, that this thread's last call chose ("" if none)."""
     return lib().mbu_last_kernel().decode()
+
+
+def last_blocks() -> int:
+    """Blocks of that kernel's launch (0 if none)."""
+    return lib().mbu_last_blocks()
 
 
 def check(rc: int) -> None:

@@ -22,7 +22,7 @@ static std::atomic<int> g_conv_path{MBU_PATH_AUTO};
 static std::atomic<int> g_stem_path{MBU_STEM_AUTO};
 static std::atomic<int> g_tune_rw{0};
 
-thread_local CallCfg t_cfg = {MBU_PATH_AUTO, MBU_STEM_AUTO, 0, false, "", nullptr};
+thread_local CallCfg t_cfg = {MBU_PATH_AUTO, MBU_STEM_AUTO, 0, false, "", nullptr, 0};
 
 void begin_call(bool dry_run)
 {
@@ -32,6 +32,7 @@ void begin_call(bool dry_run)
     t_cfg.dry_run = dry_run;
     t_cfg.kernel = "";
     t_cfg.kernel_fn = nullptr;
+    t_cfg.blocks = 0;
 }
 
 int fail(int code, const char *fmt, ...)
@@ -277,6 +278,8 @@ extern "C" {
 const char *mbu_last_error(void) { return g_err; }
 
 const char *mbu_last_kernel(void) { return kernel_instance_name(t_cfg.kernel_fn); }
+
+long long mbu_last_blocks(void) { return t_cfg.blocks; }
 
 int mbu_set_conv_path(int path)
 {
@@ -660,6 +663,7 @@ namespace mbu {
 struct StepKernel {
     const char *name;
     const void *fn;
+    long long blocks;
 };
 static int walk(const mbu_unet_desc *d, const std::vector<Step> &steps, const float *image_nchw,
                 int N, int H, int W, float *logits_nchw, uint8_t *ws, hipStream_t s,
@@ -678,6 +682,7 @@ static int walk(const mbu_unet_desc *d, const std::vector<Step> &steps, const fl
             return fail(MBU_ERR_HIP, "%s: hipEventRecord failed", fn);
         t_cfg.kernel = "";
         t_cfg.kernel_fn = nullptr;
+        t_cfg.blocks = 0;
         switch (st.kind) {
         case Step::STEM:
             rc = run_stem(image_nchw, N, d->in_channels, H, W, d->stem_w, d->base, buf((int)i), nullptr, s);
@@ -731,7 +736,7 @@ static int walk(const mbu_unet_desc *d, const std::vector<Step> &steps, const fl
             break;
         }
         if (rc) return rc;
-        if (kernel_of_step) kernel_of_step[i] = StepKernel{t_cfg.kernel, t_cfg.kernel_fn};
+        if (kernel_of_step) kernel_of_step[i] = StepKernel{t_cfg.kernel, t_cfg.kernel_fn, t_cfg.blocks};
     }
     if (!dry && d->step_events && hipEventRecord((hipEvent_t)d->step_events[steps.size()], s) != hipSuccess)
         return fail(MBU_ERR_HIP, "%s: hipEventRecord failed", fn);
@@ -820,13 +825,14 @@ int mbu_unet_step_kernel(const mbu_unet_desc *d, int N, int H, int W, int step, 
     int rc = build_plan(d, N, H, W, steps, nullptr);
     if (rc) return rc;
     if (step < 0 || step >= (int)steps.size()) return fail(MBU_ERR_ARG, "%s: step %d out of range", fn, step);
-    std::vector<StepKernel> chosen(steps.size(), StepKernel{"", nullptr});
+    std::vector<StepKernel> chosen(steps.size(), StepKernel{"", nullptr, 0});
     // a dry run dereferences no device pointer; the workspace is only an address base
     rc = walk(d, steps, nullptr, N, H, W, nullptr, (uint8_t *)256, nullptr, chosen.data());
     t_cfg.dry_run = false;
     if (rc) return rc;
     *kernel = kernel_base_name(chosen[step].name);
     t_cfg.kernel_fn = chosen[step].fn;
+    t_cfg.blocks = chosen[step].blocks;
     return MBU_OK;
 }
 

@@ -23,17 +23,21 @@ struct CallCfg {
     bool dry_run;       // true: launchers choose their kernel and record its name, launch nothing
     const char *kernel; // source name of the last kernel chosen by a launcher on this thread
     const void *kernel_fn; // ... and its handle, which differs between instances of a template
+    long long blocks;   // ... and the size of its grid
 };
 extern thread_local CallCfg t_cfg;
 void begin_call(bool dry_run = false);
 
-// Launch wrapper: records which kernel was chosen; unless the call is a dry run it drops any
+inline long long grid_blocks(const dim3 &g) { return (long long)g.x * g.y * g.z; }
+
+// Launch wrapper: records which kernel was chosen, and its grid; unless the call is a dry run it drops any
 // stale error left by earlier, unrelated runtime calls (so that check_launch() reports this
 // launch only) and launches.
 #define MBU_LAUNCH(KERNEL_, grid, block, shmem, stream, ...)                         \
     do {                                                                            \
         mbu::t_cfg.kernel = #KERNEL_;                                               \
         mbu::t_cfg.kernel_fn = reinterpret_cast<const void *>(KERNEL_);              \
+        mbu::t_cfg.blocks = mbu::grid_blocks(grid);                                 \
         if (!mbu::t_cfg.dry_run) {                                                  \
             (void)hipGetLastError();                                                \
             hipLaunchKernelGGL(KERNEL_, grid, block, shmem, stream, __VA_ARGS__);    \

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 // What bounds it: about 107 vector and 12 matrix instructions a tile, which overlap by a tenth.  Staging a row
 // once instead of three times took 175 -> 107 vector instructions.  1024x2048 36.7 -> 32.6 us back to back, 32x640x959 303 -> 265, 8x1024x1024 to 128 channels
 // 252 -> 222, 512x512 10.1 -> 9.6.  Measured and not kept: four waves per SIMD (31.9 us alone, but the layers
-// behind it get slower, see the launch); the decision of row y - 1 between the matrix instructions of row y (a
+// behind it get slower, see stem_segment_rows); the decision of row y - 1 between the matrix instructions of row y (a
 // second set of accumulators, two waves per SIMD): 38.4 us.  The undecided outputs (6 % of the tiles have one)
 // are listed and summed 64 at a time, all taps of a sum fetched at once from one base offset, and a block's
 // waves share the preparation of the weights, behind the fetches of the first image rows.  A tile with many
@@ -964,17 +964,31 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
     if (qn) flush();
 }
 
+// Rows of a segment: as many segments as it takes to give every wave slot of the chip one unit, with three waves
+// per SIMD where these segments have 32 rows or more, with two below.  The layer alone takes the same time with
+// either (1024x2048 33.6 us with three, 34.1 with two, 8x480x640 38.8 and 39.4), but a network runs at the clock that
+// its power leaves it, and on frames that are not in the caches three waves cost every layer behind this one
+// 1 to 2 % of its clock (four 3 %).  Networks of 64 channels on changing frames, us with three -> with two:
+// 720x1280 369.8 -> 359.5, 1024x2048 604.4 -> 591.1, 4x480x640 466.8 -> 454.1, 8x480x640 (26 rows) 805.8 -> 796.1,
+// 3x720x1280 (30 rows) 838.0 -> 829.1.  Where segments are longer three are better: 2x1024x2048 (44 rows) 1039.9 ->
+// 1045.8, 16x480x640 (54) 1395.6 -> 1404.3, and the layer alone, 32x640x959 268 -> 282, 8x1024x1024 to 128 channels
+// 225 -> 235.  Up to 512x512 (four rows either way) and with 32 channels there is no difference beyond 0.7 %.
+static int stem_segment_rows(int H, long base)
+{
+    auto rows = [&](long waves_per_simd) {
+        const int r = ceil_div(H, (int)std::max(1L, waves_per_simd * 4 * 256 / base));
+        return std::max(2, r + (r & 1));
+    };
+    return rows(3) < 32 ? rows(2) : rows(3);
+}
+
 static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int W, const float *w, int Co,
                             uint32_t *out_bits, hipStream_t s)
 {
     const int nchunks = ceil_div(Co, 64);
     const int strips = ceil_div(W, 32);
     const long base = (long)N * strips * nchunks;
-    // as many row segments as it takes to give every wave slot of the chip (three per SIMD) one unit.  (Four per SIMD
-    // are 2 % faster for the layer alone, but slow the layers behind it: network at 1024x2048 on changing frames 578 us
-    // with three, 588 with four.)
-    int seg_rows = ceil_div(H, (int)std::max(1L, 3L * 4 * 256 / base));
-    seg_rows = std::max(2, seg_rows + (seg_rows & 1));
+    const int seg_rows = stem_segment_rows(H, base);
     const int nseg = ceil_div(H, seg_rows);
     const long units = (long)N * strips * nseg;   // of every chunk
     if (units > 0x7fffffffL || (units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");

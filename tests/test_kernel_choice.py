@@ -116,3 +116,18 @@ def test_large_transposed_layers(n, h, w, cin, cout, kernel):
 ])
 def test_rows_per_wave_of_the_up_sampled_layers(h, w, ca, cout, kernel):
     assert up_sampled(h, w, ca, 2 * ca, cout) == kernel
+
+
+@pytest.mark.parametrize("n, h, w, blocks", [
+    (1, 512, 512, 512),          # segments of 4 rows either way
+    (1, 720, 1280, 450),         # of 10 rows at three waves per SIMD: two waves
+    (1, 1024, 2048, 512),        # 22
+    (8, 480, 640, 480),          # 26
+    (2, 720, 2048, 512),         # 30
+    (2, 768, 2048, 768),         # 32: three waves
+    (2, 1024, 2048, 768),        # 44
+    (16, 480, 640, 720),         # 54
+])
+def test_waves_of_the_first_layer(n, h, w, blocks):
+    assert choice([(32, 32)] * 4 + [(64, 32), (32, 32)], n, h, w, 0) == "stem_rows_kernel"
+    assert B.last_blocks() == blocks
