@@ -1,5 +1,6 @@
 """The native calls of the binding against its general code: same outputs, same refusals."""
 import ctypes
+import struct
 
 import pytest
 import torch
@@ -47,6 +48,17 @@ def cases(device):
         ("stem", B.stem_fp32, (randn(1, 3, 10, 33), randn(64, 3, 3, 3))),
         ("classifier", B.classifier_fp32, (a, 64, randn(19, 64), randn(19))),
     ]
+
+
+def test_the_module_has_no_thread_local_storage():
+    """A library with a thread-local segment that nothing touches sends every access of torch's own
+    thread-local state down the slow path of the dynamic linker for the rest of the process."""
+    B.lib()
+    elf = open(B.NATIVE_PATH, "rb").read()
+    assert elf[:6] == b"\x7fELF\x02\x01"
+    at, (size, n) = struct.unpack_from("<Q", elf, 32)[0], struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, at + i * size)[0] for i in range(n)]
+    assert 1 in kinds and 7 not in kinds                     # PT_LOAD, PT_TLS
 
 
 def flat(r):
