@@ -87,12 +87,22 @@ void *current_stream(const at::Tensor &t)
     return p;
 }
 
-at::Tensor make(at::IntArrayRef shape, at::ScalarType dtype, const at::Tensor &like)
+at::Tensor make(at::IntArrayRef shape, at::ScalarType dtype, c10::Device device)
 {
-    return at::empty(shape, at::TensorOptions().dtype(dtype).device(like.device()));
+    return at::empty(shape, at::TensorOptions().dtype(dtype).device(device));
 }
 
-const uint32_t *words(const at::Tensor &t) { return (const uint32_t *)t.data_ptr(); }
+// What a call takes from an input.  Read while the interpreter lock is held, together with the checks:
+// another thread may give the tensor other data (x.data = y, resize_) as soon as the lock is released.
+template <typename T> struct Input {
+    const T *p;
+    int d[4];          // sizes of the first four dimensions
+    c10::Device device;
+    explicit Input(const at::Tensor &t) : p((const T *)t.data_ptr()), d{}, device(t.device())
+    {
+        for (int64_t i = 0; i < t.dim() && i < 4; ++i) d[i] = (int)t.size(i);
+    }
+};
 uint32_t *out_words(const at::Tensor &t) { return t.defined() ? (uint32_t *)t.data_ptr() : nullptr; }
 
 // the tuple of the two outputs (None for one that was not asked for), or the error code
@@ -107,7 +117,7 @@ PyObject *result(int rc, const at::Tensor &a, const at::Tensor &b)
 }
 PyObject *result(int rc, const at::Tensor &a) { return rc != MBU_OK ? PyLong_FromLong(rc) : THPVariable_Wrap(a); }
 
-// allocates and calls without the interpreter lock, as a foreign-function call does
+// allocates and calls without the interpreter lock, as a foreign-function call does: `f` reads no input tensor
 template <typename F> int unlocked(F &&f)
 {
     struct Lock {
@@ -125,12 +135,14 @@ PyObject *conv(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (n != 5 || !g.stream || !ordinary()) Py_RETURN_NONE;
     const at::Tensor *act = plain(a[0], at::kInt, 4), *w = plain(a[2], at::kByte, 0), *th = plain(a[4], at::kInt, 0);
     if (!act || !w || !th || act->dim() != 4 || !sizes_fit(*act) || !whole(a[1], cin) || !whole(a[3], cout)) Py_RETURN_NONE;
+    const Input<uint32_t> x(*act);
+    const Input<uint8_t> blob(*w);
+    const Input<int32_t> theta(*th);
     void *s = current_stream(*act);
     at::Tensor bits;
     const int rc = unlocked([&] {
-        bits = make({act->size(0), act->size(1), act->size(2), cout / 32}, at::kInt, *act);
-        return g.conv(words(*act), (int)act->size(0), (int)act->size(1), (int)act->size(2), cin, w->data_ptr(), cout,
-                      (const int32_t *)th->data_ptr(), out_words(bits), nullptr, s);
+        bits = make({x.d[0], x.d[1], x.d[2], cout / 32}, at::kInt, x.device);
+        return g.conv(x.p, x.d[0], x.d[1], x.d[2], cin, blob.p, cout, theta.p, out_words(bits), nullptr, s);
     });
     return result(rc, bits, at::Tensor());
     END_HANDLE_TH_ERRORS
@@ -144,12 +156,14 @@ PyObject *tconv(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (n != 5 || !g.stream || !ordinary()) Py_RETURN_NONE;
     const at::Tensor *act = plain(a[0], at::kInt, 4), *w = plain(a[2], at::kByte, 0), *th = plain(a[4], at::kInt, 0);
     if (!act || !w || !th || act->dim() != 4 || !sizes_fit(*act) || !whole(a[1], cin) || !whole(a[3], cout)) Py_RETURN_NONE;
+    const Input<uint32_t> x(*act);
+    const Input<uint8_t> blob(*w);
+    const Input<int32_t> theta(*th);
     void *s = current_stream(*act);
     at::Tensor bits;
     const int rc = unlocked([&] {
-        bits = make({act->size(0), 2 * act->size(1), 2 * act->size(2), cout / 32}, at::kInt, *act);
-        return g.tconv(words(*act), (int)act->size(0), (int)act->size(1), (int)act->size(2), cin, w->data_ptr(), cout,
-                       (const int32_t *)th->data_ptr(), out_words(bits), nullptr, s);
+        bits = make({x.d[0], 2LL * x.d[1], 2LL * x.d[2], cout / 32}, at::kInt, x.device);
+        return g.tconv(x.p, x.d[0], x.d[1], x.d[2], cin, blob.p, cout, theta.p, out_words(bits), nullptr, s);
     });
     return result(rc, bits, at::Tensor());
     END_HANDLE_TH_ERRORS
@@ -172,18 +186,20 @@ template <Second KIND> PyObject *two_inputs(PyObject *, PyObject *const *a, Py_s
         !whole(a[1], ca) || !whole(a[3], cb) || !whole(a[6], cout) || !PyBool_Check(a[4]) || !PyBool_Check(a[8]))
         Py_RETURN_NONE;
     const bool up = a[4] == Py_True, want_pool = a[8] == Py_True;
+    const Input<uint32_t> x(*act), y(low ? *low : *act);
+    const Input<uint8_t> blob(*w);
+    const Input<int32_t> theta(*th);
+    const uint32_t *const pb = single ? nullptr : y.p;
     void *s = current_stream(*act);
     at::Tensor bits, pool;
     const int rc = unlocked([&] {
-        const int N = (int)act->size(0), H = (int)act->size(1), W = (int)act->size(2);
-        bits = make({N, H, W, cout / 32}, at::kInt, *act);
-        if (want_pool) pool = make({N, H / 2, W / 2, cout / 32}, at::kInt, *act);
-        const uint32_t *pa = words(*act), *pb = low ? words(*low) : nullptr;
-        const int32_t *pt = (const int32_t *)th->data_ptr();
-        if (KIND == FUSED) return g.fused(pa, ca, pb, cb, N, H, W, w->data_ptr(), cout, pt, out_words(bits), out_words(pool), s);
-        if (KIND == CONCAT) return g.concat(pa, ca, pb, cb, N, H, W, w->data_ptr(), cout, pt, out_words(bits), out_words(pool), s);
-        return g.two(pa, ca, pb, cb, (int)low->size(1), (int)low->size(2), up ? 1 : 0, N, H, W, w->data_ptr(), cout, pt,
-                     out_words(bits), out_words(pool), s);
+        const int N = x.d[0], H = x.d[1], W = x.d[2];
+        bits = make({N, H, W, cout / 32}, at::kInt, x.device);
+        if (want_pool) pool = make({N, H / 2, W / 2, cout / 32}, at::kInt, x.device);
+        uint32_t *const ob = out_words(bits), *const op = out_words(pool);
+        if (KIND == FUSED) return g.fused(x.p, ca, pb, cb, N, H, W, blob.p, cout, theta.p, ob, op, s);
+        if (KIND == CONCAT) return g.concat(x.p, ca, pb, cb, N, H, W, blob.p, cout, theta.p, ob, op, s);
+        return g.two(x.p, ca, pb, cb, y.d[1], y.d[2], up ? 1 : 0, N, H, W, blob.p, cout, theta.p, ob, op, s);
     });
     return result(rc, bits, pool);
     END_HANDLE_TH_ERRORS
@@ -194,14 +210,15 @@ PyObject *pack(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     if (n != 1 || !g.stream || !ordinary()) Py_RETURN_NONE;
-    const at::Tensor *f = plain(a[0], at::kFloat, 4), *x = f ? f : plain(a[0], at::kChar, 4);
-    if (!x || x->dim() != 4 || !sizes_fit(*x)) Py_RETURN_NONE;
-    void *s = current_stream(*x);
+    const at::Tensor *f = plain(a[0], at::kFloat, 4), *t = f ? f : plain(a[0], at::kChar, 4);
+    if (!t || t->dim() != 4 || !sizes_fit(*t)) Py_RETURN_NONE;
+    const Input<char> x(*t);
+    const int dtype = f ? 1 : 0;
+    void *s = current_stream(*t);
     at::Tensor bits;
     const int rc = unlocked([&] {
-        bits = make({x->size(0), x->size(1), x->size(2), (x->size(3) + 31) / 32}, at::kInt, *x);
-        return g.pack(x->data_ptr(), f ? 1 : 0, (int)x->size(0), (int)x->size(1), (int)x->size(2), (int)x->size(3),
-                      out_words(bits), s);
+        bits = make({x.d[0], x.d[1], x.d[2], (x.d[3] + 31LL) / 32}, at::kInt, x.device);
+        return g.pack(x.p, dtype, x.d[0], x.d[1], x.d[2], x.d[3], out_words(bits), s);
     });
     return result(rc, bits);
     END_HANDLE_TH_ERRORS
@@ -212,14 +229,14 @@ PyObject *stem(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     if (n != 2 || !g.stream || !ordinary()) Py_RETURN_NONE;
-    const at::Tensor *x = plain(a[0], at::kFloat, 4), *w = plain(a[1], at::kFloat, 1);
-    if (!x || !w || x->dim() != 4 || !sizes_fit(*x) || !sizes_fit(*w)) Py_RETURN_NONE;
-    void *s = current_stream(*x);
+    const at::Tensor *image = plain(a[0], at::kFloat, 4), *wt = plain(a[1], at::kFloat, 1);
+    if (!image || !wt || image->dim() != 4 || !sizes_fit(*image) || !sizes_fit(*wt)) Py_RETURN_NONE;
+    const Input<float> x(*image), w(*wt);
+    void *s = current_stream(*image);
     at::Tensor bits;
     const int rc = unlocked([&] {
-        bits = make({x->size(0), x->size(2), x->size(3), w->size(0) / 32}, at::kInt, *x);
-        return g.stem((const float *)x->data_ptr(), (int)x->size(0), (int)x->size(1), (int)x->size(2), (int)x->size(3),
-                      (const float *)w->data_ptr(), (int)w->size(0), out_words(bits), nullptr, s);
+        bits = make({x.d[0], x.d[2], x.d[3], w.d[0] / 32}, at::kInt, x.device);
+        return g.stem(x.p, x.d[0], x.d[1], x.d[2], x.d[3], w.p, w.d[0], out_words(bits), nullptr, s);
     });
     return result(rc, bits, at::Tensor());
     END_HANDLE_TH_ERRORS
@@ -231,15 +248,15 @@ PyObject *classifier(PyObject *, PyObject *const *a, Py_ssize_t n)
     HANDLE_TH_ERRORS
     int c;
     if (n != 4 || !g.stream || !ordinary()) Py_RETURN_NONE;
-    const at::Tensor *act = plain(a[0], at::kInt, 4), *w = plain(a[2], at::kFloat, 1), *b = plain(a[3], at::kFloat, 0);
-    if (!act || !w || !b || act->dim() != 4 || !sizes_fit(*act) || !sizes_fit(*w) || !whole(a[1], c)) Py_RETURN_NONE;
+    const at::Tensor *act = plain(a[0], at::kInt, 4), *wt = plain(a[2], at::kFloat, 1), *bias = plain(a[3], at::kFloat, 0);
+    if (!act || !wt || !bias || act->dim() != 4 || !sizes_fit(*act) || !sizes_fit(*wt) || !whole(a[1], c)) Py_RETURN_NONE;
+    const Input<uint32_t> x(*act);
+    const Input<float> w(*wt), b(*bias);
     void *s = current_stream(*act);
     at::Tensor out;
     const int rc = unlocked([&] {
-        out = make({act->size(0), w->size(0), act->size(1), act->size(2)}, at::kFloat, *act);
-        return g.classifier(words(*act), (int)act->size(0), (int)act->size(1), (int)act->size(2), c,
-                            (const float *)w->data_ptr(), (const float *)b->data_ptr(), (int)w->size(0),
-                            (float *)out.data_ptr(), s);
+        out = make({x.d[0], w.d[0], x.d[1], x.d[2]}, at::kFloat, x.device);
+        return g.classifier(x.p, x.d[0], x.d[1], x.d[2], c, w.p, b.p, w.d[0], (float *)out.data_ptr(), s);
     });
     return result(rc, out);
     END_HANDLE_TH_ERRORS

@@ -1,6 +1,8 @@
 """The native calls of the binding against its general code: same outputs, same refusals."""
 import ctypes
+import itertools
 import struct
+import threading
 
 import pytest
 import torch
@@ -106,6 +108,36 @@ def test_native_calls_return_what_the_general_code_returns(name, monkeypatch):
         assert type(x) is type(y) and x.shape == y.shape and x.dtype == y.dtype and x.device == y.device
         assert x.is_contiguous() and not x.requires_grad
         assert torch.equal(x, y) and torch.equal(z, y)
+
+
+@pytest.mark.gpu
+def test_inputs_given_other_data_by_another_thread():
+    """A call takes an input as it is when it checks it: pointer and sizes belong together, whatever another
+    thread sets the tensor to meanwhile."""
+    g = torch.Generator(device="cuda").manual_seed(11)
+    small = torch.randn((1, 3, 5, 40), generator=g, device="cuda")
+    large = torch.randn((2, 60, 70, 64), generator=g, device="cuda")
+    expected = {r.shape: r for r in (B.pack_act(small), B.pack_act(large))}
+    x, stop = torch.empty(0, device="cuda"), threading.Event()
+    x.data = small
+
+    def swap():
+        for t in itertools.cycle((large, small)):
+            x.data = t
+            if stop.is_set():
+                return
+
+    other = threading.Thread(target=swap)
+    other.start()
+    try:
+        got = [B.pack_act(x) for _ in range(300)]   # (the lock comes back after 5 ms)
+    finally:
+        stop.set()
+        other.join()
+    torch.cuda.synchronize()
+    assert {r.shape for r in got} == set(expected)           # both were met
+    for r in got:
+        assert torch.equal(r, expected[r.shape])
 
 
 class Sub(torch.Tensor):
