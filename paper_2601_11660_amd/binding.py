@@ -10,6 +10,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -69,10 +70,9 @@ def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises if it has not been built."""
     global _lib, _calls
     if _lib is None:
-        for path in (LIB_PATH, NATIVE_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError(f"{path} is missing: build it first "
-                                   "(python -m paper_2601_11660_amd.build); there is no fallback path")
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError(f"{LIB_PATH} is missing: build it first "
+                               "(python -m paper_2601_11660_amd.build); there is no fallback path")
         L = ctypes.CDLL(LIB_PATH)
         L.mbu_last_error.restype = ctypes.c_char_p
         L.mbu_last_kernel.restype = ctypes.c_char_p
@@ -117,17 +117,36 @@ def lib() -> ctypes.CDLL:
         L.mbu_event_destroy.argtypes = [vp]
         L.mbu_event_record.argtypes = [vp, vp]
         L.mbu_event_elapsed_ms.argtypes = [vp, vp, ctypes.POINTER(ctypes.c_float)]
+        _calls, _lib = _load_native(L), L
+    return _lib
+
+
+class _General:
+    """Stands in for the native calls: leaves every call to the general code."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(L: ctypes.CDLL):
+    """The native calls, bound to L.  They save a call some 2 us of its host side and nothing depends on them, so
+    a module that is missing, or built for another torch, only costs a warning."""
+    if _raw_stream is None:             # (they need it)
+        return _General()
+    try:
         loader = importlib.machinery.ExtensionFileLoader(__package__ + "._native", NATIVE_PATH)
         spec = importlib.util.spec_from_loader(loader.name, loader)
         native = importlib.util.module_from_spec(spec)
         loader.exec_module(native)
-        if _raw_stream is not None:     # (without it the native calls leave everything to the code below)
-            native.bind(*(ctypes.cast(f, vp).value for f in (
-                L.mbu_conv3x3_masked_binary, L.mbu_conv3x3_masked_binary_fused, L.mbu_conv3x3_masked_binary_concat,
-                L.mbu_conv3x3_masked_binary_two_inputs, L.mbu_tconv2x2_masked_binary, L.mbu_pack_act,
-                L.mbu_stem_fp32, L.mbu_classifier_fp32)), torch._C._cuda_getDevice, _raw_stream)
-        _calls, _lib = native, L
-    return _lib
+        native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.mbu_conv3x3_masked_binary, L.mbu_conv3x3_masked_binary_fused, L.mbu_conv3x3_masked_binary_concat,
+            L.mbu_conv3x3_masked_binary_two_inputs, L.mbu_tconv2x2_masked_binary, L.mbu_pack_act,
+            L.mbu_stem_fp32, L.mbu_classifier_fp32)), torch._C._cuda_getDevice, _raw_stream)
+        return native
+    except (ImportError, OSError) as e:
+        warnings.warn(f"{NATIVE_PATH} does not load ({e}): single-layer calls take 2 us longer until it is built "
+                      "(python -m paper_2601_11660_amd.build)", RuntimeWarning, stacklevel=3)
+        return _General()
 
 
 def _native():

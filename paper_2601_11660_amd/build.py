@@ -4,6 +4,7 @@ import concurrent.futures
 import glob
 import os
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -56,9 +57,22 @@ def build_native(verbose: bool = False) -> str:
     return NATIVE
 
 
+def build_native_or_none(verbose: bool = False) -> bool:
+    """build_native() where a host compiler and the headers of Python and torch are at hand.  Elsewhere no module is
+    left behind, an older one included: the binding does without."""
+    try:
+        build_native(verbose)
+        return True
+    except (OSError, subprocess.CalledProcessError) as e:
+        print(f"no module of the binding's calls: {e}", file=sys.stderr, flush=True)
+        if os.path.exists(NATIVE):
+            os.remove(NATIVE)
+        return False
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP source, link the shared library, and build the module of the binding's calls
-    (always recompiles)."""
+    where that is possible (always recompiles)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
@@ -73,7 +87,7 @@ def build(verbose: bool = False) -> str:
 
     workers = min(8, len(os.sched_getaffinity(0)))
     with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
-        native = pool.submit(build_native, verbose)
+        native = pool.submit(build_native_or_none, verbose)
         objs = list(pool.map(compile_one, sources()))
         native.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs

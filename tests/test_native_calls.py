@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from paper_2601_11660_amd import binding as B
+from paper_2601_11660_amd import build
 
 
 class General:
@@ -15,6 +16,32 @@ class General:
 
     def __getattr__(self, name):
         return lambda *a: None
+
+
+@pytest.mark.parametrize("content", [None, b"not a library", b"\x7fELF"])
+def test_the_binding_works_without_the_module(content, tmp_path, monkeypatch):
+    """Missing or not loadable, it takes no entry point with it."""
+    path = tmp_path / "_native.so"
+    if content is not None:
+        path.write_bytes(content)
+    monkeypatch.setattr(B, "NATIVE_PATH", str(path))
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_calls", None)
+    with pytest.warns(RuntimeWarning, match="does not load"):
+        L = B.lib()
+    assert B.lib() is L and B.packed_weights_bytes(64, 64) > 0
+    for _, f, args in cases("cpu"):
+        with pytest.raises(ValueError, match="expected a device tensor"):
+            f(*args)
+
+
+def test_a_build_without_a_host_compiler_leaves_no_module(tmp_path, monkeypatch, capsys):
+    stale = tmp_path / "_native.so"
+    stale.write_bytes(b"built for another torch")
+    monkeypatch.setattr(build, "NATIVE", str(stale))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
+    assert not build.build_native_or_none()
+    assert not stale.exists() and "no module" in capsys.readouterr().err
 
 
 def cases(device):
