@@ -475,8 +475,8 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 // P[p] = channels (0, 1), Z[p] = channel 2 of pixels (p, p + 1) - and pixel j reads, for window rows 0 .. 2,
 //     h = 0:  P0[j] P0[j+1] Z0[j] Z0[j+1]  |  P0[j+2] P1[j+2]    P1[j] P1[j+1]
 //     h = 1:  P2[j] P2[j+1] Z2[j] Z2[j+1]  |  P2[j+2] (1.0, 0)   Z1[j] Z1[j+1]
-// (the first value of a Z[j+1] meets weight 0).  The constant gives an all-zero weight row a decidable
-// estimate (see the kernel above).  The weights are loaded in the same order, and no value moves between
+// (the first value of a Z[j+1] meets weight 0).  The constant gives an all-zero weight row, and the rows beyond Co,
+// an estimate that is decided wherever the kept scale stands (SR_BIAS).  The weights are loaded in the same order, and no value moves between
 // registers: every dword is read where the matrix instruction wants it.
 //
 // What bounds it: about 107 vector and 12 matrix instructions a tile, which overlap by a tenth.  Staging a row
@@ -501,6 +501,10 @@ constexpr int SR_Q = SR_N + SR_ARR;          // undecided outputs that wait for 
 constexpr int SR_QCAP = 192;
 constexpr int SR_WAVE = SR_Q + SR_QCAP;      // dwords per wave
 constexpr float SR_FLOOR = 0x1p-9f;
+// Estimate of a row of zeros.  It has to exceed the largest threshold of a finite window: rows of a norm below
+// 2^13 (1.002: the margin in KW) against 27 values below 2^15
+constexpr float SR_BIAS = 0x1p15f;
+static_assert(SR_BIAS > STEM_KAPPA * 1.003f * 0x1p13f * 5.1962f * 0x1p15f + SR_FLOOR, "a row of zeros is decided everywhere");
 
 // index into the 27 weights of an output channel for half h, dword dh = 4t + d, fp16 value e;
 // -1: no term (weight 0), -2: the constant term
@@ -625,7 +629,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         const bool zero_row = all_zero(bits);
         const bool in_range = nrm >= 0x1p-60f && nrm <= 0x1p60f;
         const float sc = in_range ? norm_scale(nrm) : 1.0f;
-        if (zero_row && half == 1) v[10] = ch < Co ? 0x1p13f : 0x1p15f;   // the constant term (dword 5)
+        if (zero_row && half == 1) v[10] = SR_BIAS;              // the constant term (dword 5)
         uint32_t h4[4], l4[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d)

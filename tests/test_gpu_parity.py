@@ -1287,6 +1287,46 @@ def test_stem_tiles_with_many_undecided_outputs():
         assert time(x, w) < most * ordinary, name
 
 
+def test_stem_zero_weight_row_behind_a_bright_step():
+    """A row of zero weights is decided at once wherever the kept scale stands: at its upper end (a strip that
+    starts dark and turns 15.9 times as bright) the threshold of a flat bright patch is 1.3 times 2^13.  Undecided
+    in every pixel, the row would cost several times the layer."""
+    say("stem zero weight row behind a bright step")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.full((64, 3, 131, 1024), 255.0, device="cuda")
+    x[:, :, :2] = 16.0
+    w = torch.randn((64, 27), generator=g, device="cuda")
+    w *= 1.999 / w.norm(dim=1, keepdim=True)            # the largest scaled norm, just below 2^13
+    zero = w.clone()
+    zero[5] = 0.0
+    zero[40] = -0.0
+
+    def time(wts):
+        wts = wts.reshape(64, 3, 3, 3)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = float("inf")
+        for _ in range(5):
+            e[0].record()
+            for _ in range(10):
+                B.stem_fp32(x, wts)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 10)
+        return best
+
+    bits, _ = B.stem_fp32(x, zero.reshape(64, 3, 3, 3))
+    B.set_stem_path(B.STEM_VALU)
+    try:
+        ref, _ = B.stem_fp32(x, zero.reshape(64, 3, 3, 3))
+        torch.cuda.synchronize()
+    finally:
+        B.set_stem_path(B.STEM_AUTO)
+    assert torch.equal(bits, ref)
+    plain, with_zero = time(w), time(zero)
+    say(f"no zero row {plain * 1e3:.1f} us, two zero rows {with_zero * 1e3:.1f} us")
+    assert with_zero < 1.5 * plain
+
+
 def test_stem_full_size_frame():
     """All 134 M outputs of the benchmark frame's first layer against the oracle."""
     case = synth.unet_case(3, 0, 1, 1024, 2048, keep=0.6)
