@@ -673,6 +673,11 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         return max(max(__float_as_uint(v[0]) & 0x7fffffffu, __float_as_uint(v[1]) & 0x7fffffffu),
                    __float_as_uint(v[2]) & 0x7fffffffu);
     };
+    // trailing rows of a window that do not reach sc_lo under the scale just chosen for it (one of the three does)
+    auto rows_below = [&](const float (&v1)[3], const float (&v2)[3]) {
+        const uint32_t lo = __float_as_uint(sc_lo);
+        return __builtin_amdgcn_ballot_w64(row_bits(v2) >= lo) != 0 ? 0 : __builtin_amdgcn_ballot_w64(row_bits(v1) >= lo) != 0 ? 1 : 2;
+    };
     auto split2 = [](v2f f, uint32_t &hi, uint32_t &lo) {
         hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2h));
         // f - hi (exact: the difference has at most 24 bits) with the fp16 operand converted by
@@ -861,9 +866,8 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 
     // ---- one tile: matrix instructions of row y on planes B, between them the staging of row y + 2 (fetched
     // two tiles ago) for the tile below; then decision and store.  K: slot of row y, the first of the next window.
-    // (Running the decision of row y - 1 between the matrix instructions as well, with a second
-    // set of accumulators, measured no faster: the kernel is bound by the vector instruction
-    // count, and the waves that the smaller register count allows hide more.)
+    // (Running the decision of row y - 1 between the matrix instructions as well, with a second set of
+    // accumulators, measured slower, 38.4 us at 1024x2048: the kernel is bound by the vector instruction count.)
     int low = 0;                               // rows in a row that did not reach sc_lo
     auto tile = [&](auto kk, const int i, const Planes &B, Planes &Bn, float (&ld)[3]) {
         constexpr int K = decltype(kk)::value;
@@ -882,7 +886,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                 n_pair = stage_row(r0, wr + K * SR_SLOT);
                 n_prev = stage_row(r1, wr + (K + 1) % 4 * SR_SLOT);
                 n_pair += n_prev;
-                low = 0;
+                low = rows_below(r1, ld);
             }
         }
 
@@ -929,6 +933,7 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
         n_pair = stage_row(a[0], wr);
         n_prev = stage_row(a[1], wr + SR_SLOT);
         n_pair += n_prev;
+        low = rows_below(a[1], a[2]);
         Stage st;
         const float m = __uint_as_float(row_bits(a[2]));
 #pragma unroll

@@ -1327,6 +1327,41 @@ def test_stem_zero_weight_row_behind_a_bright_step():
     assert with_zero < 1.5 * plain
 
 
+def test_stem_scale_follows_rows_that_fade_in_two_steps():
+    """A scale is never kept for a window that lies wholly below its lower end: where it is chosen again because
+    three rows faded, and the last of them have already faded further than the first, the next row chooses again.
+    Kept for two rows more, a third of these windows would be summed output by output."""
+    say("stem scale on rows that fade in two steps")
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randn((64, 3, 131, 1024), generator=g, device="cuda")
+    fade = x * torch.tensor([1.0, 2.0 ** -12] + [2.0 ** -60] * 4, device="cuda").repeat(22)[:131, None]
+    w = torch.randn((64, 3, 3, 3), generator=g, device="cuda")
+    bits, _ = B.stem_fp32(fade, w)
+    B.set_stem_path(B.STEM_VALU)
+    try:
+        ref, _ = B.stem_fp32(fade, w)
+        torch.cuda.synchronize()
+    finally:
+        B.set_stem_path(B.STEM_AUTO)
+    assert torch.equal(bits, ref)
+
+    def time(image):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = float("inf")
+        for _ in range(5):
+            e[0].record()
+            for _ in range(10):
+                B.stem_fp32(image, w)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 10)
+        return best
+
+    ordinary, fading = time(x), time(fade)
+    say(f"ordinary {ordinary * 1e3:.1f} us, two steps {fading * 1e3:.1f} us")
+    assert fading < 2.5 * ordinary
+
+
 def test_stem_full_size_frame():
     """All 134 M outputs of the benchmark frame's first layer against the oracle."""
     case = synth.unet_case(3, 0, 1, 1024, 2048, keep=0.6)
