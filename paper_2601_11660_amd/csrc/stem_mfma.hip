@@ -464,8 +464,8 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 //     T = kappa * max_o ||w_o|| * ||s x_patch||  +  2^-9
 // (sum_k |w_k| 2^-25 <= sqrt(27) 2^13 2^-25 = 1.3e-3 < 2^-9 for rows scaled to a norm below
 // 2^13, whatever s).  Outputs with |estimate| <= T take the sequential route as before, so the bits are
-// those of the definition whatever the data; a window that holds values more than ~2^17
-// apart merely sends more of its small patches down that route.  Windows with an infinity, or with a
+// those of the definition whatever the data; patches below about 2^-4, scaled (2^15 below the window's largest
+// magnitude where the scale was chosen, 2^7 at the lower end to which it is kept), go down that route more often.  Windows with an infinity, or with a
 // largest magnitude below 2^-111, get T = +inf.  The squared patch norm is the
 // sum of three per-pixel sums of three rows exchanged through LDS; a NaN in it makes T NaN and the
 // comparison fail, which is the sequential route again.

@@ -2,16 +2,19 @@
 the first convolution in full precision; the library decides the SIGN of its float32 sums from
 a split-fp16 estimate and recomputes what the estimate cannot decide).
 
-The row-walking kernel scales a whole window (3 rows x 34 pixels x 3 channels) by one power of
-two s that brings its largest magnitude into [2^13, 2^14), splits every scaled value v into two
-fp16 terms v = h + l + r, does the same with every weight row (scaled to a Euclidean norm in
-[2^12, 2^13)), and sums the products wh*xh + wh*xl + wl*xh.  Its decision threshold assumes
+The row-walking kernel scales a strip by one power of two s.  It is chosen to bring the largest
+magnitude of a window (3 rows x 34 pixels x 3 channels) into [2^11, 2^12) and kept while that of
+the following windows stays in [2^3, 2^15).  Every scaled value v is split into two fp16 terms
+v = h + l + r, and so is every weight row (scaled to a Euclidean norm in [2^12, 2^13)); the
+estimate is the sum of the products wh*xh + wh*xl + wl*xh.  Its decision threshold assumes
     |estimate - exact| <= 3 * 2^-22 * ||w|| * ||x||  +  sqrt(27) * 2^13 * 2^-25
 for the terms the split drops (the rounding of the accumulation and of the reference chain are
 budgeted separately).  This test emulates the split with numpy's float16 (round to nearest
-even, subnormals kept, like the GPU's conversion) and checks that inequality on data whose
-magnitudes vary by up to 2^40 inside a window - the case in which the absolute term matters."""
+even, subnormals kept, like the GPU's conversion) and checks that inequality over the whole range
+of the scale, and below it, on data whose magnitudes vary by up to 2^40 inside a window - the case
+in which the absolute term matters."""
 import numpy as np
+import pytest
 
 
 def split16(v32):
@@ -26,7 +29,10 @@ def pow2_scale(target_exp, x):
     return np.exp2(target_exp - np.floor(np.log2(x)))
 
 
-def test_dropped_terms_of_the_window_scaled_split_stay_inside_the_budget():
+# exponent of a window's largest magnitude: both ends of the range in which a scale is kept, the one at which it
+# is chosen, the former target of the kernel, and two below the range
+@pytest.mark.parametrize("target", [-12, 0, 3, 7, 11, 13, 14])
+def test_dropped_terms_of_the_window_scaled_split_stay_inside_the_budget(target):
     rng = np.random.default_rng(3)
     worst_rel, worst_abs_used = 0.0, False
     for trial in range(40):
@@ -41,9 +47,9 @@ def test_dropped_terms_of_the_window_scaled_split_stay_inside_the_budget():
             win *= np.float32(2.0 ** float(rng.integers(-100, 100)))
         w = rng.standard_normal((Co, 3, 3, 3)).astype(np.float32)
         w *= np.exp2(rng.integers(-30, 31, size=(Co, 1, 1, 1))).astype(np.float32)
-        s = np.float32(pow2_scale(13, float(np.abs(win).max())))
+        s = np.float32(pow2_scale(target, float(np.abs(win).max())))
         t = (win * s).astype(np.float32)                        # exact: a power of two
-        assert 2.0 ** 13 <= np.abs(t).max() < 2.0 ** 14
+        assert 2.0 ** target <= np.abs(t).max() < 2.0 ** (target + 1)
         th, tl = split16(t)
         wn = np.sqrt((w.astype(np.float64) ** 2).reshape(Co, -1).sum(1))
         sw = pow2_scale(12, wn).astype(np.float32)
