@@ -618,7 +618,7 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
 // contracts them for all four positions: the words are fetched once, 4 KS bytes per lane (the lower lane half
 // takes the first KS words of a pixel, the upper half the others: which words pair up in a step is free), and
 // expanded once into registers that eight phases (position, 32-channel tile) read.  The weights of all positions
-// stay in LDS, shared by the eight waves of a block; a fragment feeds RGX matrix instructions, and its register
+// stay in LDS, shared by the waves of a block; a fragment feeds RGX matrix instructions, and its register
 // is refilled for a later phase as soon as the last of them has issued.  Pairs of rows alternate between two sets of
 // accumulators, so the signs of one pair are collected between the matrix instructions of the next.  Output
 // pixels 2x and 2x + 1 end in one wave: a lane half takes one of them and stores both words of the channel tile.
@@ -822,8 +822,9 @@ static int launch_tconv_wave(const uint32_t *act, int N, int H, int W, const Tco
     const long units = (long)N * tiles_y * tiles_x;
     if (units > 0x3fffffffL) return fail(MBU_ERR_SHAPE, "too many pixel groups for one launch");
     const int tiles64 = L.cout_pad64 / 64;
-    // one block of eight waves per compute unit in total, spread over the 64-channel tiles
-    const int per_tile = (int)std::min((units + WV - 1) / WV, (long)std::max(1, 256 / tiles64));
+    // one block of WV waves per compute unit in total, spread over the 64-channel tiles: with fewer units than wave
+    // slots every compute unit has some waves without a unit, instead of some compute units no block
+    const int per_tile = (int)std::min(units, (long)std::max(1, 256 / tiles64));
     const int32_t *wsum = (const int32_t *)((const uint8_t *)wfrag - L.off_f4 + L.off_sum);
     const dim3 grid((unsigned)per_tile, (unsigned)tiles64), block(64 * WV);
     const TileStep step = tile_step(per_tile * WV, tiles_x, tiles_y);
@@ -866,18 +867,17 @@ int launch_tconv_mfma(const uint32_t *act, int N, int H, int W, const TconvLayou
     const int tiles64 = L.cout_pad64 / 64;
     const double GiB = 1073741824.0;
     const bool small = (double)N * H * W * L.cin_words * 4 < GiB && (double)N * H * W * 4 * (L.cout >> 5) * 4 < GiB;
-    // Else up to 1024 input channels (16 steps of weights fit in registers) where a group of 1, 2 or 4 rows divides
-    // evenly over the block, at most five words of one pixel per thread: weights resident.  Against the
-    // kernels below: 64->64 at 8x160x239 18.5 -> 10.4 us, 192->96 at 2x160x239 11.2 -> 8.3, 320->512 at
-    // 20x872 16.2 -> 10.3, 384->192 at 4x80x80 12.5 -> 8.6, 640->320 at 8x80x119 56.9 -> 31.6 and at 16x16
-    // 8.1 -> 4.2, 768->512 at 64x64 10.5 -> 7.0.
-    // Large layers: a wave for all four positions.  It pays once the wave slots (two or three per SIMD) have more
-    // than one unit of two rows each: block of four position waves -> here, us in a kernel trace: 64->128 at 256x320, 2560
-    // units, 7.3 -> 6.8, 128->128 at 256x320, 2560, 7.9 -> 7.8, at 3x160x239, 3840, 9.8 -> 6.9, 256->128 at 256x320, 2560,
-    // 9.8 -> 7.6, at 160x160 twice, 1600, 7.0 -> 7.4, 384->192 at 160x160 twice, 2400, 12.3 -> 11.4; below it the
-    // position waves are four times as many (256->128 at 64x64, 128 units, 3.8 -> 5.4).  With eight steps the
-    // weights of a block are 64 KB and two rounds are wanted (512->256 at 160x160 twice, 3200, 14.0 -> 14.7, 512->512 at
-    // 128x256, 4096, 17.0 -> 16.1).  640 and more channels gain nothing (640->320 at 8x80x119 31.5 -> 31.0).
+    // Large layers: a wave for all four positions.  It pays where most of the wave slots (two or three per SIMD) have
+    // a unit of two rows; with fewer units the position waves, four times as many, fill the chip better.  Block of four
+    // position waves -> here, us back to back: 256->128 at 64x64, 128 units, 3.8 -> 5.4, at 64x1280 with 64 output channels,
+    // 1280, 4.7 -> 5.1, at 64x1280, 2560, 8.1 -> 6.5, at 8x160x239, 10240, 21.6 -> 17.2; 64->128 at 64x1280, 2560, 6.5 ->
+    // 5.1, 128->128 6.8 -> 5.5, at 3x160x239, 3840, 8.3 -> 6.7.  (They meet at 1300 to 1900 units; 2480 units, 64->128,
+    // still 6.5 there and 5.1 here.)  With eight steps the weights of a block are 64 KB and two rounds are wanted
+    // (512->256 at 160x160 twice, 3200, 14.0 -> 14.7, 512->512 at 128x256, 4096, 17.0 -> 16.1).  640 and more channels gain
+    // nothing (640->320 at 8x80x119 31.5 -> 31.0).
+    // Twelve waves a block up to four steps, where the registers allow three per SIMD: with eight 256->128 takes 17.9 at
+    // 8x160x239 and 8.4 at 3x160x239 instead of 17.2 and 8.0, 192->192 at 308x320 11.3 instead of 11.0; with 64 and 128
+    // input channels the two are within 2 %.
     // Units of four rows halve the reads of the weights where there are enough of them: 32x160x239, 256->128,
     // 61.0 -> 59.2 (four position waves 79.5), 32x320x479, 128->64, 79.0 -> 76.7 (98.0).
     const long units2 = (long)N * ceil_div(H, 2) * groups_x * tiles64;
@@ -897,6 +897,11 @@ int launch_tconv_mfma(const uint32_t *act, int N, int H, int W, const TconvLayou
         case 8: return launch_tconv_wave<8, 2, 8>(act, N, H, W, L, wfrag, thresh, out_bits, s);
         }
     }
+    // Else up to 1024 input channels (16 steps of weights fit in registers) where a group of 1, 2 or 4 rows divides
+    // evenly over the block, at most five words of one pixel per thread: weights resident.  Against the
+    // kernels below: 64->64 at 8x160x239 18.5 -> 10.4 us, 192->96 at 2x160x239 11.2 -> 8.3, 320->512 at
+    // 20x872 16.2 -> 10.3, 384->192 at 4x80x80 12.5 -> 8.6, 640->320 at 8x80x119 56.9 -> 31.6 and at 16x16
+    // 8.1 -> 4.2, 768->512 at 64x64 10.5 -> 7.0.
     if (!out_acc && small && L.cin_words == 2 * L.ksteps) switch (L.ksteps) {
         case 1: return launch_tconv_res<1, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);
         case 2: return launch_tconv_res<2, 4>(act, N, H, W, L, wfrag, thresh, out_bits, s);

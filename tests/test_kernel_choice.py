@@ -131,3 +131,15 @@ def test_rows_per_wave_of_the_up_sampled_layers(h, w, ca, cout, kernel):
 def test_waves_of_the_first_layer(n, h, w, blocks):
     assert choice([(32, 32)] * 4 + [(64, 32), (32, 32)], n, h, w, 0) == "stem_rows_kernel"
     assert B.last_blocks() == blocks
+
+
+@pytest.mark.parametrize("n, h, w, cin, cout, blocks", [
+    (1, 256, 320, 64, 128, 256),          # 2560 units of two rows: fewer than the 3072 wave slots
+    (1, 272, 320, 256, 128, 256),         # 2720
+    (1, 64, 1280, 256, 192, 255),         # three channel tiles of 85 blocks
+    (8, 160, 239, 256, 128, 256),
+])
+def test_large_transposed_layers_use_every_compute_unit(n, h, w, cin, cout, blocks):
+    convs = [(32, 32), (32, 32), (32, cin), (cin, cin), (32 + cout, 32), (32, 32)]
+    assert choice(convs, n, 2 * h, 2 * w, 6, (cin, cout)).startswith("tconv_wave_kernel<")
+    assert B.last_blocks() == blocks
