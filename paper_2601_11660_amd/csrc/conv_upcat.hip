@@ -765,6 +765,8 @@ int launch_conv_mfma_upcat(const uint32_t *act, int Ca, const uint32_t *low, int
     // input steps, whose weights then cost less than the second wave of a SIMD gains, while they have two (256 -> 512:
     // [64 | 128]->64 at 256x512 8.5 -> 7.8, [256 | 512]->256 at 128x256 15.2 -> 15.0, but [512 | 1024]->512 at 128x128 26.2 ->
     // 28.3).  Beyond, the weights are fetched twice as often for nothing ([256 | 512]->256 at 160x240 23.1 -> 25.1).
+    // (Kernel trace with the caches flushed between launches; back to back on warm caches 6.6 -> 5.2, 9.1 -> 6.7, 13.9 ->
+    // 9.7, 23.9 -> 17.7 and 6.7 -> 6.5, 14.8 -> 15.0.)
     const int tiles_x = ceil_div(W / 2, 32);
     const long blocks2 = (long)N * ceil_div(H / 2, 2) * tiles_x * tiles64;
     const int rw = t_cfg.tune_rw == 0 && blocks2 <= ((Ca + Clow) / 64 <= 12 ? 512 : 256) ? 2 : 4;

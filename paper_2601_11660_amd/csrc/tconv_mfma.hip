@@ -623,9 +623,11 @@ __global__ __launch_bounds__(256, 2) void tconv_res_kernel(
 // accumulators, so the signs of one pair are collected between the matrix instructions of the next.  Output
 // pixels 2x and 2x + 1 end in one wave: a lane half takes one of them and stores both words of the channel tile.
 // No barrier behind the weights.  Needs an even word count.
-// What bounds it: the matrix pipe, 75 % busy at 1.86 GHz (32x160x239, 256->128: 59 us = 5.4 PFLOP/s, the four position
-// waves above 79), next to 5.4 vector instructions per matrix instruction: 4 sign collections, 0.9 expansion (3.5
-// there), 0.5 words and stores.
+// What bounds it: the matrix pipe at the clock that the power leaves, next to 5.4 vector instructions per matrix
+// instruction (256 input channels: 4 sign collections, 0.9 expansion, 3.5 there, 0.5 words and stores).  256->128 at
+// 32x160x239: pipe 74 % busy at 1.8 GHz, 59 to 62 us = 5.2 to 5.4 PFLOP/s, the four position waves above 79 to 82; at
+// 8x160x239, whose 40 units a block leave a last round of a third: 65 %, 17.2 to 18.0 us = 4.5, 21.6 to 22.2 above.
+// With fewer channels a matrix instruction has more signs to itself: 128->64 40 % busy, 64->128 13 %.
 template <int KS, int RGX, int WV, bool EVEN>
 __global__ __launch_bounds__(64 * WV, WV / 4) void tconv_wave_kernel(
     const uint32_t *__restrict__ act, int N, int H, int W, const uint4 *__restrict__ wfrag, int Cout, int units,

@@ -4,6 +4,7 @@ import ctypes
 
 import pytest
 
+import bench
 from paper_2601_11660_amd import binding as B
 
 
@@ -143,3 +144,8 @@ def test_large_transposed_layers_use_every_compute_unit(n, h, w, cin, cout, bloc
     convs = [(32, 32), (32, 32), (32, cin), (cin, cin), (32 + cout, 32), (32, 32)]
     assert choice(convs, n, 2 * h, 2 * w, 6, (cin, cout)).startswith("tconv_wave_kernel<")
     assert B.last_blocks() == blocks
+
+
+def test_bound_that_the_benchmark_names_for_transposed_layers():
+    assert bench.tconv_bound("tconv_wave_kernel").startswith("mfma")
+    assert bench.tconv_bound("tconv_res_kernel").startswith("alu")
