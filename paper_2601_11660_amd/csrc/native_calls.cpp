@@ -1,7 +1,7 @@
 // The single-layer calls of binding.py without Python in between: argument checks, the output tensors and
 // the C-ABI call.  A call of a small layer is bound by its host side: of 6.5 us the launch takes 3.4, and in
 // Python the output tensor took 1.5, marshalling 0.6, the checks 0.5 and the stream 0.2; here all of these take 1.3
-// (a 64->64 layer at 64x64 6.6 -> 4.8 us, the other small calls 6.1-7.2 -> 4.8-5.1).
+// (a 64->64 layer at 64x64 6.6 -> 4.3 to 4.8 us, the other small calls 6.1-7.2 -> 4.8-5.1).
 //
 // Every function takes the plain case only - tensors of the exact type, on the device, contiguous, of the
 // expected dtype, no function or dispatch mode active - and returns None for anything else, so that the general
