@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(
 //
 // What bounds it: about 107 vector and 12 matrix instructions a tile, which overlap by a tenth.  Staging a row
 // once instead of three times took 175 -> 107 vector instructions.  1024x2048 36.7 -> 32.6 us back to back, 32x640x959 303 -> 265, 8x1024x1024 to 128 channels
-// 252 -> 222, 512x512 10.1 -> 9.6.  Measured and not kept: four waves per SIMD (31.9 us alone, but the layers
+// 252 -> 222, 512x512 10.1 -> 9.6 (three waves per SIMD).  Measured and not kept: four waves per SIMD (31.9 us alone, but the layers
 // behind it get slower, see stem_segment_rows); the decision of row y - 1 between the matrix instructions of row y (a
 // second set of accumulators, two waves per SIMD): 38.4 us.  The undecided outputs (6 % of the tiles have one)
 // are listed and summed 64 at a time, all taps of a sum fetched at once from one base offset, and a block's
@@ -534,7 +534,7 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t x)
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-__global__ __launch_bounds__(256, 3) void stem_rows_kernel(
+__global__ __launch_bounds__(256, 2) void stem_rows_kernel(
     const float *__restrict__ img, uint32_t img_bytes, int H, int W, const float *__restrict__ w, int Co,
     int nchunks, int strips, int nseg, int seg_rows, int units, uint32_t *__restrict__ out)
 {
@@ -912,9 +912,13 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
                     __builtin_amdgcn_sched_barrier(0);
                 }
         };
+        // (a wave in its matrix instructions goes ahead of waves in their vector instructions: 33.7 -> 32.8 us at
+        // 1024x2048, 267.6 -> 262.1 at 32x640x959; launch bounds of two waves per SIMD leave three room, 159 registers)
+        __builtin_amdgcn_s_setprio(1);
         mma(Wl, B.h);      // small terms first
         mma(Wh, B.l);
         mma(Wh, B.h);
+        __builtin_amdgcn_s_setprio(0);
         static_assert(STAGE_PIECES <= 12, "one piece per matrix instruction");
 
         const float n2 = B.ns[0] + B.ns[1] + B.ns[2];
@@ -975,20 +979,21 @@ __global__ __launch_bounds__(256, 3) void stem_rows_kernel(
 
 // Rows of a segment: as many segments as it takes to give every wave slot of the chip one unit, with three waves
 // per SIMD where these segments have 32 rows or more, with two below.  The layer alone takes the same time with
-// either (1024x2048 33.6 us with three, 34.1 with two, 8x480x640 38.8 and 39.4), but a network runs at the clock that
+// either (1024x2048 33.1 us with three, 33.7 with two, 8x480x640 38.4 and 39.5), but a network runs at the clock that
 // its power leaves it, and on frames that are not in the caches three waves cost every layer behind this one
 // 1 to 2 % of its clock (four 3 %).  Networks of 64 channels on changing frames, us with three -> with two:
 // 720x1280 369.8 -> 359.5, 1024x2048 604.4 -> 591.1, 4x480x640 466.8 -> 454.1, 8x480x640 (26 rows) 805.8 -> 796.1,
 // 3x720x1280 (30 rows) 838.0 -> 829.1.  Where segments are longer three are better: 2x1024x2048 (44 rows) 1039.9 ->
 // 1045.8, 16x480x640 (54) 1395.6 -> 1404.3, and the layer alone, 32x640x959 268 -> 282, 8x1024x1024 to 128 channels
-// 225 -> 235.  Up to 512x512 (four rows either way) and with 32 channels there is no difference beyond 0.7 %.
-static int stem_segment_rows(int H, long base)
+// 225 -> 235.  Three with 32 channels too, whose networks leave power: 720x1280 161.1 -> 162.4, the layer alone 16.1 ->
+// 17.0.  Up to 512x512 the rows are four either way.
+static int stem_segment_rows(int H, int Co, long base)
 {
     auto rows = [&](long waves_per_simd) {
         const int r = ceil_div(H, (int)std::max(1L, waves_per_simd * 4 * 256 / base));
         return std::max(2, r + (r & 1));
     };
-    return rows(3) < 32 ? rows(2) : rows(3);
+    return rows(3) < 32 && Co > 32 ? rows(2) : rows(3);
 }
 
 static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int W, const float *w, int Co,
@@ -997,7 +1002,7 @@ static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int 
     const int nchunks = ceil_div(Co, 64);
     const int strips = ceil_div(W, 32);
     const long base = (long)N * strips * nchunks;
-    const int seg_rows = stem_segment_rows(H, base);
+    const int seg_rows = stem_segment_rows(H, Co, base);
     const int nseg = ceil_div(H, seg_rows);
     const long units = (long)N * strips * nseg;   // of every chunk
     if (units > 0x7fffffffL || (units + 3) / 4 * nchunks > 0x7fffffffL) return fail(MBU_ERR_SHAPE, "stem: too many tiles for one launch");

@@ -8,12 +8,12 @@ import bench
 from paper_2601_11660_amd import binding as B
 
 
-def choice(convs, n, h, w, step, up=None):
+def choice(convs, n, h, w, step, up=None, base=32):
     d = B.UNetDesc()
     layers = (B.ConvLayer * len(convs))()
     for c, (cin, cout) in zip(layers, convs):
         c.cin, c.cout, c.packed_w, c.thresh = cin, cout, 0x10000, 0x20000
-    d.levels, d.base, d.in_channels, d.n_classes, d.convs, d.fuse = 1, 32, 3, 19, layers, 1
+    d.levels, d.base, d.in_channels, d.n_classes, d.convs, d.fuse = 1, base, 3, 19, layers, 1
     if up:
         d.up_convs = (B.ConvLayer * 1)(B.ConvLayer(0x10000, 0x20000, up[0], up[1], 0))
     name = ctypes.c_char_p()
@@ -119,18 +119,20 @@ def test_rows_per_wave_of_the_up_sampled_layers(h, w, ca, cout, kernel):
     assert up_sampled(h, w, ca, 2 * ca, cout) == kernel
 
 
-@pytest.mark.parametrize("n, h, w, blocks", [
-    (1, 512, 512, 512),          # segments of 4 rows either way
-    (1, 720, 1280, 450),         # of 10 rows at three waves per SIMD: two waves
-    (1, 1024, 2048, 512),        # 22
-    (8, 480, 640, 480),          # 26
-    (2, 720, 2048, 512),         # 30
-    (2, 768, 2048, 768),         # 32: three waves
-    (2, 1024, 2048, 768),        # 44
-    (16, 480, 640, 720),         # 54
+@pytest.mark.parametrize("n, h, w, co, blocks", [
+    (1, 512, 512, 64, 512),      # segments of 4 rows either way
+    (1, 720, 1280, 64, 450),     # of 10 rows at three waves per SIMD: two waves
+    (1, 720, 1280, 32, 720),     # 32 channels: three
+    (1, 1024, 2048, 64, 512),    # 22
+    (1, 1024, 2048, 128, 768),   # 44 in two chunks of channels: three
+    (8, 480, 640, 64, 480),      # 26
+    (2, 720, 2048, 64, 512),     # 30
+    (2, 768, 2048, 64, 768),     # 32: three waves
+    (2, 1024, 2048, 64, 768),    # 44
+    (16, 480, 640, 64, 720),     # 54
 ])
-def test_waves_of_the_first_layer(n, h, w, blocks):
-    assert choice([(32, 32)] * 4 + [(64, 32), (32, 32)], n, h, w, 0) == "stem_rows_kernel"
+def test_waves_of_the_first_layer(n, h, w, co, blocks):
+    assert choice([(co, co)] * 4 + [(2 * co, co), (co, co)], n, h, w, 0, base=co) == "stem_rows_kernel"
     assert B.last_blocks() == blocks
 
 
