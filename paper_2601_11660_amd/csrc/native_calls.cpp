@@ -100,9 +100,11 @@ template <typename T> struct Input {
     c10::Device device;
     explicit Input(const at::Tensor &t) : p((const T *)t.data_ptr()), d{}, device(t.device())
     {
-        for (int64_t i = 0; i < t.dim() && i < 4; ++i) d[i] = (int)t.size(i);
+        const at::IntArrayRef sizes = t.sizes();
+        for (size_t i = 0; i < sizes.size() && i < 4; ++i) d[i] = (int)sizes[i];
     }
 };
+template <typename T> const T *pointer(const at::Tensor &t) { return (const T *)t.data_ptr(); }
 uint32_t *out_words(const at::Tensor &t) { return t.defined() ? (uint32_t *)t.data_ptr() : nullptr; }
 
 // the tuple of the two outputs (None for one that was not asked for), or the error code
@@ -136,13 +138,13 @@ PyObject *conv(PyObject *, PyObject *const *a, Py_ssize_t n)
     const at::Tensor *act = plain(a[0], at::kInt, 4), *w = plain(a[2], at::kByte, 0), *th = plain(a[4], at::kInt, 0);
     if (!act || !w || !th || act->dim() != 4 || !sizes_fit(*act) || !whole(a[1], cin) || !whole(a[3], cout)) Py_RETURN_NONE;
     const Input<uint32_t> x(*act);
-    const Input<uint8_t> blob(*w);
-    const Input<int32_t> theta(*th);
+    const void *const blob = pointer<uint8_t>(*w);
+    const int32_t *const theta = pointer<int32_t>(*th);
     void *s = current_stream(*act);
     at::Tensor bits;
     const int rc = unlocked([&] {
         bits = make({x.d[0], x.d[1], x.d[2], cout / 32}, at::kInt, x.device);
-        return g.conv(x.p, x.d[0], x.d[1], x.d[2], cin, blob.p, cout, theta.p, out_words(bits), nullptr, s);
+        return g.conv(x.p, x.d[0], x.d[1], x.d[2], cin, blob, cout, theta, out_words(bits), nullptr, s);
     });
     return result(rc, bits, at::Tensor());
     END_HANDLE_TH_ERRORS
@@ -157,13 +159,13 @@ PyObject *tconv(PyObject *, PyObject *const *a, Py_ssize_t n)
     const at::Tensor *act = plain(a[0], at::kInt, 4), *w = plain(a[2], at::kByte, 0), *th = plain(a[4], at::kInt, 0);
     if (!act || !w || !th || act->dim() != 4 || !sizes_fit(*act) || !whole(a[1], cin) || !whole(a[3], cout)) Py_RETURN_NONE;
     const Input<uint32_t> x(*act);
-    const Input<uint8_t> blob(*w);
-    const Input<int32_t> theta(*th);
+    const void *const blob = pointer<uint8_t>(*w);
+    const int32_t *const theta = pointer<int32_t>(*th);
     void *s = current_stream(*act);
     at::Tensor bits;
     const int rc = unlocked([&] {
         bits = make({x.d[0], 2LL * x.d[1], 2LL * x.d[2], cout / 32}, at::kInt, x.device);
-        return g.tconv(x.p, x.d[0], x.d[1], x.d[2], cin, blob.p, cout, theta.p, out_words(bits), nullptr, s);
+        return g.tconv(x.p, x.d[0], x.d[1], x.d[2], cin, blob, cout, theta, out_words(bits), nullptr, s);
     });
     return result(rc, bits, at::Tensor());
     END_HANDLE_TH_ERRORS
@@ -186,9 +188,9 @@ template <Second KIND> PyObject *two_inputs(PyObject *, PyObject *const *a, Py_s
         !whole(a[1], ca) || !whole(a[3], cb) || !whole(a[6], cout) || !PyBool_Check(a[4]) || !PyBool_Check(a[8]))
         Py_RETURN_NONE;
     const bool up = a[4] == Py_True, want_pool = a[8] == Py_True;
-    const Input<uint32_t> x(*act), y(low ? *low : *act);
-    const Input<uint8_t> blob(*w);
-    const Input<int32_t> theta(*th);
+    const Input<uint32_t> x(*act), y(single ? *act : *low);
+    const void *const blob = pointer<uint8_t>(*w);
+    const int32_t *const theta = pointer<int32_t>(*th);
     const uint32_t *const pb = single ? nullptr : y.p;
     void *s = current_stream(*act);
     at::Tensor bits, pool;
@@ -197,9 +199,9 @@ template <Second KIND> PyObject *two_inputs(PyObject *, PyObject *const *a, Py_s
         bits = make({N, H, W, cout / 32}, at::kInt, x.device);
         if (want_pool) pool = make({N, H / 2, W / 2, cout / 32}, at::kInt, x.device);
         uint32_t *const ob = out_words(bits), *const op = out_words(pool);
-        if (KIND == FUSED) return g.fused(x.p, ca, pb, cb, N, H, W, blob.p, cout, theta.p, ob, op, s);
-        if (KIND == CONCAT) return g.concat(x.p, ca, pb, cb, N, H, W, blob.p, cout, theta.p, ob, op, s);
-        return g.two(x.p, ca, pb, cb, y.d[1], y.d[2], up ? 1 : 0, N, H, W, blob.p, cout, theta.p, ob, op, s);
+        if (KIND == FUSED) return g.fused(x.p, ca, pb, cb, N, H, W, blob, cout, theta, ob, op, s);
+        if (KIND == CONCAT) return g.concat(x.p, ca, pb, cb, N, H, W, blob, cout, theta, ob, op, s);
+        return g.two(x.p, ca, pb, cb, y.d[1], y.d[2], up ? 1 : 0, N, H, W, blob, cout, theta, ob, op, s);
     });
     return result(rc, bits, pool);
     END_HANDLE_TH_ERRORS
@@ -251,12 +253,13 @@ PyObject *classifier(PyObject *, PyObject *const *a, Py_ssize_t n)
     const at::Tensor *act = plain(a[0], at::kInt, 4), *wt = plain(a[2], at::kFloat, 1), *bias = plain(a[3], at::kFloat, 0);
     if (!act || !wt || !bias || act->dim() != 4 || !sizes_fit(*act) || !sizes_fit(*wt) || !whole(a[1], c)) Py_RETURN_NONE;
     const Input<uint32_t> x(*act);
-    const Input<float> w(*wt), b(*bias);
+    const Input<float> w(*wt);
+    const float *const b = pointer<float>(*bias);
     void *s = current_stream(*act);
     at::Tensor out;
     const int rc = unlocked([&] {
         out = make({x.d[0], w.d[0], x.d[1], x.d[2]}, at::kFloat, x.device);
-        return g.classifier(x.p, x.d[0], x.d[1], x.d[2], c, w.p, b.p, w.d[0], (float *)out.data_ptr(), s);
+        return g.classifier(x.p, x.d[0], x.d[1], x.d[2], c, w.p, b, w.d[0], (float *)out.data_ptr(), s);
     });
     return result(rc, out);
     END_HANDLE_TH_ERRORS

@@ -978,7 +978,7 @@ __global__ __launch_bounds__(256, 2) void stem_rows_kernel(
 }
 
 // Rows of a segment: as many segments as it takes to give every wave slot of the chip one unit, with three waves
-// per SIMD where these segments have 32 rows or more, with two below.  The layer alone takes the same time with
+// per SIMD, but with two where these segments would have 8 to 31 rows.  The layer alone takes the same time with
 // either (1024x2048 33.1 us with three, 33.7 with two, 8x480x640 38.4 and 39.5), but a network runs at the clock that
 // its power leaves it, and on frames that are not in the caches three waves cost every layer behind this one
 // 1 to 2 % of its clock (four 3 %).  Networks of 64 channels on changing frames, us with three -> with two:
@@ -986,14 +986,15 @@ __global__ __launch_bounds__(256, 2) void stem_rows_kernel(
 // 3x720x1280 (30 rows) 838.0 -> 829.1.  Where segments are longer three are better: 2x1024x2048 (44 rows) 1039.9 ->
 // 1045.8, 16x480x640 (54) 1395.6 -> 1404.3, and the layer alone, 32x640x959 268 -> 282, 8x1024x1024 to 128 channels
 // 225 -> 235.  Three with 32 channels too, whose networks leave power: 720x1280 161.1 -> 162.4, the layer alone 16.1 ->
-// 17.0.  Up to 512x512 the rows are four either way.
+// 17.0, and where segments are shorter: their passes are short of waves, not of power (480x640 195.0 and 194.9), and the
+// layer alone loses when its few rows are rounded up (2x186x334 to 128 channels, 4 -> 6 rows, 9.8 -> 10.8).
 static int stem_segment_rows(int H, int Co, long base)
 {
     auto rows = [&](long waves_per_simd) {
         const int r = ceil_div(H, (int)std::max(1L, waves_per_simd * 4 * 256 / base));
         return std::max(2, r + (r & 1));
     };
-    return rows(3) < 32 && Co > 32 ? rows(2) : rows(3);
+    return rows(3) >= 8 && rows(3) < 32 && Co > 32 ? rows(2) : rows(3);
 }
 
 static int launch_stem_rows(const float *img, uint32_t bytes, int N, int H, int W, const float *w, int Co,

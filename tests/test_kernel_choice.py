@@ -120,8 +120,11 @@ def test_rows_per_wave_of_the_up_sampled_layers(h, w, ca, cout, kernel):
 
 
 @pytest.mark.parametrize("n, h, w, co, blocks", [
-    (1, 512, 512, 64, 512),      # segments of 4 rows either way
-    (1, 720, 1280, 64, 450),     # of 10 rows at three waves per SIMD: two waves
+    (1, 512, 512, 64, 512),      # segments of 4 rows at three waves per SIMD: three waves
+    (2, 186, 334, 128, 518),     # 4
+    (2, 120, 1146, 128, 720),    # 6
+    (1, 540, 1280, 64, 450),     # 8: two
+    (1, 720, 1280, 64, 450),     # 10
     (1, 720, 1280, 32, 720),     # 32 channels: three
     (1, 1024, 2048, 64, 512),    # 22
     (1, 1024, 2048, 128, 768),   # 44 in two chunks of channels: three
